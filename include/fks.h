@@ -103,8 +103,9 @@ typedef struct fks_map fks_map;       /* opaque; owns all of its device memory *
  * alloc makes the call release everything it took and return FKS_ENOMEM
  * without writing its out-parameter.  The built object keeps a copy of the
  * struct and returns its memory through it when it is released, so `user`
- * must stay valid until then.  NULL selects hipMallocAsync / hipFreeAsync on
- * the device's default memory pool.  Both function pointers must be set
+ * must stay valid until then.  NULL selects the library's own pool of the
+ * current device, which keeps up to an eighth of the device's memory for the
+ * next builds.  Both function pointers must be set
  * (FKS_EINVAL otherwise).  The library calls them from the thread that made
  * the entry-point call.                                                       */
 typedef struct fks_allocator {
@@ -144,7 +145,7 @@ void fks_params_default(fks_params* p);
  *            values, seed, params).
  *   params : NULL for defaults.
  *   alloc  : where the map and the call's scratch live (see fks_allocator);
- *            NULL for the device's default stream-ordered pool.
+ *            NULL for the library's own stream-ordered pool.
  *   out    : receives the new map (release with fks_destroy).
  * Errors: FKS_EINVAL, FKS_ENOMEM, FKS_EDUPKEY, FKS_EBUILD, FKS_EHIP.
  */

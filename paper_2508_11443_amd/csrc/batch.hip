@@ -580,7 +580,7 @@ struct fks_batch {
     std::vector<fks::BDesc> host;   // outcome, copied back after the build
     uint64_t device_bytes;
     uint32_t schedule;
-    fks_allocator alloc;    // where the pools came from (has_alloc == 0: the default pool)
+    fks_allocator alloc;    // where the pools came from (has_alloc == 0: the library's pool)
     int has_alloc;
 };
 
@@ -726,15 +726,14 @@ extern "C" int fks_build_batch_u64(const uint64_t* d_keys, const uint32_t* d_val
     uint8_t* rank_s = (uint8_t*)dev_alloc(total ? total : 1, st);
     uint2* gscan_s = (uint2*)dev_alloc(8 * (groups ? groups : 1), st);
     Cell* grouped_s = (Cell*)dev_alloc(16 * (total ? total : 1), st);
-    auto cleanup_scratch = [&]() {
-        dev_free(d_order, st);
-        dev_free(rank_s, st);
-        dev_free(gscan_s, st);
-        dev_free(grouped_s, st);
+    std::vector<void*> wide;   // the partition passes' scratch
+    auto cleanup_scratch = [&](bool settled) {
+        for (void* p : {(void*)d_order, (void*)rank_s, (void*)gscan_s, (void*)grouped_s}) dev_free(p, st, settled);
+        for (void* p : wide) dev_free(p, st, settled);
     };
     if (!B->bdesc || !B->ldesc || !B->Cpool || !B->hdr_pool || !B->slot_pool || !d_order || !rank_s ||
         !gscan_s || !grouped_s) {
-        cleanup_scratch();
+        cleanup_scratch(false);
         batch_release(B, st);
         return FKS_ENOMEM;
     }
@@ -743,7 +742,7 @@ extern "C" int fks_build_batch_u64(const uint64_t* d_keys, const uint32_t* d_val
     hipError_t e = hipMemcpyAsync(B->bdesc, B->host.data(), sizeof(BDesc) * M, hipMemcpyHostToDevice, st);
     if (e == hipSuccess) e = hipMemcpyAsync(d_order, order.data(), 4 * M, hipMemcpyHostToDevice, st);
     if (e != hipSuccess) {
-        cleanup_scratch();
+        cleanup_scratch(false);
         batch_release(B, st);
         return hip_fail(e);
     }
@@ -805,10 +804,7 @@ extern "C" int fks_build_batch_u64(const uint64_t* d_keys, const uint32_t* d_val
                 e = hipGetLastError();
                 if (e != hipSuccess) rc = hip_fail(e);
             }
-            dev_free(d_segs, st);
-            dev_free(d_flags, st);
-            dev_free(d_cbase, st);
-            dev_free(d_scratch, st);
+            wide = {d_segs, d_flags, d_cbase, d_scratch};
         }
         if (rc == FKS_OK) {
             std::vector<uint32_t> small;
@@ -853,7 +849,7 @@ extern "C" int fks_build_batch_u64(const uint64_t* d_keys, const uint32_t* d_val
         rc = has_equal_keys(d_keys + d.key_off, d.n, nullptr, nullptr, st, &equal);
         if (rc == FKS_OK && equal) d.status = FKS_EDUPKEY;
     }
-    cleanup_scratch();
+    cleanup_scratch(rc == FKS_OK);   // the outcomes were the last thing waited for
     if (rc) {
         batch_release(B, st);
         return rc;

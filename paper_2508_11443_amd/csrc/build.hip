@@ -111,9 +111,9 @@ struct Scratch {
     Readback* host = nullptr;    // pinned
 };
 
-static void free_scratch(Scratch& w, hipStream_t st) {
-    dev_free(w.y, st);
-    dev_free(w.ctrl, st);
+static void free_scratch(Scratch& w, hipStream_t st, bool settled) {
+    dev_free(w.y, st, settled);
+    dev_free(w.ctrl, st, settled);
     w = Scratch{};
 }
 
@@ -163,7 +163,6 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
     // allocated from a bound on S; the paper's rounds need S on the host before their search
     const bool direct = P.schedule == 0;
     const PartPlan plan = part_plan(n);
-    const uint32_t Q = plan.Q;
     PartArgs a{};
     a.n = n;
     a.G = G;
@@ -177,80 +176,16 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
     std::vector<void*> owned;
     Cell* slots = nullptr;   // direct form: the cells, kept across attempts
     uint64_t cap = 0;
-    auto release = [&]() {
-        for (void* p : owned) dev_free(p, st);
+    auto release = [&](bool settled) {
+        for (void* p : owned) dev_free(p, st, settled);
         owned.clear();
     };
-    size_t total = 0;
-    auto carve = [&](size_t bytes_) {   // first pass sizes, second pass hands out addresses
-        const size_t at = total;
-        total += (bytes_ + 255) & ~(size_t)255;
-        return at;
-    };
-    // one or two passes in the direct form reserve their runs on cursors: the records then sit
-    // in fixed-capacity regions (binsA of them after a first of two passes, Q after the last)
+    // one or two passes in the direct form reserve their runs on cursors, in fixed-capacity regions
     const bool cursor = direct && (plan.passes == 1 || plan.passes == 2);
-    const uint64_t r1 = cursor ? std::max<uint64_t>(n, plan.cap1 * plan.binsA) : n;
-    const uint64_t r2 = cursor ? std::max<uint64_t>(n, plan.capQ * Q) : n;
-    const size_t o_k1 = plan.passes >= 2 ? carve(8 * r1) : 0, o_v1 = plan.passes >= 2 ? carve(4 * r1) : 0;
-    const size_t o_a1 = plan.passes >= 2 && carry ? carve(4 * r1) : 0;
-    const size_t o_k2 = plan.passes >= 1 ? carve(8 * r2) : 0, o_v2 = plan.passes >= 1 ? carve(4 * r2) : 0;
-    const size_t o_a2 = plan.passes >= 1 && carry ? carve(4 * r2) : 0;
-    const size_t o_cur1 = cursor ? carve(8 * (size_t)plan.binsA) : 0, o_cur2 = cursor ? carve(8 * (size_t)Q) : 0;
-    const size_t o_begA = cursor ? carve(8 * (size_t)plan.binsA) : 0, o_begQ = cursor ? carve(8 * (size_t)Q) : 0;
-    const size_t o_cnt = carve(4 * plan.matrix), o_off = carve(4 * plan.matrix);
-    const size_t o_tsum = carve(4 * part_scan_tiles(plan)), o_tpre = carve(8 * (part_scan_tiles(plan) + 1));
-    const size_t o_offA = carve(8 * 257), o_offQ = carve(8 * ((size_t)Q + 1)), o_sqQ = carve(4 * (size_t)Q);
-    const size_t o_offAB = plan.passes == 3 ? carve(8 * ((size_t)plan.binsAB + 1)) : 0;
-    const size_t o_cbase = carve(8 * ((size_t)Q + 1)), o_sizes = carve(4 * (size_t)Q * (kPartBuckets / 8));
-    char* base = nullptr;
-    // points the passes' buffers into the scratch at base
-    auto attach_scratch = [&]() {
-        if (plan.passes >= 2) {
-            a.k1 = (uint64_t*)(base + o_k1);
-            a.v1 = (uint32_t*)(base + o_v1);
-            if (carry) a.a1 = (uint32_t*)(base + o_a1);
-        }
-        if (plan.passes >= 1) {
-            a.k2 = (uint64_t*)(base + o_k2);
-            a.v2 = (uint32_t*)(base + o_v2);
-            if (carry) a.a2 = (uint32_t*)(base + o_a2);
-        }
-        a.cnt = (uint32_t*)(base + o_cnt);
-        a.off = (uint32_t*)(base + o_off);
-        a.tsum = (uint32_t*)(base + o_tsum);
-        a.tpre = (uint64_t*)(base + o_tpre);
-        a.offA = (uint64_t*)(base + o_offA);
-        if (plan.passes == 3) a.offAB = (uint64_t*)(base + o_offAB);
-        a.offQ = (uint64_t*)(base + o_offQ);
-        a.sqQ = (uint32_t*)(base + o_sqQ);
-        a.cbase = (uint64_t*)(base + o_cbase);
-        a.sizes = (uint32_t*)(base + o_sizes);
-        if (cursor) {
-            a.cur1 = (unsigned long long*)(base + o_cur1);
-            a.cur2 = (unsigned long long*)(base + o_cur2);
-            a.begA = (uint64_t*)(base + o_begA);
-            a.begQ = (uint64_t*)(base + o_begQ);
-        }
-    };
-    // (re)takes the scratch and points the passes' buffers into it
-    auto ensure_scratch = [&]() {
-        if (base) return true;
-        base = (char*)dev_alloc(total, st);
-        if (!base) return false;
-        owned.push_back(base);
-        attach_scratch();
-        return true;
-    };
-    auto release_scratch = [&]() {
-        release();
-        base = nullptr;
-    };
-    if (!ensure_scratch()) return FKS_ENOMEM;
-    // with the device's default pool the scratch goes back, in stream order, as soon as its
-    // last reader (the final pass) is queued: the host's wait for the outcome then ends the
-    // call with nothing left to release.  The rare second pass or attempt takes it again.
-    const bool early_release = direct && dev_pool_default();
+    char* const base = (char*)dev_alloc(part_scratch(plan, n, carry, cursor, !direct, nullptr, nullptr), st);
+    if (!base) return FKS_ENOMEM;
+    owned.push_back(base);
+    part_scratch(plan, n, carry, cursor, !direct, base, &a);
     a.overflow = &ctrl->overflow;
     a.S_dev = &ctrl->S;
     a.oversize = &ctrl->oversize;
@@ -263,7 +198,7 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
         cap = cells_guess(n, P.c);
         slots = (Cell*)dev_alloc(16 * cap, st);
         if (!slots) {
-            release();
+            release(false);
             return FKS_ENOMEM;
         }
     }
@@ -290,10 +225,6 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
                                          M->ctx_bytes, M->ctx_nbytes, n, beta, y, ctrl));
             a.keys = y;
         }
-        if (!ensure_scratch()) {
-            rc = FKS_ENOMEM;
-            break;
-        }
         PartOut o;
         if ((rc = part_prepare(a, st, o))) break;
         if (direct) {
@@ -302,7 +233,6 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
             if ((rc = part_finish(a, o, M->C, P.T, M->header, slots, &ctrl->exhausted, M->ctx_off, M->ctx_bytes,
                                   nullptr, reject, cap, st)))
                 break;
-            if (early_release) release_scratch();
             if ((rc = readback())) break;
             if (host->bad_input) {
                 rc = FKS_EINVAL;
@@ -332,18 +262,9 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
                     break;
                 }
                 hipLaunchKernelGGL(k_zero_ctrl, 1, 64, 0, st, ctrl);
-                if (!base) {
-                    // the scratch went back early: the partition passes run again into it
-                    if (!ensure_scratch()) {
-                        rc = FKS_ENOMEM;
-                        break;
-                    }
-                    if ((rc = part_prepare(a, st, o))) break;
-                }
                 if ((rc = part_finish(a, o, M->C, P.T, M->header, slots, &ctrl->exhausted, M->ctx_off,
                                       M->ctx_bytes, nullptr, reject, cap, st)))
                     break;
-                if (early_release) release_scratch();
                 if ((rc = readback())) break;
             }
             if (host->exhausted) {
@@ -361,7 +282,7 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
             M->beta = beta;
             M->max_t = host->max_t;
             M->device_bytes += 16 * cap;
-            release();
+            release(true);
             return FKS_OK;
         }
         if ((rc = readback())) break;
@@ -424,11 +345,11 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
         M->beta = beta;
         M->max_t = host->max_t;
         M->device_bytes += 16 * S;
-        release();
+        release(true);
         return FKS_OK;
     }
     drop_slots();
-    release();
+    release(false);
     if (rc) return rc;
     // every attempt was rejected: equal keys, which no attempt can separate, make it a
     // broken precondition rather than bad luck
@@ -449,7 +370,7 @@ static int build_common(fks_map* M, const uint64_t* d_keys_in, const uint32_t* d
     Scratch w;
     int rc = FKS_OK;
     auto fail = [&](int code) {
-        free_scratch(w, st);
+        free_scratch(w, st, false);
         return code;
     };
     w.ctrl = (Ctrl*)dev_alloc(sizeof(Ctrl), st);
@@ -477,7 +398,7 @@ static int build_common(fks_map* M, const uint64_t* d_keys_in, const uint32_t* d
 
     M->magic_n = fastmod_magic((uint32_t)n);
     rc = attempts_partitioned(M, d_keys_in, d_vals, d_aux_in, P, w.ctrl, w.host, w.y, st);
-    free_scratch(w, st);
+    free_scratch(w, st, rc == FKS_OK);   // an accepted attempt's outcome was the last thing waited for
     return rc;
 }
 
@@ -562,8 +483,8 @@ extern "C" int fks_build_u64_v64(const uint64_t* d_keys, const uint64_t* d_vals,
             hipLaunchKernelGGL(k_split_u64, grid_for(n, kBlock, 65536), kBlock, 0, st, d_vals, n, lo, hi);
             rc = build_common(M, d_keys, lo, hi, nullptr, nullptr, 0, P, st);
         }
-        dev_free(lo, st);
-        dev_free(hi, st);
+        dev_free(lo, st, rc == FKS_OK);
+        dev_free(hi, st, rc == FKS_OK);
     }
     if (rc) {
         release_partial(M, st);

@@ -3,8 +3,6 @@
 #include <hip/hip_runtime.h>
 
 #include <cstring>
-#include <mutex>
-#include <vector>
 
 #include "fks_internal.hpp"
 
@@ -20,24 +18,10 @@ int hip_fail(hipError_t e) {
     return FKS_EHIP;
 }
 
-static std::once_flag g_pool_once[64];
-
-static void configure_pool(int dev) {
-    // keep freed stream-ordered blocks cached in the pool instead of returning
-    // them to the driver at every synchronisation
-    hipMemPool_t pool;
-    if (hipDeviceGetDefaultMemPool(&pool, dev) == hipSuccess) {
-        uint64_t threshold = ~0ull;
-        (void)hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &threshold);
-    }
-}
-
 static thread_local const fks_allocator* tl_alloc = nullptr;
 
 AllocScope::AllocScope(const fks_allocator* a) : prev_(tl_alloc) { tl_alloc = a; }
 AllocScope::~AllocScope() { tl_alloc = prev_; }
-
-bool dev_pool_default() { return tl_alloc == nullptr; }
 
 void* dev_alloc(size_t bytes, hipStream_t s) {
     if (bytes == 0) bytes = 16;
@@ -46,17 +30,7 @@ void* dev_alloc(size_t bytes, hipStream_t s) {
         if (!p) set_hip_error(hipErrorOutOfMemory);
         return p;
     }
-    int dev = 0;
-    (void)hipGetDevice(&dev);
-    if (dev >= 0 && dev < 64) std::call_once(g_pool_once[dev], configure_pool, dev);
-    void* p = nullptr;
-    hipError_t e = hipMallocAsync(&p, bytes, s);
-    if (e != hipSuccess) {
-        set_hip_error(e);
-        (void)hipGetLastError();
-        return nullptr;
-    }
-    return p;
+    return pool_take(bytes, s);
 }
 
 // per-workgroup LDS histogram of the 4-bit bucket sizes, folded into 16 global counters
@@ -94,10 +68,10 @@ int size_histogram(const Group* header, uint64_t n, uint64_t hist[16]) {
     return e == hipSuccess ? FKS_OK : hip_fail(e);
 }
 
-void dev_free(void* p, hipStream_t s) {
+void dev_free(void* p, hipStream_t s, bool settled) {
     if (!p) return;
     if (tl_alloc) tl_alloc->free(p, (void*)s, tl_alloc->user);
-    else (void)hipFreeAsync(p, s);
+    else pool_give(p, s, settled);
 }
 
 }  // namespace fks

@@ -257,7 +257,7 @@ struct fks_map {
     uint8_t* ctx_bytes;   // bytes maps: copy of the context
     uint64_t ctx_nbytes;
     uint64_t device_bytes;
-    fks_allocator alloc;  // where the map's memory came from (has_alloc == 0: the default pool)
+    fks_allocator alloc;  // where the map's memory came from (has_alloc == 0: the library's pool)
     int has_alloc;
 };
 
@@ -269,15 +269,15 @@ int hip_fail(hipError_t e);
 
 // Device memory.  dev_alloc / dev_free go to the allocator of the innermost
 // AllocScope on the calling thread: a caller's fks_allocator, or (none, or NULL)
-// stream-ordered allocations from the device's default pool, which keeps freed
-// blocks cached for the next build.  Every entry point that allocates opens a
+// the library's own pool (pool.cpp), which keeps freed blocks for the next
+// build.  Every entry point that allocates opens a
 // scope with the caller's allocator (or, to release an object, the allocator
 // the object was built with), so all of a call's memory comes from one place.
+// settled: the host has waited for the block's last use.
 void* dev_alloc(size_t bytes, hipStream_t s);
-void dev_free(void* p, hipStream_t s);
-// the current call allocates from the device's default pool (hipMallocAsync / hipFreeAsync),
-// whose stream-ordered release may be issued while queued work still uses the memory
-bool dev_pool_default();
+void dev_free(void* p, hipStream_t s, bool settled = false);
+void* pool_take(size_t bytes, hipStream_t s);
+void pool_give(void* p, hipStream_t s, bool settled);
 class AllocScope {
   public:
     explicit AllocScope(const fks_allocator* a);

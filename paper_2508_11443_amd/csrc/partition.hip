@@ -18,6 +18,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "fks_internal.hpp"
 #include "partition.hpp"
@@ -1098,6 +1099,46 @@ PartPlan part_plan(uint64_t n) {
     uint64_t m3 = P.passes == 3 ? (uint64_t)P.binsAB * kBins * P.W3 : 0;
     P.matrix = std::max(m1, std::max(m2, m3));
     return P;
+}
+
+size_t part_scratch(const PartPlan& plan, uint64_t n, bool carry, bool cursor, bool sizes, char* base, PartArgs* a) {
+    size_t total = 0;
+    auto carve = [&](auto PartArgs::*field, size_t bytes) {
+        if (base) a->*field = reinterpret_cast<std::remove_reference_t<decltype(a->*field)>>(base + total);
+        total += (bytes + 255) & ~(size_t)255;
+    };
+    const uint64_t Q = plan.Q;
+    // the cursor form keeps its records in fixed-capacity regions (binsA of them after a first
+    // of two passes, Q after the last)
+    const uint64_t r1 = cursor ? std::max<uint64_t>(n, plan.cap1 * plan.binsA) : n;
+    const uint64_t r2 = cursor ? std::max<uint64_t>(n, plan.capQ * Q) : n;
+    if (plan.passes >= 2) {
+        carve(&PartArgs::k1, 8 * r1);
+        carve(&PartArgs::v1, 4 * r1);
+        if (carry) carve(&PartArgs::a1, 4 * r1);
+    }
+    if (plan.passes >= 1) {
+        carve(&PartArgs::k2, 8 * r2);
+        carve(&PartArgs::v2, 4 * r2);
+        if (carry) carve(&PartArgs::a2, 4 * r2);
+    }
+    if (cursor) {
+        carve(&PartArgs::cur1, 8 * (size_t)plan.binsA);
+        carve(&PartArgs::cur2, 8 * Q);
+        carve(&PartArgs::begA, 8 * (size_t)plan.binsA);
+        carve(&PartArgs::begQ, 8 * Q);
+    }
+    carve(&PartArgs::cnt, 4 * plan.matrix);
+    carve(&PartArgs::off, 4 * plan.matrix);
+    carve(&PartArgs::tsum, 4 * part_scan_tiles(plan));
+    carve(&PartArgs::tpre, 8 * (part_scan_tiles(plan) + 1));
+    carve(&PartArgs::offA, 8 * 257);
+    carve(&PartArgs::offQ, 8 * (Q + 1));
+    carve(&PartArgs::sqQ, 4 * Q);
+    if (plan.passes == 3) carve(&PartArgs::offAB, 8 * ((size_t)plan.binsAB + 1));
+    carve(&PartArgs::cbase, 8 * (Q + 1));
+    if (sizes) carve(&PartArgs::sizes, 4 * Q * kGroupsPerPart);
+    return total;
 }
 
 uint64_t exscan_tiles(uint64_t N) { return (N + kXTile - 1) / kXTile; }

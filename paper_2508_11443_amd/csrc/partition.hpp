@@ -100,6 +100,11 @@ void exscan_u32(const uint32_t* in, uint64_t N, uint32_t* tsum, uint64_t* tpre, 
 
 PartPlan part_plan(uint64_t n);
 
+// Bytes of the passes' scratch for n keys (carry: an aux word travels; cursor: the cursor
+// form's regions; sizes: the size words of the unfused form); with base given, a's scratch
+// pointers are set into it.
+size_t part_scratch(const PartPlan& plan, uint64_t n, bool carry, bool cursor, bool sizes, char* base, PartArgs* a);
+
 // The partition passes over the wide maps of a batch (attempt 0 of each).  Inputs:
 // d_keys/d_vals (the batch input), segs (nseg device descriptors), Cpool (the maps'
 // level-two triples, T per map, at index map*T), pools.  Scratch: as allocated by the

@@ -28,7 +28,7 @@ struct fks_sorted {
     int device;
     uint64_t* keys;   // n keys in layout order
     uint32_t* vals;   // their values
-    fks_allocator alloc;   // where keys and vals came from (has_alloc == 0: the default pool)
+    fks_allocator alloc;   // where keys and vals came from (has_alloc == 0: the library's pool)
     int has_alloc;
 };
 
@@ -324,21 +324,21 @@ extern "C" int fks_sorted_build_u64(const uint64_t* d_keys, const uint32_t* d_va
     uint64_t* tpre = (uint64_t*)dev_alloc(8 * (exscan_tiles(N) + 1), st);
     uint32_t* flag = (uint32_t*)dev_alloc(64, st);
     uint32_t* hflag = nullptr;
-    auto cleanup = [&]() {
+    auto cleanup = [&](bool settled) {
         for (int z = 0; z < 2; ++z) {
-            dev_free(kb[z], st);
-            dev_free(vb[z], st);
+            dev_free(kb[z], st, settled);
+            dev_free(vb[z], st, settled);
         }
-        dev_free(cnt, st);
-        dev_free(off, st);
-        dev_free(tsum, st);
-        dev_free(tpre, st);
-        dev_free(flag, st);
+        dev_free(cnt, st, settled);
+        dev_free(off, st, settled);
+        dev_free(tsum, st, settled);
+        dev_free(tpre, st, settled);
+        dev_free(flag, st, settled);
         if (hflag) (void)hipHostFree(hflag);
     };
     if (!kb[0] || !kb[1] || !vb[0] || !vb[1] || !cnt || !off || !tsum || !tpre || !flag ||
         hipHostMalloc((void**)&hflag, 4, hipHostMallocDefault) != hipSuccess) {
-        cleanup();
+        cleanup(false);
         delete S;
         return FKS_ENOMEM;
     }
@@ -380,7 +380,7 @@ extern "C" int fks_sorted_build_u64(const uint64_t* d_keys, const uint32_t* d_va
         if (e != hipSuccess) rc = hip_fail(e);
     }
     if (rc != FKS_OK) {
-        cleanup();
+        cleanup(false);
         delete S;
         return rc;
     }
@@ -389,8 +389,8 @@ extern "C" int fks_sorted_build_u64(const uint64_t* d_keys, const uint32_t* d_va
     S->vals = const_cast<uint32_t*>(vin);
     kb[cur ^ 1] = nullptr;
     vb[cur ^ 1] = nullptr;
-    cleanup();
     e = hipStreamSynchronize(st);
+    cleanup(e == hipSuccess);
     if (e != hipSuccess) {
         dev_free(S->keys, st);
         dev_free(S->vals, st);

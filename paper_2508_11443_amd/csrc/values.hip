@@ -255,7 +255,7 @@ extern "C" int fks_map_values(const fks_map* map, uint32_t op, uint64_t a, uint6
     uint32_t bad = 0;
     if (e == hipSuccess) e = hipMemcpyAsync(&bad, flag, 4, hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
-    dev_free(flag, st);
+    dev_free(flag, st, e == hipSuccess);
     if (e != hipSuccess || bad) {
         free_map(M, st);
         return e != hipSuccess ? hip_fail(e) : FKS_EINVAL;

@@ -84,7 +84,7 @@ def torch_allocator(device=None) -> Allocator:
     the stream the library names, caching_allocator_delete to release), so that a map's
     memory is visible to, and reused by, the allocator the rest of the program uses.  Each
     allocation is a call from C back into Python (a few microseconds), so builds that
-    allocate little and often may prefer the default (allocator=None: the device's
+    allocate little and often may prefer the default (allocator=None: the library's own
     stream-ordered pool)."""
     import torch
     dev = torch.cuda.current_device() if device is None else int(device)
@@ -284,7 +284,7 @@ def fks_build_u64(keys, vals, seed: int, c=None, T=None, R=None, stream=None, sc
     """from_array_nodup over n uint64 keys (device tensor, int64 or uint64) and uint32 values.
     schedule=1 searches level two with the paper's flattened rounds (same table).
     allocator: an Allocator (e.g. torch_allocator()) for the map and the build's scratch, or
-    None for the device's stream-ordered pool."""
+    None for the library's own stream-ordered pool."""
     n = keys.numel()
     if vals.numel() != n:
         raise ValueError("keys and values differ in length")
