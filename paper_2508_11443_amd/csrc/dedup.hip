@@ -1,70 +1,149 @@
 // from_array (Figure 2): the constructor that accepts repeated keys.
 //
-// The input's distinct keys are collected in a linear-probing table with
-// 64-bit compare-and-swap (load factor at most 1/2); every occurrence also
-// lowers the slot's smallest input index with an atomic minimum, so a
-// repeated key keeps the value of its first occurrence whatever the order in
-// which the threads arrive.  The occupied slots are compacted and handed to
+// The input records (key, value, input index) are moved into partitions by the radix passes
+// of partition.hip over a random level-one hash, so that all occurrences of a key lie in one
+// partition; one workgroup per pair of partitions then collects its distinct keys in an LDS
+// table, where every occurrence lowers the slot's smallest input index with an atomic minimum
+// (a repeated key keeps the value of its first occurrence, in whatever order the threads
+// arrive), and appends each key's first occurrence to a dense list.  The list is handed to
 // from_array_nodup, whose table does not depend on the order of its input.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "fks_internal.hpp"
+#include "partition.hpp"
 #include "prof.hpp"
 
 namespace fks {
 
-constexpr uint64_t kEmpty = ~0ull;   // slot marker; the key ~0 itself is tracked on the side
+constexpr uint64_t kEmpty = ~0ull;            // slot marker; the key ~0 itself is tracked on the side
+constexpr uint32_t kDdThreads = 512;
+constexpr uint32_t kDdParts = 2;              // partitions per workgroup
+constexpr uint32_t kDdSlots = 4096;           // slots of a workgroup's table (about 2048 records without repeats)
+constexpr uint32_t kDdUnroll = 4;             // records per thread in flight
+constexpr uint32_t kDdAttempts = 16;          // partition hashes tried before the build gives up
 
-__global__ void k_dd_init(unsigned long long* __restrict__ tkey, uint32_t* __restrict__ tidx, uint64_t cap,
-                          uint32_t* __restrict__ side) {
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < cap; i += (uint64_t)gridDim.x * blockDim.x) {
-        tkey[i] = kEmpty;
-        tidx[i] = 0xFFFFFFFFu;
-    }
-    if (blockIdx.x == 0 && threadIdx.x < 2) side[threadIdx.x] = threadIdx.x == 0 ? 0xFFFFFFFFu : 0u;
+// what the host reads back
+struct DdCtrl {
+    uint32_t count;      // distinct keys
+    uint32_t full;       // a workgroup's table had no room for its keys
+    uint32_t overflow;   // a region of the cursor passes overflowed
+    uint32_t pad;
+};
+
+__global__ void k_dd_clear(DdCtrl* c) {
+    if (threadIdx.x == 0) *c = DdCtrl{0, 0, 0, 0};
 }
 
-__global__ __launch_bounds__(256) void k_dd_insert(const uint64_t* __restrict__ keys, uint64_t u,
-                                                     unsigned long long* __restrict__ tkey, uint32_t* __restrict__ tidx,
-                                                     uint64_t mask, uint32_t* __restrict__ side) {
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < u; i += (uint64_t)gridDim.x * blockDim.x) {
-        const uint64_t x = keys[i];
-        if (x == kEmpty) {
-            atomicMin(&side[0], (uint32_t)i);
-            continue;
-        }
-        uint64_t h = sm_fin(x) & mask;
-        for (uint64_t probe = 0; probe <= mask; ++probe) {
-            const unsigned long long old = atomicCAS(&tkey[h], (unsigned long long)kEmpty, (unsigned long long)x);
-            if (old == kEmpty || old == x) {
-                atomicMin(&tidx[h], (uint32_t)i);
-                break;
+// Distinct keys of partitions kDdParts * blockIdx.x on.  Bound by the LDS atomics' latency and
+// by the one device atomic per workgroup that reserves its place in the list: those on one
+// address take 11.4 ns each (65536 of them 747 us), which is why a workgroup takes two
+// partitions (8192 partitions of 2^23 records: 47 us of atomics instead of 93).  A table in
+// device memory with a compare-and-swap per record and a list position per occupied slot took
+// 0.83 + 3.0 ms for 2^23 records of 2^22 keys; the two passes and this kernel take 0.2 ms.
+__global__ __launch_bounds__(kDdThreads) void k_dd_distinct(
+    const uint64_t* __restrict__ keys, const uint32_t* __restrict__ vals, const uint32_t* __restrict__ idx,
+    const uint64_t* __restrict__ qbeg, const uint64_t* __restrict__ qend, uint64_t qcap, uint32_t Q, Triple H,
+    uint64_t* __restrict__ out_keys, uint32_t* __restrict__ out_vals, uint64_t out_cap, DdCtrl* __restrict__ ctrl) {
+    __shared__ uint64_t tkey[kDdSlots];
+    __shared__ uint32_t tidx[kDdSlots];
+    __shared__ uint32_t side;       // smallest index of the key kEmpty
+    __shared__ uint32_t distinct, base, put, full;
+    const uint32_t tid = threadIdx.x;
+    for (uint32_t s = tid; s < kDdSlots; s += kDdThreads) {
+        tkey[s] = kEmpty;
+        tidx[s] = 0xFFFFFFFFu;
+    }
+    if (tid == 0) {
+        side = 0xFFFFFFFFu;
+        distinct = put = full = 0;
+    }
+    __syncthreads();
+    const uint32_t q0 = blockIdx.x * kDdParts, q1 = min(Q, q0 + kDdParts);
+    auto slot_of = [&](uint64_t x) { return mshash(H, x) >> (32 - 12); };
+    static_assert(kDdSlots == 1u << 12, "the slot hash takes 12 bits");
+    uint32_t claimed = 0;
+    for (uint32_t q = q0; q < q1; ++q) {
+        const uint64_t lo = qbeg[q], hi = qcap ? min(qend[q], lo + qcap) : qend[q];
+        for (uint64_t i0 = lo; i0 < hi; i0 += kDdThreads * kDdUnroll) {
+            uint64_t x[kDdUnroll];
+            uint32_t at[kDdUnroll];
+#pragma unroll
+            for (uint32_t k = 0; k < kDdUnroll; ++k) {
+                const uint64_t i = i0 + tid + (uint64_t)k * kDdThreads;
+                x[k] = i < hi ? keys[i] : 0;
+                at[k] = i < hi ? (idx ? idx[i] : (uint32_t)i) : 0;
             }
-            h = (h + 1) & mask;
+#pragma unroll
+            for (uint32_t k = 0; k < kDdUnroll; ++k) {
+                if (i0 + tid + (uint64_t)k * kDdThreads >= hi) continue;
+                if (x[k] == kEmpty) {
+                    if (atomicMin(&side, at[k]) == 0xFFFFFFFFu) ++claimed;
+                    continue;
+                }
+                uint32_t s = slot_of(x[k]);
+                uint32_t probe = 0;
+                for (; probe < kDdSlots; ++probe) {
+                    // a slot's key never changes once it is set: read before the swap
+                    unsigned long long old = tkey[s];
+                    if (old == kEmpty) {
+                        old = atomicCAS(reinterpret_cast<unsigned long long*>(&tkey[s]), (unsigned long long)kEmpty,
+                                        (unsigned long long)x[k]);
+                        if (old == kEmpty) ++claimed;
+                    }
+                    if (old == kEmpty || old == x[k]) {
+                        atomicMin(&tidx[s], at[k]);
+                        break;
+                    }
+                    s = (s + 1) & (kDdSlots - 1);
+                }
+                if (probe == kDdSlots) full = 1;
+            }
         }
     }
-}
-
-__global__ __launch_bounds__(256) void k_dd_compact(const unsigned long long* __restrict__ tkey,
-                                                      const uint32_t* __restrict__ tidx, uint64_t cap,
-                                                      const uint32_t* __restrict__ vals, uint64_t* __restrict__ out_keys,
-                                                      uint32_t* __restrict__ out_vals, uint32_t* __restrict__ side) {
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < cap; i += (uint64_t)gridDim.x * blockDim.x) {
-        const uint64_t x = tkey[i];
-        if (x != kEmpty) {
-            const uint32_t pos = atomicAdd(&side[1], 1u);
-            out_keys[pos] = x;
-            out_vals[pos] = vals[tidx[i]];
-        }
+    if (claimed) atomicAdd(&distinct, claimed);
+    __syncthreads();
+    if (tid == 0) {
+        base = 0;
+        if (full) atomicOr(&ctrl->full, 1u);
+        else if (distinct) base = atomicAdd(&ctrl->count, distinct);
     }
-}
-
-__global__ void k_dd_sentinel(const uint32_t* __restrict__ vals, uint64_t* __restrict__ out_keys,
-                              uint32_t* __restrict__ out_vals, uint32_t* __restrict__ side) {
-    if (threadIdx.x == 0 && side[0] != 0xFFFFFFFFu) {
-        const uint32_t pos = side[1]++;
-        out_keys[pos] = kEmpty;
-        out_vals[pos] = vals[side[0]];
+    __syncthreads();
+    if (full) return;   // the whole block: the host tries another hash
+    // the record that is its key's first occurrence goes to the list
+    for (uint32_t q = q0; q < q1; ++q) {
+        const uint64_t lo = qbeg[q], hi = qcap ? min(qend[q], lo + qcap) : qend[q];
+        for (uint64_t i0 = lo; i0 < hi; i0 += kDdThreads * kDdUnroll) {
+            uint64_t x[kDdUnroll];
+            uint32_t at[kDdUnroll], v[kDdUnroll];
+#pragma unroll
+            for (uint32_t k = 0; k < kDdUnroll; ++k) {
+                const uint64_t i = i0 + tid + (uint64_t)k * kDdThreads;
+                x[k] = i < hi ? keys[i] : 0;
+                at[k] = i < hi ? (idx ? idx[i] : (uint32_t)i) : 0;
+                v[k] = i < hi ? vals[i] : 0;
+            }
+#pragma unroll
+            for (uint32_t k = 0; k < kDdUnroll; ++k) {
+                if (i0 + tid + (uint64_t)k * kDdThreads >= hi) continue;
+                bool first;
+                if (x[k] == kEmpty) {
+                    first = side == at[k];
+                } else {
+                    uint32_t s = slot_of(x[k]);
+                    while (tkey[s] != x[k]) s = (s + 1) & (kDdSlots - 1);
+                    first = tidx[s] == at[k];
+                }
+                if (first) {
+                    const uint64_t pos = (uint64_t)base + atomicAdd(&put, 1u);
+                    if (pos < out_cap) {
+                        out_keys[pos] = x[k];
+                        out_vals[pos] = v[k];
+                    }
+                }
+            }
+        }
     }
 }
 
@@ -79,47 +158,72 @@ extern "C" int fks_build_u64_from_array(const uint64_t* d_keys, const uint32_t* 
     if (u == 0) return fks_build_u64(d_keys, d_vals, 0, seed, params, alloc, stream, out);
     AllocScope scope(alloc);
     hipStream_t st = (hipStream_t)stream;
-    uint64_t cap = 1;
-    while (cap < 2 * u) cap <<= 1;
-    unsigned long long* tkey = (unsigned long long*)dev_alloc(8 * cap, st);
-    uint32_t* tidx = (uint32_t*)dev_alloc(4 * cap, st);
+    const PartPlan plan = part_plan(u);
+    const bool cursor = plan.passes == 1 || plan.passes == 2;
+    const size_t scratch_bytes = part_scratch(plan, u, true, cursor, false, nullptr, nullptr);
+    char* scratch = (char*)dev_alloc(scratch_bytes, st);
     uint64_t* dk = (uint64_t*)dev_alloc(8 * u, st);
     uint32_t* dv = (uint32_t*)dev_alloc(4 * u, st);
-    uint32_t* side = (uint32_t*)dev_alloc(64, st);
-    auto cleanup = [&]() {
-        dev_free(tkey, st);
-        dev_free(tidx, st);
-        dev_free(dk, st);
-        dev_free(dv, st);
-        dev_free(side, st);
+    DdCtrl* ctrl = (DdCtrl*)dev_alloc(sizeof(DdCtrl), st);
+    auto cleanup = [&](bool settled) {
+        dev_free(scratch, st, settled);
+        dev_free(dk, st, settled);
+        dev_free(dv, st, settled);
+        dev_free(ctrl, st, settled);
     };
-    if (!tkey || !tidx || !dk || !dv || !side) {
-        cleanup();
+    if (!scratch || !dk || !dv || !ctrl) {
+        cleanup(false);
         return FKS_ENOMEM;
     }
-    auto grid = [](uint64_t items) {
-        uint64_t g = (items + 255) / 256;
-        return (unsigned)(g < 1 ? 1 : g > 65536 ? 65536 : g);
-    };
-    hipLaunchKernelGGL(k_dd_init, grid(cap), 256, 0, st, tkey, tidx, cap, side);
-    FKS_TIMED("fks_dedup_insert", st,
-              hipLaunchKernelGGL(k_dd_insert, grid(u), 256, 0, st, d_keys, u, tkey, tidx, cap - 1, side));
-    FKS_TIMED("fks_dedup_compact", st,
-              hipLaunchKernelGGL(k_dd_compact, grid(cap), 256, 0, st, tkey, tidx, cap, d_vals, dk, dv, side));
-    hipLaunchKernelGGL(k_dd_sentinel, 1, 64, 0, st, d_vals, dk, dv, side);
+    PartArgs a{};
+    part_scratch(plan, u, true, cursor, false, scratch, &a);
+    a.n = u;
+    a.aux = true;
+    a.magic = fastmod_magic((uint32_t)u);
+    a.keys = d_keys;
+    a.vals = d_vals;
+    a.overflow = &ctrl->overflow;
+    a.fused = true;   // no size pass: only the partitions' records are wanted
+    a.cursor = cursor;
     uint32_t n = 0;
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = hipMemcpyAsync(&n, side + 1, 4, hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (e != hipSuccess) {
-        cleanup();
-        return hip_fail(e);
+    int rc = FKS_EBUILD;
+    for (uint32_t r = 0; r < kDdAttempts; ++r) {
+        // partition and slot hashes of a stream of their own (~seed), fresh in every attempt
+        a.A = level1_triple(~seed, r);
+        const Triple H = level2_triple(~seed, r, 0);
+        hipLaunchKernelGGL(k_dd_clear, 1, 64, 0, st, ctrl);
+        PartOut o;
+        if ((rc = part_prepare(a, st, o))) break;
+        FKS_TIMED("fks_dedup_distinct", st,
+                  hipLaunchKernelGGL(k_dd_distinct, (plan.Q + kDdParts - 1) / kDdParts, kDdThreads, 0, st, o.keys,
+                                     o.vals, o.aux_is_pos ? nullptr : o.aux, o.qbeg, o.qend, o.qcap, plan.Q, H, dk,
+                                     dv, u, ctrl));
+        DdCtrl got{};
+        hipError_t e = hipGetLastError();
+        if (e == hipSuccess) e = hipMemcpyAsync(&got, ctrl, sizeof(got), hipMemcpyDeviceToHost, st);
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        if (e != hipSuccess) {
+            rc = hip_fail(e);
+            break;
+        }
+        if (got.overflow) {
+            // a key repeated many times crowds its partition's region: the same hash again,
+            // with counted passes, whose partitions hold any number of records
+            a.cursor = false;
+            --r;
+            continue;
+        }
+        if (got.full) {
+            rc = FKS_EBUILD;   // more distinct keys than slots: another hash
+            continue;
+        }
+        n = got.count;
+        rc = FKS_OK;
+        break;
     }
-    dev_free(tkey, st);
-    dev_free(tidx, st);
-    tkey = nullptr;
-    tidx = nullptr;
-    int rc = fks_build_u64(dk, dv, n, seed, params, alloc, stream, out);
-    cleanup();
+    dev_free(scratch, st, rc == FKS_OK);
+    scratch = nullptr;
+    if (rc == FKS_OK) rc = fks_build_u64(dk, dv, n, seed, params, alloc, stream, out);
+    cleanup(rc == FKS_OK);   // the build has waited for its own last kernel
     return rc;
 }
