@@ -455,7 +455,9 @@ typedef struct fks_sorted fks_sorted;
 #define FKS_LAYOUT_EYTZINGER 1u   /* level order of the complete search tree */
 
 /* d_keys, d_vals: n device records, read only during the call; n < 2^32.
-   The structure owns 12 bytes of device memory per key.  Synchronizes the
+   The structure owns about 12.6 bytes of device memory per key, 14.2 in the
+   Eytzinger layout (the pairs, and every 16th (4th) key, every 256th (64th)
+   and so on as separators for the search).  Synchronizes the
    stream once (duplicate check).  Errors: FKS_EINVAL, FKS_ENOMEM, FKS_EDUPKEY,
    FKS_EHIP. */
 int fks_sorted_build_u64(const uint64_t* d_keys, const uint32_t* d_vals, uint64_t n, uint32_t layout,

@@ -11,9 +11,10 @@
 // keys.  The Eytzinger layout gathers the sorted pairs into the level order of
 // the complete binary search tree, computing each node's in-order rank in
 // closed form.
-// Lookup: the branch-free binary search (a fixed ceil(log2 n) steps for every
-// needle, four needles per lane in lockstep), or the Eytzinger descent with the
-// tree's top levels staged in LDS.
+// Lookup: a search through an index of separators (every 16th key in order, every
+// 256th and so on; Eytzinger: every 4th, every 64th), whose top level is staged in
+// LDS, a line of sixteen at a time by eight lanes together; the last step runs on
+// the keys themselves.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -22,12 +23,33 @@
 #include "partition.hpp"
 #include "prof.hpp"
 
+namespace fks {
+
+// The separators of a sorted or Eytzinger map.  Level l (1 = lowest) holds the keys at in-order
+// positions 2^gran * 16^(l-1) * (j + 1) - 1 that part two groups of the level below (for the
+// Eytzinger layout positions of the perfect tree of its depth; all of these nodes exist).  A group
+// is a 128-byte line of sixteen entries; levels are filled up to whole lines with all-ones words.
+constexpr uint32_t kSepLevels = 8;
+struct SepIndex {
+    uint32_t levels;                    // at least 1
+    uint32_t gran;                      // log2 of the in-order keys per lowest separator
+    uint64_t count[kSepLevels + 1];     // entries of level l
+    uint64_t at[kSepLevels + 1];        // where level l starts in the index
+    uint64_t total;                     // entries of all levels, filled up
+    uint32_t depth;                     // Eytzinger: floor(log2 n)
+    uint64_t first_node;                // Eytzinger: leftmost of the nodes below the separators
+};
+
+}  // namespace fks
+
 struct fks_sorted {
     uint64_t n;
     uint32_t layout;
     int device;
     uint64_t* keys;   // n keys in layout order
     uint32_t* vals;   // their values
+    uint64_t* index;  // separators, level by level
+    fks::SepIndex sep;
     fks_allocator alloc;   // where keys and vals came from (has_alloc == 0: the library's pool)
     int has_alloc;
 };
@@ -38,8 +60,8 @@ constexpr uint32_t kRB = 256;                 // threads per block
 constexpr uint32_t kRItems = 16;              // records per thread per tile
 constexpr uint32_t kRTile = kRB * kRItems;    // 4096 records per tile
 constexpr uint32_t kWaveSpan = 64 * kRItems;  // records of one wave inside a tile
-constexpr uint32_t kTopLevels = 12;           // Eytzinger levels staged in LDS
-constexpr uint32_t kTopNodes = (1u << kTopLevels) - 1;
+constexpr uint32_t kTopSeps = 4095;           // most separators of the top level, staged in LDS (12 steps)
+constexpr uint32_t kSortedGran = 4, kEytzGran = 2;   // the lowest separators: every 16th and every 4th key
 
 __device__ __forceinline__ void chunk_of(uint64_t n, uint32_t W, uint64_t& a, uint64_t& b) {
     const uint64_t chunk = (n + W - 1) / W;
@@ -200,94 +222,186 @@ __global__ void k_eytzinger(const uint64_t* __restrict__ sk, const uint32_t* __r
     }
 }
 
-constexpr uint32_t kQ = 4;   // needles per lane in lockstep
+// in-order position p of the perfect tree of depth H: its node (1-based, level order)
+__device__ __forceinline__ uint64_t node_at(uint64_t p, uint32_t H) {
+    const uint32_t z = (uint32_t)__ffsll((long long)(p + 1)) - 1;
+    return (1ull << (H - z)) + ((p + 1) >> (z + 1));
+}
 
-template <bool WANT_VALS>
-__global__ __launch_bounds__(256) void k_bsearch(const uint64_t* __restrict__ sk, const uint32_t* __restrict__ sv,
-                                                   uint64_t n, const uint64_t* __restrict__ q, uint64_t m,
-                                                   uint32_t* __restrict__ out_vals, uint8_t* __restrict__ out_found,
-                                                   uint32_t missing) {
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x * kQ;
-    for (uint64_t j0 = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) * kQ; j0 < m; j0 += stride) {
-        uint64_t x[kQ], lo[kQ];
-#pragma unroll
-        for (uint32_t u = 0; u < kQ; ++u) {
-            x[u] = j0 + u < m ? q[j0 + u] : 0;
-            lo[u] = 0;
+// the separators of every level, gathered from the keys in layout order
+template <bool EYTZ>
+__global__ void k_separators(const uint64_t* __restrict__ keys, SepIndex sep, uint64_t* __restrict__ index) {
+    for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < sep.total;
+         e += (uint64_t)gridDim.x * blockDim.x) {
+        uint32_t l = 1;
+        while (l < sep.levels && e >= sep.at[l + 1]) ++l;
+        const uint64_t j = e - sep.at[l];
+        uint64_t x = ~0ull;
+        if (j < sep.count[l]) {
+            const uint64_t p = ((j + 1) << (sep.gran + 4 * (l - 1))) - 1;
+            x = keys[EYTZ ? node_at(p, sep.depth) - 1 : p];
         }
-        // the lower bound stays in [lo, lo + len]; len shrinks the same way for every needle
-        uint64_t len = n;
-        while (len > 1) {
-            const uint64_t half = len >> 1;
+        index[e] = x;
+    }
+}
+
+constexpr uint32_t kSBlock = 512;
+
+// sums over the eight lanes of a group, in every lane (all lanes active)
+__device__ __forceinline__ uint32_t sum8(uint32_t v) {
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false);    // lanes 1,0,3,2 of each four
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false);    // lanes 2,3,0,1
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, false);   // mirrored within eight lanes
+    return v;
+}
+
+// the two entries of a line that lane `at` of its eight holds
+struct Two {
+    uint64_t a, b;
+};
+
+// Every needle's lower bound.  The search is bound by 128-byte lines from beyond L1 (about 52 G/s
+// from HBM, up to 270 G/s from L2), so a line is read once, whole, by eight lanes, which count its
+// entries below the needle: lane l of a group answers needle l of the group, and for the lines all
+// eight lanes work on the group's eight needles in turn, with eight lines in flight.  (With a lane
+// per needle and four dependent reads in each line, the lines left the 32 KiB L1 between the reads:
+// 2.19 ms for 2^24 needles and keys; a binary search over the bare array, 22 lines per needle,
+// 3.93 ms.)
+template <bool EYTZ, bool WANT_VALS>
+__global__ __launch_bounds__(kSBlock) __attribute__((amdgpu_waves_per_eu(6))) void k_sep_search(const uint64_t* __restrict__ keys,
+                                                          const uint32_t* __restrict__ vals, uint64_t n,
+                                                          const uint64_t* __restrict__ index, SepIndex sep,
+                                                          const uint64_t* __restrict__ q, uint64_t m,
+                                                          uint32_t* __restrict__ out_vals,
+                                                          uint8_t* __restrict__ out_found, uint32_t missing) {
+    __shared__ uint64_t top[kTopSeps + 1];
+    const uint32_t ntop = (uint32_t)sep.count[sep.levels];
+    uint32_t step0 = 1;   // smallest power of two above ntop
+    while (step0 <= ntop) step0 <<= 1;
+    {
+        const uint64_t* src = index + sep.at[sep.levels];
+        for (uint32_t i = threadIdx.x; i < step0; i += kSBlock) top[i] = i < ntop ? src[i] : ~0ull;
+    }
+    __syncthreads();
+    const uint32_t lane = threadIdx.x & 63u, l8 = lane & 7u, g8 = lane & 56u;
+    const uint64_t wave = ((uint64_t)blockIdx.x * kSBlock + threadIdx.x) >> 6, waves = (uint64_t)gridDim.x * (kSBlock / 64);
+    for (uint64_t i0 = wave * 64; i0 < m; i0 += waves * 64) {   // the same for all lanes of a wave
+        const uint64_t mine = i0 + lane;
+        const uint64_t xm = mine < m ? q[mine] : 0;
+        uint64_t x[8];
 #pragma unroll
-            for (uint32_t u = 0; u < kQ; ++u) lo[u] = sk[lo[u] + half] < x[u] ? lo[u] + half : lo[u];
-            len -= half;
+        for (uint32_t s = 0; s < 8; ++s) x[s] = i0 + g8 + s < m ? q[i0 + g8 + s] : 0;
+        uint32_t jm = 0;
+        for (uint32_t st = step0 >> 1; st; st >>= 1) jm += top[jm + st - 1] < xm ? st : 0u;
+        uint32_t j[8];
+#pragma unroll
+        for (uint32_t s = 0; s < 8; ++s) j[s] = (uint32_t)__shfl((int)jm, (int)(g8 + s), 64);
+        // counts of entries below the needles, four needles to a word
+        auto count = [&](const Two (&e)[8]) {
+#pragma unroll
+            for (uint32_t h = 0; h < 8; h += 4) {
+                uint32_t c = 0;
+#pragma unroll
+                for (uint32_t s = 0; s < 4; ++s)
+                    c += ((e[h + s].a < x[h + s] ? 1u : 0u) + (e[h + s].b < x[h + s] ? 1u : 0u)) << (8 * s);
+                c = sum8(c);
+#pragma unroll
+                for (uint32_t s = 0; s < 4; ++s) j[h + s] = (j[h + s] << 4) + ((c >> (8 * s)) & 31u);
+            }
+        };
+        for (uint32_t l = sep.levels - 1; l >= 1; --l) {
+            const uint64_t* level = index + sep.at[l] + 2 * l8;
+            Two e[8];
+#pragma unroll
+            for (uint32_t s = 0; s < 8; ++s) e[s] = *reinterpret_cast<const Two*>(level + ((uint64_t)j[s] << 4));
+            count(e);
         }
+        bool hit = false;
+        uint64_t at = 0;
+        if (EYTZ) {
+            // each lane's own needle down the tree below the separators: a right turn appends a 1 to
+            // the node number, a left turn a 0; the lower bound is the node of the last left turn
+            uint32_t jo = j[0];
 #pragma unroll
-        for (uint32_t u = 0; u < kQ; ++u) {
-            if (j0 + u >= m) break;
-            // the lower bound is lo or lo + 1
-            uint64_t pos = lo[u];
-            bool hit = false;
-            if (n) {
-                const uint64_t kk = sk[pos];
-                if (kk < x[u]) {
-                    ++pos;
-                    hit = pos < n && sk[pos] == x[u];
-                } else {
-                    hit = kk == x[u];
+            for (uint32_t s = 1; s < 8; ++s) jo = l8 == s ? j[s] : jo;
+            uint64_t i = sep.first_node + jo, last = 0;
+            bool left = false;
+#pragma unroll
+            for (uint32_t d = 0; d < kEytzGran; ++d) {
+                if (i <= n) {
+                    const uint64_t k = keys[i - 1];
+                    const bool right = k < xm;
+                    if (!right) {
+                        left = true;
+                        last = k;
+                    }
+                    i = 2 * i + (right ? 1 : 0);
                 }
             }
-            out_found[j0 + u] = hit;
-            if (WANT_VALS) out_vals[j0 + u] = hit ? sv[pos] : missing;
+            const uint64_t lb = i >> __ffsll((long long)~i);   // 0: none
+            if (!left && lb != 0) last = keys[lb - 1];         // a separator
+            hit = lb != 0 && last == xm;
+            at = lb - 1;
+        } else {
+            Two e[8];
+#pragma unroll
+            for (uint32_t s = 0; s < 8; ++s) {
+                const uint64_t k = ((uint64_t)j[s] << 4) + 2 * l8;
+                if (k + 1 < n) e[s] = *reinterpret_cast<const Two*>(keys + k);
+                else e[s] = Two{k < n ? keys[k] : ~0ull, ~0ull};
+            }
+            // the line holds the lower bound, when a key equals the needle (entries past n are all
+            // ones, and the needle of all ones is told by its position)
+            uint32_t eq[2] = {0, 0};
+#pragma unroll
+            for (uint32_t s = 0; s < 8; ++s) eq[s >> 2] += (e[s].a == x[s] || e[s].b == x[s] ? 1u : 0u) << (8 * (s & 3));
+            count(e);
+            eq[0] = sum8(eq[0]);
+            eq[1] = sum8(eq[1]);
+            uint32_t jo = j[0], eo = eq[0] & 255u;
+#pragma unroll
+            for (uint32_t s = 1; s < 8; ++s) {
+                jo = l8 == s ? j[s] : jo;
+                eo = l8 == s ? (eq[s >> 2] >> (8 * (s & 3))) & 255u : eo;
+            }
+            at = jo;
+            hit = eo != 0 && at < n;
+        }
+        if (mine < m) {
+            if (WANT_VALS) __builtin_nontemporal_store(hit ? vals[at] : missing, out_vals + mine);
+            __builtin_nontemporal_store((uint8_t)hit, out_found + mine);
         }
     }
 }
 
-template <bool WANT_VALS>
-__global__ __launch_bounds__(256) void k_eytz_search(const uint64_t* __restrict__ ek,
-                                                       const uint32_t* __restrict__ ev, uint64_t n,
-                                                       const uint64_t* __restrict__ q, uint64_t m,
-                                                       uint32_t* __restrict__ out_vals,
-                                                       uint8_t* __restrict__ out_found, uint32_t missing) {
-    __shared__ uint64_t top[kTopNodes];
-    const uint64_t ntop = min(n, (uint64_t)kTopNodes);
-    for (uint32_t i = threadIdx.x; i < ntop; i += blockDim.x) top[i] = ek[i];
-    __syncthreads();
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x * kQ;
-    for (uint64_t j0 = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) * kQ; j0 < m; j0 += stride) {
-        uint64_t x[kQ], i[kQ];
-#pragma unroll
-        for (uint32_t u = 0; u < kQ; ++u) {
-            x[u] = j0 + u < m ? q[j0 + u] : 0;
-            i[u] = 1;
-        }
-        // descend: a right turn appends a 1 to the node number, a left turn a 0
-        for (uint32_t lvl = 0; lvl < kTopLevels; ++lvl) {
-#pragma unroll
-            for (uint32_t u = 0; u < kQ; ++u)
-                if (i[u] <= ntop) i[u] = 2 * i[u] + (top[i[u] - 1] < x[u] ? 1 : 0);
-        }
-        bool more = true;
-        while (more) {
-            more = false;
-#pragma unroll
-            for (uint32_t u = 0; u < kQ; ++u)
-                if (i[u] <= n) {
-                    i[u] = 2 * i[u] + (ek[i[u] - 1] < x[u] ? 1 : 0);
-                    more = true;
-                }
-        }
-#pragma unroll
-        for (uint32_t u = 0; u < kQ; ++u) {
-            if (j0 + u >= m) break;
-            // the lower bound is the node of the last left turn (0: none)
-            const uint64_t lb = i[u] >> (__ffsll((long long)~i[u]));
-            const bool hit = lb != 0 && ek[lb - 1] == x[u];
-            out_found[j0 + u] = hit;
-            if (WANT_VALS) out_vals[j0 + u] = hit ? ev[lb - 1] : missing;
-        }
+__global__ void k_none_found(uint64_t m, uint32_t* __restrict__ vals, uint8_t* __restrict__ found, uint32_t missing) {
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += (uint64_t)gridDim.x * blockDim.x) {
+        if (vals) vals[i] = missing;
+        found[i] = 0;
     }
+}
+
+// levels of separators over n keys: up to the first that fits the LDS
+static SepIndex sep_layout(uint64_t n, bool eytz) {
+    SepIndex s{};
+    s.gran = eytz ? kEytzGran : kSortedGran;
+    uint64_t below = n, group = 1ull << s.gran;   // entries that the next level parts, and a group of them
+    if (eytz) {
+        while ((2ull << s.depth) <= n) ++s.depth;
+        below = (2ull << s.depth) - 1;
+        s.first_node = 1ull << (s.depth + 1 > s.gran ? s.depth + 1 - s.gran : 0);
+    }
+    do {
+        below = (below + group - 1) / group - 1;
+        group = 16;
+        s.count[++s.levels] = below;
+    } while (below > kTopSeps);
+    for (uint32_t l = 1; l <= s.levels; ++l) {
+        s.at[l] = s.total;
+        // the lines of a level: one more than the separators that part them
+        s.total += l < s.levels ? 16 * (s.count[l + 1] + 1) : (s.count[l] + 16) & ~15ull;
+    }
+    return s;
 }
 
 static unsigned sgrid(uint64_t items, uint64_t per_block, unsigned cap) {
@@ -384,6 +498,17 @@ extern "C" int fks_sorted_build_u64(const uint64_t* d_keys, const uint32_t* d_va
         delete S;
         return rc;
     }
+    S->sep = sep_layout(n, layout == 1);
+    S->index = (uint64_t*)dev_alloc(8 * S->sep.total, st);
+    if (!S->index) {
+        cleanup(false);
+        delete S;
+        return FKS_ENOMEM;
+    }
+    if (layout == 1)
+        hipLaunchKernelGGL(k_separators<true>, sgrid(S->sep.total, 256, 8192), 256, 0, st, kin, S->sep, S->index);
+    else
+        hipLaunchKernelGGL(k_separators<false>, sgrid(S->sep.total, 256, 8192), 256, 0, st, kin, S->sep, S->index);
     // keep the final pair of arrays, release the rest
     S->keys = const_cast<uint64_t*>(kin);
     S->vals = const_cast<uint32_t*>(vin);
@@ -394,6 +519,7 @@ extern "C" int fks_sorted_build_u64(const uint64_t* d_keys, const uint32_t* d_va
     if (e != hipSuccess) {
         dev_free(S->keys, st);
         dev_free(S->vals, st);
+        dev_free(S->index, st);
         delete S;
         return hip_fail(e);
     }
@@ -406,25 +532,23 @@ extern "C" int fks_sorted_lookup_u64(const fks_sorted* S, const uint64_t* d_q, u
     if (!S || (m && (!d_q || !d_found_out))) return FKS_EINVAL;
     if (m == 0) return FKS_OK;
     hipStream_t st = (hipStream_t)stream;
-    const unsigned grid = sgrid(m, 256 * kQ, 16384);
+    if (S->n == 0) {
+        hipLaunchKernelGGL(k_none_found, sgrid(m, 256, 8192), 256, 0, st, m, d_vals_out, d_found_out, missing_value);
+        const hipError_t e = hipGetLastError();
+        return e == hipSuccess ? FKS_OK : hip_fail(e);
+    }
+    // at most four workgroups per CU, as many as its wave slots hold: each stages the top separators once
+    const unsigned grid = sgrid(m, kSBlock, 1024);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, kSBlock, 0, st, S->keys, S->vals, S->n, S->index, S->sep, d_q, m, d_vals_out,
+                           d_found_out, missing_value);
+    };
     if (S->layout == 0) {
-        if (d_vals_out)
-            FKS_TIMED("fks_bsearch_u64", st,
-                      hipLaunchKernelGGL(k_bsearch<true>, grid, 256, 0, st, S->keys, S->vals, S->n, d_q, m,
-                                         d_vals_out, d_found_out, missing_value));
-        else
-            FKS_TIMED("fks_bsearch_u64", st,
-                      hipLaunchKernelGGL(k_bsearch<false>, grid, 256, 0, st, S->keys, S->vals, S->n, d_q, m,
-                                         nullptr, d_found_out, missing_value));
+        FKS_TIMED("fks_bsearch_u64", st,
+                  d_vals_out ? launch(k_sep_search<false, true>) : launch(k_sep_search<false, false>));
     } else {
-        if (d_vals_out)
-            FKS_TIMED("fks_eytzinger_u64", st,
-                      hipLaunchKernelGGL(k_eytz_search<true>, grid, 256, 0, st, S->keys, S->vals, S->n, d_q, m,
-                                         d_vals_out, d_found_out, missing_value));
-        else
-            FKS_TIMED("fks_eytzinger_u64", st,
-                      hipLaunchKernelGGL(k_eytz_search<false>, grid, 256, 0, st, S->keys, S->vals, S->n, d_q, m,
-                                         nullptr, d_found_out, missing_value));
+        FKS_TIMED("fks_eytzinger_u64", st,
+                  d_vals_out ? launch(k_sep_search<true, true>) : launch(k_sep_search<true, false>));
     }
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? FKS_OK : hip_fail(e);
@@ -456,6 +580,7 @@ extern "C" void fks_sorted_destroy(fks_sorted* S) {
         AllocScope scope(S->has_alloc ? &S->alloc : nullptr);
         dev_free(S->keys, nullptr);
         dev_free(S->vals, nullptr);
+        dev_free(S->index, nullptr);
     }
     (void)hipSetDevice(prev);
     delete S;
