@@ -1,7 +1,10 @@
 // The comparison maps of Section 4: the same (key, value) pairs as a sorted
 // array searched by binary search, or in Eytzinger (level-order) layout.
 //
-// Build: a least-significant-digit radix sort of the pairs, eight passes of
+// Build: the sample sort of sort.hip, which writes the pairs in order or in level order
+// and reports equal keys.  Beyond its largest size, with a caller's allocator (whose memory
+// may have been sized for it) and after one of its regions overflowed: a
+// least-significant-digit radix sort of the pairs, eight passes of
 // 8-bit digits.  Each pass is a per-worker digit count, an exclusive scan of the
 // (digit, worker) count matrix, and a stable scatter: inside a 4096-record tile
 // every wave owns a contiguous stretch and ranks its records round by round
@@ -22,25 +25,7 @@
 #include "fks_internal.hpp"
 #include "partition.hpp"
 #include "prof.hpp"
-
-namespace fks {
-
-// The separators of a sorted or Eytzinger map.  Level l (1 = lowest) holds the keys at in-order
-// positions 2^gran * 16^(l-1) * (j + 1) - 1 that part two groups of the level below (for the
-// Eytzinger layout positions of the perfect tree of its depth; all of these nodes exist).  A group
-// is a 128-byte line of sixteen entries; levels are filled up to whole lines with all-ones words.
-constexpr uint32_t kSepLevels = 8;
-struct SepIndex {
-    uint32_t levels;                    // at least 1
-    uint32_t gran;                      // log2 of the in-order keys per lowest separator
-    uint64_t count[kSepLevels + 1];     // entries of level l
-    uint64_t at[kSepLevels + 1];        // where level l starts in the index
-    uint64_t total;                     // entries of all levels, filled up
-    uint32_t depth;                     // Eytzinger: floor(log2 n)
-    uint64_t first_node;                // Eytzinger: leftmost of the nodes below the separators
-};
-
-}  // namespace fks
+#include "sort.hpp"
 
 struct fks_sorted {
     uint64_t n;
@@ -246,6 +231,7 @@ __global__ void k_separators(const uint64_t* __restrict__ keys, SepIndex sep, ui
 }
 
 constexpr uint32_t kSBlock = 512;
+constexpr int kSortAgain = 1;   // inside this file: the sample sort gave up
 
 // sums over the eight lanes of a group, in every lane (all lanes active)
 __device__ __forceinline__ uint32_t sum8(uint32_t v) {
@@ -409,25 +395,59 @@ static unsigned sgrid(uint64_t items, uint64_t per_block, unsigned cap) {
     return (unsigned)(g < 1 ? 1 : g > cap ? cap : g);
 }
 
-}  // namespace fks
+static void separators(const fks_sorted* S, hipStream_t st) {
+    const unsigned grid = sgrid(S->sep.total, 256, 8192);
+    if (S->layout == 1)
+        hipLaunchKernelGGL(k_separators<true>, grid, 256, 0, st, S->keys, S->sep, S->index);
+    else
+        hipLaunchKernelGGL(k_separators<false>, grid, 256, 0, st, S->keys, S->sep, S->index);
+}
 
-using namespace fks;
+// pinned words for the outcome of a sort, one pair per host thread, kept for the life of the process
+static SortFlags* pinned_flags() {
+    static thread_local SortFlags* buf = nullptr;
+    if (!buf && hipHostMalloc((void**)&buf, sizeof(SortFlags), hipHostMallocDefault) != hipSuccess) buf = nullptr;
+    return buf;
+}
 
-extern "C" int fks_sorted_build_u64(const uint64_t* d_keys, const uint32_t* d_vals, uint64_t n, uint32_t layout,
-                                    const fks_allocator* alloc, void* stream, fks_sorted** out) {
-    if (!out || (n && (!d_keys || !d_vals)) || n >= (1ull << 32) || layout > 1 || !allocator_ok(alloc))
-        return FKS_EINVAL;
-    AllocScope scope(alloc);
-    hipStream_t st = (hipStream_t)stream;
-    fks_sorted* S = new fks_sorted{};
-    keep_allocator(alloc, S->alloc, S->has_alloc);
-    S->n = n;
-    S->layout = layout;
-    (void)hipGetDevice(&S->device);
-    if (n == 0) {
-        *out = S;
-        return FKS_OK;
+// The map by sample sort: everything is queued before the one wait for the outcome.
+// kSortAgain: sort another way (a region overflowed, or there is no memory for the regions).
+static int build_sampled(fks_sorted* S, const uint64_t* d_keys, const uint32_t* d_vals, hipStream_t st) {
+    const uint64_t n = S->n;
+    SortFlags* host = pinned_flags();
+    void* scratch = dev_alloc(sample_sort_scratch(n), st);
+    SortFlags* flags = (SortFlags*)dev_alloc(sizeof(SortFlags), st);
+    S->keys = (uint64_t*)dev_alloc(8 * n, st);
+    S->vals = (uint32_t*)dev_alloc(4 * n, st);
+    S->index = (uint64_t*)dev_alloc(8 * S->sep.total, st);
+    int rc = host && scratch && flags && S->keys && S->vals && S->index ? FKS_OK : kSortAgain;
+    bool settled = false;
+    if (rc == FKS_OK) {
+        sample_sort(d_keys, d_vals, n, S->layout == 1, S->keys, S->vals, S->sep, S->index, flags, scratch, st);
+        hipError_t e = hipGetLastError();
+        if (e == hipSuccess) e = hipMemcpyAsync(host, flags, sizeof(SortFlags), hipMemcpyDeviceToHost, st);
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        settled = e == hipSuccess;
+        if (e != hipSuccess) rc = hip_fail(e);
+        else if (host->overflow) rc = kSortAgain;
+        else if (host->dup) rc = FKS_EDUPKEY;
     }
+    dev_free(scratch, st, settled);
+    dev_free(flags, st, settled);
+    if (rc != FKS_OK) {
+        dev_free(S->keys, st, settled);
+        dev_free(S->vals, st, settled);
+        dev_free(S->index, st, settled);
+        S->keys = S->index = nullptr;
+        S->vals = nullptr;
+    }
+    return rc;
+}
+
+// The map by radix sort.
+static int build_radix(fks_sorted* S, const uint64_t* d_keys, const uint32_t* d_vals, hipStream_t st) {
+    const uint64_t n = S->n;
+    const uint32_t layout = S->layout;
     const uint32_t W = (uint32_t)std::min<uint64_t>(4096, std::max<uint64_t>(1, n / (4 * (uint64_t)kRTile)));
     const uint64_t N = 256ull * W;
     uint64_t* kb[2] = {(uint64_t*)dev_alloc(8 * n, st), (uint64_t*)dev_alloc(8 * n, st)};
@@ -453,7 +473,6 @@ extern "C" int fks_sorted_build_u64(const uint64_t* d_keys, const uint32_t* d_va
     if (!kb[0] || !kb[1] || !vb[0] || !vb[1] || !cnt || !off || !tsum || !tpre || !flag ||
         hipHostMalloc((void**)&hflag, 4, hipHostMallocDefault) != hipSuccess) {
         cleanup(false);
-        delete S;
         return FKS_ENOMEM;
     }
     const uint64_t* kin = d_keys;
@@ -495,23 +514,17 @@ extern "C" int fks_sorted_build_u64(const uint64_t* d_keys, const uint32_t* d_va
     }
     if (rc != FKS_OK) {
         cleanup(false);
-        delete S;
         return rc;
     }
-    S->sep = sep_layout(n, layout == 1);
     S->index = (uint64_t*)dev_alloc(8 * S->sep.total, st);
     if (!S->index) {
         cleanup(false);
-        delete S;
         return FKS_ENOMEM;
     }
-    if (layout == 1)
-        hipLaunchKernelGGL(k_separators<true>, sgrid(S->sep.total, 256, 8192), 256, 0, st, kin, S->sep, S->index);
-    else
-        hipLaunchKernelGGL(k_separators<false>, sgrid(S->sep.total, 256, 8192), 256, 0, st, kin, S->sep, S->index);
     // keep the final pair of arrays, release the rest
     S->keys = const_cast<uint64_t*>(kin);
     S->vals = const_cast<uint32_t*>(vin);
+    separators(S, st);
     kb[cur ^ 1] = nullptr;
     vb[cur ^ 1] = nullptr;
     e = hipStreamSynchronize(st);
@@ -520,8 +533,37 @@ extern "C" int fks_sorted_build_u64(const uint64_t* d_keys, const uint32_t* d_va
         dev_free(S->keys, st);
         dev_free(S->vals, st);
         dev_free(S->index, st);
-        delete S;
         return hip_fail(e);
+    }
+    return FKS_OK;
+}
+
+}  // namespace fks
+
+using namespace fks;
+
+extern "C" int fks_sorted_build_u64(const uint64_t* d_keys, const uint32_t* d_vals, uint64_t n, uint32_t layout,
+                                    const fks_allocator* alloc, void* stream, fks_sorted** out) {
+    if (!out || (n && (!d_keys || !d_vals)) || n >= (1ull << 32) || layout > 1 || !allocator_ok(alloc))
+        return FKS_EINVAL;
+    AllocScope scope(alloc);
+    hipStream_t st = (hipStream_t)stream;
+    fks_sorted* S = new fks_sorted{};
+    keep_allocator(alloc, S->alloc, S->has_alloc);
+    S->n = n;
+    S->layout = layout;
+    (void)hipGetDevice(&S->device);
+    if (n == 0) {
+        *out = S;
+        return FKS_OK;
+    }
+    S->sep = sep_layout(n, layout == 1);
+    int rc = kSortAgain;
+    if (!alloc && n <= kSampleSortMax) rc = build_sampled(S, d_keys, d_vals, st);
+    if (rc == kSortAgain) rc = build_radix(S, d_keys, d_vals, st);
+    if (rc != FKS_OK) {
+        delete S;
+        return rc;
     }
     *out = S;
     return FKS_OK;
