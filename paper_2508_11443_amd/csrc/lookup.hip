@@ -9,7 +9,10 @@
 // in flight so that their random probes overlap.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "fks_internal.hpp"
+#include "ordered.hpp"
 #include "prof.hpp"
 
 namespace fks {
@@ -81,6 +84,145 @@ __global__ __launch_bounds__(kLBlock) void k_lookup_u64(const Group* __restrict_
             }
         }
     }
+}
+
+// ---- ordered lookups (ordered.hpp) ----------------------------------------------------------
+
+OrdScratch::OrdScratch(uint64_t m, uint32_t bins, bool ids, uint32_t val_bytes, bool found, hipStream_t s, size_t more)
+    : st_(s) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (s != nullptr && hipStreamIsCapturing(s, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+    }
+    if (cap != hipStreamCaptureStatusNone) return;
+    a_.tile = ord_tile(ids);
+    a_.bins = bins;
+    const size_t tiles = (m + a_.tile - 1) / a_.tile;
+    size_t total = 0;
+    auto carve = [&](size_t bytes) {
+        const size_t at = total;
+        total += (bytes + 255) & ~(size_t)255;
+        return at;
+    };
+    const size_t x = carve(8 * m), id = carve(ids ? 4 * m : 0), slot = carve(2 * m),
+                 start = carve(2 * tiles * (bins + 1)), val = carve((size_t)val_bytes * m),
+                 fnd = carve(found ? m : 0), own = carve(more);
+    base_ = pool_take(total, s);
+    if (!base_) return;
+    char* p = (char*)base_;
+    a_.x = (uint64_t*)(p + x);
+    a_.id = (uint32_t*)(p + id);
+    a_.slot = (uint16_t*)(p + slot);
+    a_.start = (uint16_t*)(p + start);
+    a_.val = val_bytes ? p + val : nullptr;
+    more_ = p + own;
+    a_.found = found ? (uint8_t*)(p + fnd) : nullptr;
+}
+
+OrdScratch::~OrdScratch() {
+    if (base_) pool_give(base_, st_, false);
+}
+
+// Needles in their own order against ordered, 50 % hits: over 4 * 10^6 keys 52 and 58 us for 2^21
+// needles, 98 and 88 us for 2^22, 370 and 278 us for 2^24; 2^22 needles over 2^21 keys 84 and
+// 83 us, over 2^25 keys 135 and 145 us (half the table's lines are not needed at all); 2^23 needles
+// over 2^18 keys 138 and 126 us, over 2^25 keys 264 and 248 us.  The three launches and the table's one pass
+// have to be paid back by 10-15 ps per needle.
+uint32_t ord_parts(uint64_t m, uint64_t table_bytes) {
+    constexpr uint32_t kParts = 256;
+    if (m >= (1u << 23)) return table_bytes >= (8u << 20) && table_bytes / 136 <= m ? kParts : 0;
+    return m >= (1u << 22) && table_bytes >= (128u << 20) && table_bytes / 68 <= m ? kParts : 0;
+}
+
+// part of the table that answers an integer needle: equal ranges of buckets
+struct BucketPart {
+    static constexpr uint32_t kLds = 0;
+    Triple A;
+    uint64_t magic;
+    uint32_t n;
+    uint32_t scale;   // floor(2^32 parts / n) with n > parts: parts come out below their number
+    __device__ void setup(uint64_t*) const {}
+    __device__ uint32_t of(const uint64_t*, uint64_t x, uint32_t) const {
+        return __umulhi(fastmod(mshash(A, x), magic, n), scale);
+    }
+};
+
+// Needles grouped by part, answered at their places.  Bound by the requests that reach L2 (a
+// group record and a cell for each needle, 5.1 ps of it per needle at L2's 270 G requests/s when all hit) and by the
+// lines that miss it (the table once).  10^7 needles over as many keys: 160 us, 80 of it without
+// the cells and 45 without any table access.  Workgroups of 1024 threads with two needles each in
+// flight keep few parts open at a time: with 256 threads and four needles 181 us; with 128 or
+// 512 parts instead of 256 10-20 us more.
+template <bool V64>
+__global__ __launch_bounds__(kOrdBlock) void k_ord_lookup(const Group* __restrict__ header,
+                                                        const Cell* __restrict__ slots, Triple A, uint64_t magic,
+                                                        uint32_t n, const Triple* __restrict__ Cg, uint32_t T,
+                                                        OrdArgs o, uint64_t missing) {
+    __shared__ Triple C[kTMax];
+    __shared__ OrdRuns R;
+    for (uint32_t t = threadIdx.x; t < T; t += kOrdBlock) C[t] = Cg[t];
+    uint32_t part;
+    const uint32_t total = ord_runs(o, R, part);
+    constexpr uint32_t Q = 2;
+    for (uint32_t i0 = 0; i0 < total; i0 += kOrdBlock * Q) {
+        uint64_t x[Q], at[Q];
+        Group h[Q];
+        uint32_t kk[Q];
+#pragma unroll
+        for (uint32_t k = 0; k < Q; ++k) {
+            const uint32_t i = i0 + threadIdx.x + k * kOrdBlock;
+            at[k] = i < total ? ord_place(R, i) : 0;
+            x[k] = i < total ? __builtin_nontemporal_load(o.x + at[k]) : 0;
+        }
+#pragma unroll
+        for (uint32_t k = 0; k < Q; ++k) {
+            const uint32_t j = fastmod(mshash(A, x[k]), magic, n);
+            kk[k] = j & 7u;
+            if (i0 + threadIdx.x + k * kOrdBlock < total) h[k] = header[j >> 3];
+            else h[k] = Group{0, 0, 0, 0};
+        }
+        Cell c[Q];
+#pragma unroll
+        for (uint32_t k = 0; k < Q; ++k) {
+            uint32_t p;
+            c[k] = cell_of(h[k], kk[k], C, x[k], p) ? slots[p] : Cell{~x[k], 0, 0};
+        }
+#pragma unroll
+        for (uint32_t k = 0; k < Q; ++k) {
+            if (i0 + threadIdx.x + k * kOrdBlock < total) {
+                const bool hit = c[k].key == x[k];
+                if (V64) {
+                    if (o.val) ((uint64_t*)o.val)[at[k]] = hit ? ((uint64_t)c[k].aux << 32) | c[k].val : missing;
+                } else {
+                    if (o.val) ((uint32_t*)o.val)[at[k]] = hit ? c[k].val : (uint32_t)missing;
+                }
+                if (o.found) o.found[at[k]] = hit ? 1 : 0;
+            }
+        }
+    }
+}
+
+// The whole lookup in table order; false: not worth it, no scratch, or a map in a caller's
+// memory (whose lookups take none of the library's).
+template <bool V64, typename V>
+static bool ordered_lookup(const fks_map* map, const uint64_t* q, uint64_t m, V* vals, uint8_t* found, V missing,
+                           hipStream_t st) {
+    const uint32_t n = (uint32_t)map->n, bins = ord_parts(m, 2 * map->n + 16 * map->S);
+    if (bins == 0 || n <= bins || map->has_alloc) return false;
+    const uint64_t slice = std::min<uint64_t>(m, kOrdSlice);
+    OrdScratch s(slice, bins, false, vals ? sizeof(V) : 0, found != nullptr, st);
+    if (!s) return false;
+    const BucketPart part{map->A, map->magic_n, n, (uint32_t)(((uint64_t)bins << 32) / n)};
+    for (uint64_t at = 0; at < m; at += slice) {
+        const OrdArgs a = s.part(std::min(slice, m - at));
+        ord_group<BucketPart, false>(part, q + at, nullptr, a, st);
+        FKS_TIMED("fks_order_lookup", st,
+                  hipLaunchKernelGGL(k_ord_lookup<V64>, ord_grid(a), kOrdBlock, 0, st, map->header, map->slots, map->A,
+                                     map->magic_n, n, map->C, map->T, a, (uint64_t)missing));
+        ord_return<V, false>(a, vals ? vals + at : nullptr, found ? found + at : nullptr, st);
+    }
+    return true;
 }
 
 // String needles: fingerprint, probe, then compare the stored bytes on a fingerprint hit.
@@ -165,7 +307,7 @@ extern "C" int fks_lookup_u64(const fks_map* map, const uint64_t* d_queries, uin
     if (map->n == 0) {
         FKS_TIMED("fks_fill_outputs", st, hipLaunchKernelGGL(k_fill_outputs, lookup_grid(m, kLBlock), kLBlock, 0, st, m, d_vals_out, nullptr, d_found_out,
                            missing, 0ull));
-    } else {
+    } else if (!ordered_lookup<false, uint32_t>(map, d_queries, m, d_vals_out, d_found_out, missing, st)) {
         const unsigned grid = lookup_grid(m, (uint64_t)kLBlock * kQ);
         if (d_vals_out && d_found_out)
             FKS_TIMED("fks_lookup_u64", st, hipLaunchKernelGGL((k_lookup_u64<true, true>), grid, kLBlock, 0, st, map->header, map->slots, map->A,
@@ -199,7 +341,7 @@ extern "C" int fks_lookup_u64_v64(const fks_map* map, const uint64_t* d_queries,
         FKS_TIMED("fks_fill_outputs", st,
                   hipLaunchKernelGGL(k_fill_outputs, lookup_grid(m, kLBlock), kLBlock, 0, st, m, nullptr, d_vals_out,
                                      d_found_out, 0u, missing));
-    } else {
+    } else if (!ordered_lookup<true, uint64_t>(map, d_queries, m, d_vals_out, d_found_out, missing, st)) {
         const unsigned grid = lookup_grid(m, (uint64_t)kLBlock * kQ);
         if (d_found_out)
             FKS_TIMED("fks_lookup_u64_v64", st,

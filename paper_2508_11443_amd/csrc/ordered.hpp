@@ -1,0 +1,255 @@
+// Ordered lookups: many needles against a table far larger than the caches.
+//
+// A lookup in the needles' own order fetches a 128-byte line from HBM for every 16 bytes it reads
+// and runs at the device's rate of such lines (about 54 G/s), so the same line is fetched for each
+// of the needles that need it.  Here the needles are first grouped by the part of the table that
+// answers them, tile by tile (k_ord_group: a counting sort in LDS, written to the tile's own
+// place), then every part is answered by the workgroups of one XCD, through whose L2 its lines
+// pass once (the structure's own kernel over OrdRuns), and the answers go back to the needles'
+// order, tile by tile (k_ord_return).  The two extra passes move about 30 bytes per needle,
+// all of it in streams.
+//
+// 10^7 needles over as many keys: 347 us in their own order, 246 us so (grouping 44, answers 156,
+// return 41); 2^26 over 2^26: 2.10 and 1.47 ms.  Runs are kept long (large tiles, few parts): with 512
+// parts a run is 30 needles, and its partial lines cost more than the smaller parts gain
+// (264 us, 1.60 ms).  Part w mod 8 on each XCD rather than a stretch of neighbours: parts differ
+// in needles where keys are clustered, and neighbours alike (a sorted map 632 us instead of 516).
+// Reading the next part's lines ahead of their use changed nothing (253 us) or lost (1.74 ms).
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "fks_internal.hpp"
+#include "prof.hpp"
+
+namespace fks {
+
+constexpr uint32_t kOrdThreads = 1024;
+constexpr uint32_t kOrdBins = 512;          // most parts of a table
+constexpr uint32_t kOrdItems = 15;          // needles per thread of a tile: 8 bytes each in LDS ...
+constexpr uint32_t kOrdItemsIds = 12;       // ... or 12 with a map id
+constexpr uint32_t kOrdRunTiles = 32;        // tiles whose runs of one part a workgroup answers
+constexpr uint32_t kOrdBlock = 1024;        // its threads
+
+// Device arrays of one call (m needles in `tiles` tiles of `tile`, the last one short).
+struct OrdArgs {
+    uint64_t m;
+    uint32_t tile, tiles, bins;   // bins: parts of the table, at most kOrdBins
+    uint64_t* x;        // needles, every tile grouped by part
+    uint32_t* id;       // their map ids (batches)
+    uint16_t* slot;     // the place in its tile of every needle of the caller's order
+    uint16_t* start;    // tiles x (bins + 1): where a part's run starts in its tile
+    void* val;          // answers at the needles' places
+    uint8_t* found;
+};
+
+// exclusive scan of one value per thread over the block's first kOrdBins threads
+__device__ __forceinline__ uint32_t ord_exscan(uint32_t v, uint32_t* wsum) {
+    const uint32_t lane = threadIdx.x & 63u, w = threadIdx.x >> 6;
+    uint32_t inc = v;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t u = __shfl_up(inc, d, 64);
+        if (lane >= (uint32_t)d) inc += u;
+    }
+    if (lane == 63 && w < kOrdBins / 64) wsum[w] = inc;
+    __syncthreads();
+    uint32_t pre = 0;
+#pragma unroll
+    for (uint32_t q = 0; q < kOrdBins / 64; ++q) pre += q < w ? wsum[q] : 0u;
+    return pre + inc - v;
+}
+
+// One tile of needles grouped by part.  Part: setup(lds) once (512 words of LDS), then of(lds, x, id).
+template <typename Part, bool IDS>
+__global__ __launch_bounds__(kOrdThreads) void k_ord_group(Part part, const uint64_t* __restrict__ q,
+                                                          const uint32_t* __restrict__ ids, OrdArgs o) {
+    constexpr uint32_t ITEMS = IDS ? kOrdItemsIds : kOrdItems, TILE = kOrdThreads * ITEMS;
+    __shared__ uint64_t sx[TILE];
+    __shared__ uint32_t sid[IDS ? TILE : 1];
+    __shared__ uint32_t cnt[kOrdBins], at[kOrdBins], wsum[kOrdBins / 64];
+    __shared__ uint64_t own[Part::kLds ? Part::kLds : 1];
+    const uint32_t tid = threadIdx.x;
+    const uint64_t base = (uint64_t)blockIdx.x * TILE;
+    const uint32_t count = (uint32_t)min((uint64_t)TILE, o.m - base);
+    uint64_t x[ITEMS];
+    uint32_t id[IDS ? ITEMS : 1];
+#pragma unroll
+    for (uint32_t k = 0; k < ITEMS; ++k) {
+        const uint32_t i = tid + k * kOrdThreads;
+        x[k] = i < count ? __builtin_nontemporal_load(q + base + i) : 0;
+        if (IDS) id[IDS ? k : 0] = i < count ? __builtin_nontemporal_load(ids + base + i) : 0;
+    }
+    part.setup(own);
+    if (tid < kOrdBins) cnt[tid] = 0;
+    __syncthreads();
+    uint32_t bin[ITEMS], rank[ITEMS];
+#pragma unroll
+    for (uint32_t k = 0; k < ITEMS; ++k) bin[k] = part.of(own, x[k], IDS ? id[IDS ? k : 0] : 0u);
+#pragma unroll
+    for (uint32_t k = 0; k < ITEMS; ++k) {
+        if (tid + k * kOrdThreads < count) {
+            // a wave whose needles all fall into one part counts them at once: atomics of 64 lanes
+            // on one word would be served one after the other
+            const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)bin[k]);
+            const uint64_t here = __ballot(true);
+            if (__all(bin[k] == first)) {
+                uint32_t r = 0;
+                const uint32_t lane = tid & 63u;
+                if (lane == 0) r = atomicAdd(&cnt[first], (uint32_t)__popcll(here));
+                rank[k] = (uint32_t)__builtin_amdgcn_readfirstlane((int)r) + lane;
+            } else {
+                rank[k] = atomicAdd(&cnt[bin[k]], 1u);
+            }
+        }
+    }
+    __syncthreads();
+    {
+        const uint32_t e = ord_exscan(tid < kOrdBins ? cnt[tid] : 0u, wsum);
+        if (tid < kOrdBins) at[tid] = e;
+        if (tid <= o.bins) o.start[(uint64_t)blockIdx.x * (o.bins + 1) + tid] = (uint16_t)(tid < o.bins ? e : count);
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t k = 0; k < ITEMS; ++k) {
+        const uint32_t i = tid + k * kOrdThreads;
+        if (i < count) {
+            const uint32_t e = at[bin[k]] + rank[k];
+            sx[e] = x[k];
+            if (IDS) sid[IDS ? e : 0] = id[IDS ? k : 0];
+            o.slot[base + i] = (uint16_t)e;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t k = 0; k < ITEMS; ++k) {
+        const uint32_t i = tid + k * kOrdThreads;
+        if (i < count) {
+            o.x[base + i] = sx[i];
+            if (IDS) o.id[base + i] = sid[IDS ? i : 0];
+        }
+    }
+}
+
+// The runs of one part in kOrdRunTiles consecutive tiles, as one sequence.  Workgroups are dealt
+// to the eight XCDs in turn, so workgroup w answers a part of number w mod 8 (mod 8).
+struct OrdRuns {
+    uint32_t pre[kOrdRunTiles + 1];
+    uint64_t src[kOrdRunTiles];
+};
+__host__ __device__ inline uint32_t ord_chunks(uint32_t tiles) { return (tiles + kOrdRunTiles - 1) / kOrdRunTiles; }
+// workgroups of the answering kernel
+inline unsigned ord_grid(const OrdArgs& o) { return ((o.bins + 7) / 8) * 8 * ord_chunks(o.tiles); }
+// the part of this workgroup; its runs in R, their total length returned (after a barrier)
+__device__ __forceinline__ uint32_t ord_runs(const OrdArgs& o, OrdRuns& R, uint32_t& part) {
+    const uint32_t chunks = ord_chunks(o.tiles), g = blockIdx.x >> 3;
+    part = (g / chunks) * 8 + (blockIdx.x & 7u);
+    if (threadIdx.x < 64) {
+        const uint32_t t = threadIdx.x, tile = (g % chunks) * kOrdRunTiles + t;
+        uint32_t len = 0;
+        uint64_t at = 0;
+        if (t < kOrdRunTiles && tile < o.tiles && part < o.bins) {
+            const uint16_t* s = o.start + (uint64_t)tile * (o.bins + 1) + part;
+            at = (uint64_t)tile * o.tile + s[0];
+            len = (uint32_t)s[1] - s[0];
+        }
+        uint32_t inc = len;
+#pragma unroll
+        for (int d = 1; d < (int)kOrdRunTiles; d <<= 1) {
+            const uint32_t u = __shfl_up(inc, d, 64);
+            if (t >= (uint32_t)d) inc += u;
+        }
+        if (t < kOrdRunTiles) {
+            R.pre[t + 1] = inc;
+            R.src[t] = at - (inc - len);
+        }
+        if (t == 0) R.pre[0] = 0;
+    }
+    __syncthreads();
+    return R.pre[kOrdRunTiles];
+}
+// the place of needle i of the sequence
+__device__ __forceinline__ uint64_t ord_place(const OrdRuns& R, uint32_t i) {
+    uint32_t r = 0;
+#pragma unroll
+    for (uint32_t st = kOrdRunTiles >> 1; st; st >>= 1) r += R.pre[r + st] <= i ? st : 0u;
+    return R.src[r] + i;
+}
+
+// One tile of answers back in the caller's order.
+template <typename V, uint32_t TILE>
+__global__ __launch_bounds__(kOrdThreads) void k_ord_return(OrdArgs o, V* __restrict__ vals,
+                                                           uint8_t* __restrict__ found) {
+    constexpr uint32_t ITEMS = TILE / kOrdThreads;
+    __shared__ V sv[TILE];
+    __shared__ uint8_t sf[TILE];
+    const uint64_t base = (uint64_t)blockIdx.x * TILE;
+    const uint32_t count = (uint32_t)min((uint64_t)TILE, o.m - base), tid = threadIdx.x;
+    const V* val = (const V*)o.val + base;
+    uint16_t slot[ITEMS];
+#pragma unroll
+    for (uint32_t k = 0; k < ITEMS; ++k) {
+        const uint32_t i = tid + k * kOrdThreads;
+        slot[k] = 0;
+        if (i < count) {
+            slot[k] = __builtin_nontemporal_load(o.slot + base + i);
+            if (vals) sv[i] = __builtin_nontemporal_load(val + i);
+            if (found) sf[i] = __builtin_nontemporal_load(o.found + base + i);
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t k = 0; k < ITEMS; ++k) {
+        const uint32_t i = tid + k * kOrdThreads;
+        if (i < count) {
+            if (vals) __builtin_nontemporal_store(sv[slot[k]], vals + base + i);
+            if (found) __builtin_nontemporal_store(sf[slot[k]], found + base + i);
+        }
+    }
+}
+
+// ---- host side ---------------------------------------------------------------------------
+
+constexpr uint64_t kOrdSlice = 1ull << 27;   // needles at a time: 2 GB of scratch
+constexpr uint32_t ord_tile(bool ids) { return kOrdThreads * (ids ? kOrdItemsIds : kOrdItems); }
+
+// Scratch of one call on stream s, given back in stream order when it goes out of scope.
+class OrdScratch {
+  public:
+    // false: no memory, or the stream is being captured (a graph would keep the scratch)
+    OrdScratch(uint64_t m, uint32_t bins, bool ids, uint32_t val_bytes, bool found, hipStream_t s, size_t more = 0);
+    void* more() const { return more_; }   // as many bytes for the caller
+    ~OrdScratch();
+    OrdScratch(const OrdScratch&) = delete;
+    OrdScratch& operator=(const OrdScratch&) = delete;
+    explicit operator bool() const { return base_ != nullptr; }
+    // for a slice of m needles
+    OrdArgs part(uint64_t m) const {
+        OrdArgs a = a_;
+        a.m = m;
+        a.tiles = (uint32_t)((m + a.tile - 1) / a.tile);
+        return a;
+    }
+
+  private:
+    OrdArgs a_{};
+    void *base_ = nullptr, *more_ = nullptr;
+    hipStream_t st_;
+};
+
+// parts for a table of that many bytes; 0: the lookup stays in the caller's order
+uint32_t ord_parts(uint64_t m, uint64_t table_bytes);
+
+template <typename Part, bool IDS>
+void ord_group(const Part& part, const uint64_t* q, const uint32_t* ids, const OrdArgs& a, hipStream_t st) {
+    FKS_TIMED("fks_order_group", st,
+              hipLaunchKernelGGL((k_ord_group<Part, IDS>), a.tiles, kOrdThreads, 0, st, part, q, ids, a));
+}
+template <typename V, bool IDS>
+void ord_return(const OrdArgs& a, V* vals, uint8_t* found, hipStream_t st) {
+    FKS_TIMED("fks_order_return", st,
+              hipLaunchKernelGGL((k_ord_return<V, ord_tile(IDS)>), a.tiles, kOrdThreads, 0, st, a, vals, found));
+}
+
+}  // namespace fks

@@ -11,8 +11,9 @@
 // handed out again at once.  One that comes back on the null stream may still be in use by work
 // queued before that; it is handed to the null stream as it is, and to another stream after
 // that stream has been made to wait for the null stream.  One that comes back on any other
-// stream carries an event recorded there and stays aside until the event is done.  No stream
-// handle is kept: a stream may be destroyed after the call.
+// stream carries an event recorded there and stays aside until the event is done, or until a
+// stream that needs a block of its size is made to wait for the event.  No kept stream handle
+// is used: a stream may be destroyed after the call.
 //
 // Bounds.  Free memory above an eighth of the device's is given back to the driver, whole
 // segments at a time (hipFree waits for the device, so nothing queued still uses them); when the
@@ -59,6 +60,7 @@ class Pool {
         collect(false);
         const bool small = bytes <= kSmall;
         if (void* p = fit(bytes, small, s)) return p;
+        if (void* p = small ? nullptr : adopt(bytes, s)) return p;
         const size_t seg = small ? kSmallSegment : (bytes + kPage - 1) & ~(kPage - 1);
         if (!grow(seg, small)) {
             // the driver has no more: wait for what is on its way back, then return every free segment
@@ -88,7 +90,8 @@ class Pool {
             }
             if (ev) {
                 it->second.state = kPending;
-                pending_.push_back({it->first, ev});
+                pending_.push_back({it->first, ev, s});
+                pending_bytes_ += it->second.size;
             } else {
                 (void)hipGetLastError();
                 (void)hipStreamSynchronize(s);
@@ -177,17 +180,42 @@ class Pool {
     // blocks whose events are done become free
     void collect(bool wait) {
         for (size_t i = 0; i < pending_.size();) {
-            const hipError_t e = wait ? hipEventSynchronize(pending_[i].second) : hipEventQuery(pending_[i].second);
+            const hipError_t e = wait ? hipEventSynchronize(pending_[i].done) : hipEventQuery(pending_[i].done);
             if (e != hipSuccess) {
                 (void)hipGetLastError();
                 ++i;
                 continue;
             }
-            (void)hipEventDestroy(pending_[i].second);
-            release(chunks_.find(pending_[i].first), kIdle);
-            pending_[i] = pending_.back();
-            pending_.pop_back();
+            auto it = chunks_.find(pending_[i].block);
+            forget(i);
+            release(it, kIdle);
         }
+    }
+    void forget(size_t i) {
+        pending_bytes_ -= chunks_.find(pending_[i].block)->second.size;
+        (void)hipEventDestroy(pending_[i].done);
+        pending_[i] = pending_.back();
+        pending_.pop_back();
+    }
+
+    // A large block that another call's work may still use, for stream s to use after it: one that
+    // came back on a stream of the same handle (nothing is waited for unless the stream is a
+    // new one), or any, once more waits on its way back than the pool keeps free.  So calls queued
+    // one behind the other share a block, and calls on many streams cannot pile up memory.
+    void* adopt(size_t bytes, hipStream_t s) {
+        for (size_t i = 0; i < pending_.size(); ++i) {
+            auto it = chunks_.find(pending_[i].block);
+            if (it->second.small || it->second.size < bytes || it->second.size / 2 > bytes) continue;
+            if (pending_[i].stream != s && pending_bytes_ <= keep_) continue;
+            if (hipStreamWaitEvent(s, pending_[i].done, 0) != hipSuccess) {
+                (void)hipGetLastError();
+                continue;
+            }
+            forget(i);
+            it->second.state = kUsed;
+            return it->first;
+        }
+        return nullptr;
     }
 
     bool grow(size_t seg, bool small) {
@@ -227,7 +255,13 @@ class Pool {
     size_t keep_ = 4ull << 30, free_bytes_ = 0;
     Chunks chunks_;                 // every block, by address
     Index free_[2][2];              // free blocks by size: [settled, null-ordered][large, small]
-    std::vector<std::pair<char*, hipEvent_t>> pending_;
+    struct Pending {
+        char* block;
+        hipEvent_t done;
+        hipStream_t stream;   // compared, never used: it may have been destroyed
+    };
+    std::vector<Pending> pending_;
+    size_t pending_bytes_ = 0;
 };
 
 std::mutex g_mu;
