@@ -142,8 +142,16 @@ static int check_params(uint64_t n, const fks_params* p, fks_params& out) {
 // the sum of the squared bucket sizes; with n keys hashed into n buckets the sizes are
 // close to Poisson(1), so S has mean 2n - 1 and variance about 11n (the
 // fourth moment of Poisson(1) is 15).  Eight standard deviations above the mean hold it
-// but for a negligible fraction of builds; a larger S costs one more final pass into an
-// exact allocation.  More than c*n cells are never needed: such an attempt is rejected.
+// but for a negligible fraction of builds over keys spread at random; a larger S costs one more
+// final pass into an exact allocation.  More than c*n cells are never needed: such an attempt is
+// rejected.
+//
+// Keys in runs do not follow that estimate: with half the keys one run of consecutive integers
+// S was 1.75n to 3.2n over 60 hashes and above it for 11 of them, and the second final pass
+// takes 0.93 ms of the 3.5 ms of 2^26 keys' build and lookup.  So 4n cells are taken from the library's
+// own pool, and what S leaves goes back once the host knows it; up to kRoomyCells, so that
+// what a build needs for a moment stays a small part of the device's memory.
+constexpr uint64_t kRoomyCells = 1ull << 29;   // 8 GiB
 static uint64_t cells_guess(uint64_t n, uint32_t c) {
     const uint64_t g = 2 * n + (uint64_t)(8.0 * std::sqrt(11.0 * (double)n)) + 64;
     const uint64_t lim = (uint64_t)c * n;
@@ -176,6 +184,7 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
     std::vector<void*> owned;
     Cell* slots = nullptr;   // direct form: the cells, kept across attempts
     uint64_t cap = 0;
+    bool roomy = false;      // more cells than the estimate were taken
     auto release = [&](bool settled) {
         for (void* p : owned) dev_free(p, st, settled);
         owned.clear();
@@ -195,8 +204,14 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
     a.cursor = cursor;
     const uint32_t* const reject = &ctrl->oversize;   // followed by bad_input
     if (direct) {
-        cap = cells_guess(n, P.c);
-        slots = (Cell*)dev_alloc(16 * cap, st);
+        cap = std::min<uint64_t>(P.c, 4) * n;
+        roomy = !M->has_alloc && cap <= kRoomyCells;
+        if (roomy) slots = (Cell*)dev_alloc(16 * cap, st);
+        if (!slots) {
+            roomy = false;
+            cap = cells_guess(n, P.c);
+            slots = (Cell*)dev_alloc(16 * cap, st);
+        }
         if (!slots) {
             release(false);
             return FKS_ENOMEM;
@@ -274,6 +289,7 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
                 }
                 continue;
             }
+            if (roomy && pool_trim(slots, 16 * S)) cap = S;
             M->slots = slots;
             slots = nullptr;
             M->S = S;

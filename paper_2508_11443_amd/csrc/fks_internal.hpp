@@ -278,6 +278,9 @@ void* dev_alloc(size_t bytes, hipStream_t s);
 void dev_free(void* p, hipStream_t s, bool settled = false);
 void* pool_take(size_t bytes, hipStream_t s);
 void pool_give(void* p, hipStream_t s, bool settled);
+// the bytes of the pool's block from `bytes` on come back; nothing may be using them (false: not
+// a block of the pool)
+bool pool_trim(void* p, size_t bytes);
 class AllocScope {
   public:
     explicit AllocScope(const fks_allocator* a);

@@ -102,6 +102,19 @@ class Pool {
         return true;
     }
 
+    // the end of a block, from `bytes` on, is not needed and nothing uses it
+    bool trim(void* p, size_t bytes) {
+        bytes = (bytes + kAlign - 1) & ~(kAlign - 1);
+        std::lock_guard<std::mutex> lk(mu_);
+        auto it = chunks_.find((char*)p);
+        if (it == chunks_.end() || it->second.state != kUsed) return false;
+        if (it->second.size < bytes + kAlign) return true;
+        Chunk rest{it->second.size - bytes, kUsed, false, it->second.small};
+        it->second.size = bytes;
+        release(chunks_.emplace_hint(std::next(it), it->first + bytes, rest), kIdle);
+        return true;
+    }
+
   private:
     enum State { kUsed, kIdle, kNull, kPending };
     struct Chunk {
@@ -299,6 +312,13 @@ void pool_give(void* p, hipStream_t s, bool settled) {
     Pool* pool = pool_of(dev, false);
     if (pool && pool->give(p, s, settled)) return;
     (void)hipFreeAsync(p, s);
+}
+
+bool pool_trim(void* p, size_t bytes) {
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    Pool* pool = pool_of(dev, false);
+    return pool && bytes && pool->trim(p, bytes);
 }
 
 }  // namespace fks
