@@ -33,7 +33,6 @@ constexpr uint32_t kPTile = kPB * kPItems;    // 4096 keys per tile
 // per bin, 149 KB of LDS: one workgroup and four waves per SIMD on a CU), or x 8 when an aux
 // word travels (16-byte records, 8192-record tiles, 133 KB)
 constexpr uint32_t kPScatterThreads = 1024, kPScatterItems = 12, kPScatterItemsAux = 8;
-constexpr uint64_t kWorkerKeys = 2ull * kPScatterThreads * kPScatterItems;   // keys per scatter worker: two tiles
 constexpr uint32_t kBins = 256;               // bins per scatter pass
 constexpr uint32_t kFinalKeyCap = 1248;       // keys of one partition held in LDS (mean 1024, sd 32)
 constexpr uint32_t kLdsTrials = 16;          // level-two triples held in the final pass's LDS (larger trials are rare)
@@ -1061,7 +1060,24 @@ PartPlan part_plan(uint64_t n) {
     while ((1ull << bits) < P.Q) ++bits;
     P.bits_q = bits;
     auto clampu = [](uint64_t v, uint64_t lo, uint64_t hi) { return (uint32_t)(v < lo ? lo : v > hi ? hi : v); };
-    P.W1 = clampu((n + kWorkerKeys - 1) / (kWorkerKeys), 1, 4096);
+    // Tiles of the cursor form and keys per worker, so that a small input is not left to a few
+    // CUs.  Build, one lookup and release with tiles of 12288 keys, two per worker, and here: 2^16 keys
+    // (three workers) 69 and 56 us with tiles of 2048 (57 of 4096), 2^18 75 and 62, 2^20 107
+    // and 98 with tiles of 4096 (104 of 2048), 3 * 10^6 156 and 153 with one large tile per
+    // worker (157 and 172 with tiles of 4096 and 2048).  One large tile per worker as long as
+    // every worker has a CU of its own: the passes over 2^22 keys take 31 + 23 us with 171
+    // workers of two tiles, 34 + 26 with 342 of one.
+    uint64_t worker = 2ull * kPScatterThreads * kPScatterItems;
+    if (n <= 256ull * kPartBuckets) {
+        P.items = 2;
+        worker = (uint64_t)kPScatterThreads * P.items;
+    } else if (n < (1ull << 21)) {
+        P.items = 4;
+        worker = (uint64_t)kPScatterThreads * P.items;
+    } else if (n <= 256ull * kPScatterThreads * kPScatterItems) {
+        worker = (uint64_t)kPScatterThreads * kPScatterItems;
+    }
+    P.W1 = clampu((n + worker - 1) / worker, 1, 4096);
     // regions of the cursor form: a first-level bin covers 2^shiftA partitions of 1024
     // buckets and a partition 1024 buckets; with n keys in n buckets the keys of B buckets
     // number B on average with a standard deviation of about sqrt(B), and the regions hold
@@ -1081,7 +1097,7 @@ PartPlan part_plan(uint64_t n) {
         P.shiftA = bits - 8;
         P.binsA = (uint32_t)((P.Q + (1u << P.shiftA) - 1) >> P.shiftA);
         P.bitsB = P.shiftA;
-        P.W2 = clampu((n / P.binsA + kWorkerKeys - 1) / (kWorkerKeys), 1, 64);
+        P.W2 = clampu((n / P.binsA + worker - 1) / worker, 1, 64);
         P.cap1 = region((uint64_t)kPartBuckets << P.shiftA);
         P.capQ = region(kPartBuckets);
     } else {
@@ -1091,8 +1107,8 @@ PartPlan part_plan(uint64_t n) {
         P.bitsC = bits - 16;
         P.bitsB = 8;
         P.binsAB = (uint32_t)((P.Q + (1u << P.bitsC) - 1) >> P.bitsC);
-        P.W2 = clampu((n / P.binsA + kWorkerKeys - 1) / (kWorkerKeys), 1, 64);
-        P.W3 = clampu((n / P.binsAB + kWorkerKeys - 1) / (kWorkerKeys), 1, 64);
+        P.W2 = clampu((n / P.binsA + worker - 1) / worker, 1, 64);
+        P.W3 = clampu((n / P.binsAB + worker - 1) / worker, 1, 64);
     }
     uint64_t m1 = (uint64_t)kBins * P.W1;
     uint64_t m2 = P.passes >= 2 ? (uint64_t)P.binsA * kBins * P.W2 : 0;
@@ -1164,15 +1180,19 @@ static void scatter(const PartArgs& a, const uint64_t* kin, const uint32_t* vin,
 }
 
 template <bool AUX>
-static void scatter_cursor(const PartArgs& a, const uint64_t* kin, const uint32_t* vin, const uint32_t* ain,
-                           const uint64_t* ranges, const uint64_t* ranges_hi, uint64_t in_cap, dim3 grid, uint32_t W,
-                           uint32_t shift, uint32_t mask, uint64_t* kout, uint32_t* vout, uint32_t* aout,
-                           unsigned long long* cursor, uint64_t cap, hipStream_t st) {
-    FKS_TIMED("fks_part_scatter", st,
-              hipLaunchKernelGGL((k_dscatter<AUX, AUX ? kPScatterItemsAux : kPScatterItems, kPScatterThreads, true>),
-                                 grid, kPScatterThreads, 0, st, kin, vin, ain, a.n, a.A, a.magic, ranges, W, shift,
-                                 mask, nullptr, kout, vout, aout, nullptr, cursor, ranges_hi, cap, a.overflow,
-                                 in_cap));
+static void scatter_cursor(const PartArgs& a, const PartPlan& P, const uint64_t* kin, const uint32_t* vin,
+                           const uint32_t* ain, const uint64_t* ranges, const uint64_t* ranges_hi, uint64_t in_cap,
+                           dim3 grid, uint32_t W, uint32_t shift, uint32_t mask, uint64_t* kout, uint32_t* vout,
+                           uint32_t* aout, unsigned long long* cursor, uint64_t cap, hipStream_t st) {
+    auto launch = [&](auto kernel) {
+        FKS_TIMED("fks_part_scatter", st,
+                  hipLaunchKernelGGL(kernel, grid, kPScatterThreads, 0, st, kin, vin, ain, a.n, a.A, a.magic, ranges, W,
+                                     shift, mask, nullptr, kout, vout, aout, nullptr, cursor, ranges_hi, cap,
+                                     a.overflow, in_cap));
+    };
+    if (P.items == 2) launch(k_dscatter<AUX, 2, kPScatterThreads, true>);
+    else if (P.items == 4) launch(k_dscatter<AUX, 4, kPScatterThreads, true>);
+    else launch(k_dscatter<AUX, AUX ? kPScatterItemsAux : kPScatterItems, kPScatterThreads, true>);
 }
 
 static unsigned grid_for_count(uint64_t count) { return (unsigned)std::min<uint64_t>((count + 255) / 256, 4096); }
@@ -1210,10 +1230,10 @@ int part_prepare(const PartArgs& a, hipStream_t st, PartOut& o) {
                            nzw, a.fused ? a.sqQ : nullptr);
         o.prezeroed = a.fused;
         if (aux)
-            scatter_cursor<true>(a, a.keys, a.vals, a.aux_in, nullptr, nullptr, 0, dim3(P.W1, 1), P.W1, 0, 255, a.k2,
+            scatter_cursor<true>(a, P, a.keys, a.vals, a.aux_in, nullptr, nullptr, 0, dim3(P.W1, 1), P.W1, 0, 255, a.k2,
                                  a.v2, a.a2, a.cur2, P.capQ, st);
         else
-            scatter_cursor<false>(a, a.keys, a.vals, nullptr, nullptr, nullptr, 0, dim3(P.W1, 1), P.W1, 0, 255,
+            scatter_cursor<false>(a, P, a.keys, a.vals, nullptr, nullptr, nullptr, 0, dim3(P.W1, 1), P.W1, 0, 255,
                                   a.k2, a.v2, a.a2, a.cur2, P.capQ, st);
         o.keys = a.k2;
         o.vals = a.v2;
@@ -1243,18 +1263,18 @@ int part_prepare(const PartArgs& a, hipStream_t st, PartOut& o) {
                            reinterpret_cast<uint32_t*>(a.cbase), nzw, a.fused ? a.sqQ : nullptr);
         o.prezeroed = a.fused;
         if (aux)
-            scatter_cursor<true>(a, a.keys, a.vals, a.aux_in, nullptr, nullptr, 0, dim3(P.W1, 1), P.W1, P.shiftA,
+            scatter_cursor<true>(a, P, a.keys, a.vals, a.aux_in, nullptr, nullptr, 0, dim3(P.W1, 1), P.W1, P.shiftA,
                                  255, a.k1, a.v1, a.a1, a.cur1, P.cap1, st);
         else
-            scatter_cursor<false>(a, a.keys, a.vals, nullptr, nullptr, nullptr, 0, dim3(P.W1, 1), P.W1, P.shiftA,
+            scatter_cursor<false>(a, P, a.keys, a.vals, nullptr, nullptr, nullptr, 0, dim3(P.W1, 1), P.W1, P.shiftA,
                                   255, a.k1, a.v1, a.a1, a.cur1, P.cap1, st);
         const uint32_t maskB = (1u << P.bitsB) - 1;
         const uint64_t* hi1 = reinterpret_cast<const uint64_t*>(a.cur1);
         if (aux)
-            scatter_cursor<true>(a, a.k1, a.v1, a.a1, a.begA, hi1, P.cap1, dim3(P.W2, P.binsA), P.W2, 0, maskB, a.k2,
+            scatter_cursor<true>(a, P, a.k1, a.v1, a.a1, a.begA, hi1, P.cap1, dim3(P.W2, P.binsA), P.W2, 0, maskB, a.k2,
                                  a.v2, a.a2, a.cur2, P.capQ, st);
         else
-            scatter_cursor<false>(a, a.k1, a.v1, nullptr, a.begA, hi1, P.cap1, dim3(P.W2, P.binsA), P.W2, 0, maskB,
+            scatter_cursor<false>(a, P, a.k1, a.v1, nullptr, a.begA, hi1, P.cap1, dim3(P.W2, P.binsA), P.W2, 0, maskB,
                                   a.k2, a.v2, a.a2, a.cur2, P.capQ, st);
         o.keys = a.k2;
         o.vals = a.v2;

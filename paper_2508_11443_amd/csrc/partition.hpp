@@ -37,6 +37,7 @@ struct PartPlan {
     uint32_t bitsB;    // two passes: second-level bin = q & (2^bitsB - 1); three: (q >> bitsC) & 255
     uint32_t binsAB;   // three passes: bins after the second pass (q >> bitsC)
     uint32_t bitsC;    // three passes: third-level bin = q & (2^bitsC - 1)
+    uint32_t items;    // records per thread of a cursor pass's tile: 2, 4, or 0 for the largest tile
     uint32_t W1, W2, W3;   // workers of the first pass / per bin of the second and third passes
     uint64_t matrix;   // entries of the largest count matrix
     // two passes with cursors: capacity of a first-level bin's region and of a partition's
