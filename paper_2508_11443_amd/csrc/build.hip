@@ -201,6 +201,9 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
     a.stalled = &ctrl->stalled;
     // the direct form runs the fused final pass: it sizes the partitions itself
     a.fused = direct;
+    // maps in a caller's memory (the server's builds, several at a time beside its lookups) keep
+    // the tickets
+    a.ticketed = M->has_alloc;
     a.cursor = cursor;
     const uint32_t* const reject = &ctrl->oversize;   // followed by bad_input
     if (direct) {
@@ -254,6 +257,11 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
                 break;
             }
             if (host->stalled) {
+                if (!a.ticketed) {   // workgroups out of order: the same attempt again with tickets
+                    a.ticketed = true;
+                    --r;
+                    continue;
+                }
                 rc = hip_fail(hipErrorLaunchFailure);
                 break;
             }

@@ -71,6 +71,7 @@ struct PartArgs {
     uint64_t* S_dev;            // total cells
     uint32_t* oversize;         // a bucket above 15 keys
     uint32_t* stalled;          // fused final pass: a look-back gave up
+    bool ticketed;              // fused final pass: partitions go in ticket order
     bool fused;                 // the final pass sizes the partitions itself (no size pass and scan)
     // two passes without count passes: each tile reserves its runs on per-bin cursors in
     // fixed-capacity regions (k1/v1/a1 hold binsA * cap1 records, k2/v2/a2 Q * capQ)
