@@ -836,10 +836,10 @@ extern "C" int fks_build_batch_u64(const uint64_t* d_keys, const uint32_t* d_val
     int dummy_bt, dummy_cu;
     if (!decode_schedule(sched, dummy_bt, dummy_cu)) rc = FKS_EINVAL;
     uint32_t count = M;
+    std::vector<WideSeg> segs;   // lives until the host has waited
     if (rc == FKS_OK && (sched & kScheduleWide)) {
         // large maps: attempt 0 of all of them by the partition passes; the order list then
         // holds only the small maps, and a large map that the passes reject follows below
-        std::vector<WideSeg> segs;
         uint64_t wide_keys = 0;
         for (uint32_t m = 0; m < M; ++m) {
             const BDesc& d = B->host[m];
@@ -883,17 +883,9 @@ extern "C" int fks_build_batch_u64(const uint64_t* d_keys, const uint32_t* d_val
             }
             wide = {d_segs, d_flags, d_cbase, d_scratch};
         }
-        if (rc == FKS_OK) {
-            std::vector<uint32_t> small;
-            for (uint32_t m : order)
-                if (B->host[m].n < kWideMin) small.push_back(m);
-            count = (uint32_t)small.size();
-            e = hipMemcpyAsync(d_order, small.data(), 4 * (size_t)count, hipMemcpyHostToDevice, st);
-            if (e == hipSuccess) e = hipStreamSynchronize(st);   // the small list is read before it goes out of scope
-            if (e != hipSuccess) rc = hip_fail(e);
-        }
+        count = M - (uint32_t)segs.size();   // the small maps are the end of the list
     }
-    if (rc == FKS_OK) rc = launch_batch(B, d_keys, d_vals, d_order, count, d_queue, rank_s, gscan_s, grouped_s, sched, st);
+    if (rc == FKS_OK) rc = launch_batch(B, d_keys, d_vals, d_order + (M - count), count, d_queue, rank_s, gscan_s, grouped_s, sched, st);
     if (rc == FKS_OK) {
         e = hipMemcpyAsync(B->host.data(), B->bdesc, sizeof(BDesc) * M, hipMemcpyDeviceToHost, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);

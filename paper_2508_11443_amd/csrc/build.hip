@@ -117,15 +117,6 @@ static void free_scratch(Scratch& w, hipStream_t st, bool settled) {
     w = Scratch{};
 }
 
-// one pinned readback buffer per host thread, kept for the life of the process
-static Readback* pinned_readback() {
-    static thread_local Readback* buf = nullptr;
-    if (!buf) {
-        if (hipHostMalloc((void**)&buf, sizeof(Readback), hipHostMallocDefault) != hipSuccess) buf = nullptr;
-    }
-    return buf;
-}
-
 static int check_params(uint64_t n, const fks_params* p, fks_params& out) {
     fks_params_default(&out);
     if (p) out = *p;
@@ -225,8 +216,7 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
         slots = nullptr;
     };
     auto readback = [&]() {
-        hipError_t e = hipMemcpyAsync(host, ctrl, sizeof(Readback), hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        const hipError_t e = words_to_host(host, ctrl, sizeof(Readback), st);
         return e == hipSuccess ? FKS_OK : hip_fail(e);
     };
     int rc = FKS_OK;
@@ -236,7 +226,10 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
         a.A = A;
         a.magic = M->magic_n;
         a.keys = d_keys_in;
-        hipLaunchKernelGGL(k_attempt_setup, 1, 256, 0, st, ctrl, M->C, M->seed, r, P.T);
+        // the outcome words are cleared before the fingerprints, which may set one
+        const bool with_passes = !bytes && (a.cursor || plan.passes == 0);
+        a.start = with_passes ? AttemptStart{(uint32_t*)ctrl, sizeof(Ctrl) / 4, M->C, M->seed, r, P.T} : AttemptStart{};
+        if (!with_passes) hipLaunchKernelGGL(k_attempt_setup, 1, 256, 0, st, ctrl, M->C, M->seed, r, P.T);
         if (bytes) {
             FKS_TIMED("fks_fingerprint", st,
                       hipLaunchKernelGGL(k_fingerprint, grid_for(n, kBlock, 65536), kBlock, 0, st, M->ctx_off,
@@ -400,7 +393,7 @@ static int build_common(fks_map* M, const uint64_t* d_keys_in, const uint32_t* d
     w.ctrl = (Ctrl*)dev_alloc(sizeof(Ctrl), st);
     if (bytes) w.y = (uint64_t*)dev_alloc(8 * n, st);
     if (!w.ctrl || (bytes && !w.y)) return fail(FKS_ENOMEM);
-    w.host = pinned_readback();
+    w.host = (Readback*)pinned_words();
     if (!w.host) return fail(FKS_ENOMEM);
     M->header = (Group*)dev_alloc(16 * G, st);
     M->C = (Triple*)dev_alloc(sizeof(Triple) * P.T, st);

@@ -68,6 +68,23 @@ int size_histogram(const Group* header, uint64_t n, uint64_t hist[16]) {
     return e == hipSuccess ? FKS_OK : hip_fail(e);
 }
 
+void* pinned_words() {
+    static thread_local void* buf = nullptr;
+    if (!buf && hipHostMalloc(&buf, kPinnedBytes, hipHostMallocDefault) != hipSuccess) buf = nullptr;
+    return buf;
+}
+
+// One small kernel in place of a copy: FIG_COPY
+__global__ void k_words_to_host(uint32_t* __restrict__ host, const uint32_t* __restrict__ dev, uint32_t words) {
+    if (threadIdx.x < words) host[threadIdx.x] = dev[threadIdx.x];
+}
+
+hipError_t words_to_host(void* pinned, const void* dev, size_t bytes, hipStream_t st) {
+    hipLaunchKernelGGL(k_words_to_host, 1, 64, 0, st, (uint32_t*)pinned, (const uint32_t*)dev, (uint32_t)(bytes / 4));
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? hipStreamSynchronize(st) : e;
+}
+
 void dev_free(void* p, hipStream_t s, bool settled) {
     if (!p) return;
     if (tl_alloc) tl_alloc->free(p, (void*)s, tl_alloc->user);

@@ -171,7 +171,8 @@ extern "C" int fks_build_u64_from_array(const uint64_t* d_keys, const uint32_t* 
         dev_free(dv, st, settled);
         dev_free(ctrl, st, settled);
     };
-    if (!scratch || !dk || !dv || !ctrl) {
+    DdCtrl* const pinned = (DdCtrl*)pinned_words();
+    if (!scratch || !dk || !dv || !ctrl || !pinned) {
         cleanup(false);
         return FKS_ENOMEM;
     }
@@ -191,21 +192,22 @@ extern "C" int fks_build_u64_from_array(const uint64_t* d_keys, const uint32_t* 
         // partition and slot hashes of a stream of their own (~seed), fresh in every attempt
         a.A = level1_triple(~seed, r);
         const Triple H = level2_triple(~seed, r, 0);
-        hipLaunchKernelGGL(k_dd_clear, 1, 64, 0, st, ctrl);
+        const bool with_passes = a.cursor || plan.passes == 0;
+        a.start = with_passes ? AttemptStart{(uint32_t*)ctrl, sizeof(DdCtrl) / 4, nullptr, 0, 0, 0} : AttemptStart{};
+        if (!with_passes) hipLaunchKernelGGL(k_dd_clear, 1, 64, 0, st, ctrl);
         PartOut o;
         if ((rc = part_prepare(a, st, o))) break;
         FKS_TIMED("fks_dedup_distinct", st,
                   hipLaunchKernelGGL(k_dd_distinct, (plan.Q + kDdParts - 1) / kDdParts, kDdThreads, 0, st, o.keys,
                                      o.vals, o.aux_is_pos ? nullptr : o.aux, o.qbeg, o.qend, o.qcap, plan.Q, H, dk,
                                      dv, u, ctrl));
-        DdCtrl got{};
         hipError_t e = hipGetLastError();
-        if (e == hipSuccess) e = hipMemcpyAsync(&got, ctrl, sizeof(got), hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        if (e == hipSuccess) e = words_to_host(pinned, ctrl, sizeof(DdCtrl), st);
         if (e != hipSuccess) {
             rc = hip_fail(e);
             break;
         }
+        const DdCtrl got = *pinned;
         if (got.overflow) {
             // a key repeated many times crowds its partition's region: the same hash again,
             // with counted passes, whose partitions hold any number of records

@@ -309,7 +309,15 @@ int size_histogram(const Group* header, uint64_t n, uint64_t hist[16]);
 int has_equal_keys(const uint64_t* keys, uint64_t n, const int64_t* off, const uint8_t* bytes, hipStream_t st,
                    bool* equal);
 
-// pinned host staging for the small readbacks of a build
+// kPinnedBytes of pinned host memory, one block per host thread, kept for the life of the process
+// (null: none to be had).
+constexpr size_t kPinnedBytes = 64;
+void* pinned_words();
+// `bytes` (whole words, at most kPinnedBytes) from the device to pinned memory, after all work
+// queued on st; waits for them.
+hipError_t words_to_host(void* pinned, const void* dev, size_t bytes, hipStream_t st);
+
+// the small readback of a build
 struct Readback {
     uint64_t S;          // sum of squared sizes of the attempt
     uint32_t oversize;   // some bucket holds more than 15 keys

@@ -45,13 +45,6 @@ __global__ void k_zero_words(uint32_t* __restrict__ p, uint64_t count) {
         p[i] = 0;
 }
 
-__global__ void k_set_range(uint64_t* off, uint64_t n) {
-    if (threadIdx.x == 0) {
-        off[0] = 0;
-        off[1] = n;
-    }
-}
-
 __device__ __forceinline__ uint32_t bucket_of(const Triple& A, uint64_t magic, uint32_t n, uint64_t x) {
     return fastmod(mshash(A, x), magic, n);
 }
@@ -240,12 +233,15 @@ __global__ __launch_bounds__(BT) void k_dscatter(const uint64_t* __restrict__ ke
     }
 }
 
-// the set-up of the cursor passes in one launch: the cursor of fixed-capacity region i of
-// either pass starts at i * cap (begin[i] keeps that start), and the fused final pass's
-// look-back words and ticket (zw words) start at zero
-__global__ void k_init_cursors(unsigned long long* __restrict__ cur1, uint64_t* __restrict__ beg1, uint64_t count1,
-                               uint64_t cap1, unsigned long long* __restrict__ cur2, uint64_t* __restrict__ beg2,
-                               uint64_t count2, uint64_t cap2, uint32_t* __restrict__ zw, uint64_t nzw,
+// The set-up of an attempt in one launch: the outcome words cleared and the level-two triples
+// written (start), the cursor of fixed-capacity region i of either pass at i * cap (begin[i] keeps
+// that start), the one partition of an input without passes, and the fused final pass's look-back
+// words and ticket (nzw words) at zero.  A launch costs a small build more than its work does: these
+// were one to four of its four to seven.
+__global__ void k_attempt_init(AttemptStart start, unsigned long long* __restrict__ cur1, uint64_t* __restrict__ beg1,
+                               uint64_t count1, uint64_t cap1, unsigned long long* __restrict__ cur2,
+                               uint64_t* __restrict__ beg2, uint64_t count2, uint64_t cap2,
+                               uint64_t* __restrict__ one, uint64_t n, uint32_t* __restrict__ zw, uint64_t nzw,
                                uint32_t* __restrict__ ticket) {
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count1 + count2 + nzw; i += stride) {
@@ -260,9 +256,17 @@ __global__ void k_init_cursors(unsigned long long* __restrict__ cur1, uint64_t* 
             zw[i - count1 - count2] = 0;
         }
     }
-    if (ticket && blockIdx.x == 0 && threadIdx.x == 0) *ticket = 0;
+    if (blockIdx.x != 0) return;
+    if (threadIdx.x < start.words) start.clear[threadIdx.x] = 0;
+    for (uint32_t t = threadIdx.x; t < start.T; t += blockDim.x) start.C[t] = level2_triple(start.seed, start.r, t);
+    if (threadIdx.x == 0) {
+        if (ticket) *ticket = 0;
+        if (one) {
+            one[0] = 0;
+            one[1] = n;
+        }
+    }
 }
-
 
 // ---- exclusive scan of a u32 array across blocks (values sum below 2^32) --------------------
 
@@ -1228,16 +1232,19 @@ int part_prepare(const PartArgs& a, hipStream_t st, PartOut& o) {
                   hipLaunchKernelGGL(k_dcount, grid, kPB, 0, st, kin, n, a.A, a.magic, ranges, W, shift, mask,
                                      a.cnt));
     };
+    auto init = [&](uint64_t bins1, uint64_t parts, bool one) {
+        const uint64_t nzw = a.fused ? 2 * (uint64_t)P.Q : 0;
+        hipLaunchKernelGGL(k_attempt_init, grid_for_count(std::max<uint64_t>(1, bins1 + parts + nzw)), 256, 0, st, a.start,
+                           a.cur1, a.begA, bins1, P.cap1, a.cur2, a.begQ, parts, P.capQ, one ? a.offQ : nullptr, n,
+                           reinterpret_cast<uint32_t*>(a.cbase), nzw, a.fused ? a.sqQ : nullptr);
+        o.prezeroed = a.fused;
+    };
     if (P.passes == 0) {
-        hipLaunchKernelGGL(k_set_range, 1, 64, 0, st, a.offQ, n);
+        init(0, 0, true);
     } else if (P.passes == 1 && a.cursor) {
         // one pass straight into the partitions' regions, each run reserved on its partition's
-        // cursor; the fused final pass's look-back words and ticket are cleared in the same launch
-        const uint64_t nzw = a.fused ? 2 * (uint64_t)P.Q : 0;
-        hipLaunchKernelGGL(k_init_cursors, grid_for_count(P.Q + nzw), 256, 0, st, a.cur1, a.begA, (uint64_t)0,
-                           (uint64_t)0, a.cur2, a.begQ, (uint64_t)P.Q, P.capQ, reinterpret_cast<uint32_t*>(a.cbase),
-                           nzw, a.fused ? a.sqQ : nullptr);
-        o.prezeroed = a.fused;
+        // cursor
+        init(0, P.Q, false);
         if (aux)
             scatter_cursor<true>(a, P, a.keys, a.vals, a.aux_in, nullptr, nullptr, 0, dim3(P.W1, 1), P.W1, 0, 255, a.k2,
                                  a.v2, a.a2, a.cur2, P.capQ, st);
@@ -1264,13 +1271,8 @@ int part_prepare(const PartArgs& a, hipStream_t st, PartOut& o) {
         o.aux = a.a2;
         o.aux_is_pos = aux ? 0 : 1;
     } else if (P.passes == 2 && a.cursor) {
-        // first-level bins, then partitions, each reserved run by run on the bin's cursor; the
-        // fused final pass's look-back words and ticket are cleared in the same launch
-        const uint64_t nzw = a.fused ? 2 * (uint64_t)P.Q : 0;
-        hipLaunchKernelGGL(k_init_cursors, grid_for_count(P.binsA + P.Q + nzw), 256, 0, st, a.cur1, a.begA,
-                           (uint64_t)P.binsA, P.cap1, a.cur2, a.begQ, (uint64_t)P.Q, P.capQ,
-                           reinterpret_cast<uint32_t*>(a.cbase), nzw, a.fused ? a.sqQ : nullptr);
-        o.prezeroed = a.fused;
+        // first-level bins, then partitions, each reserved run by run on the bin's cursor
+        init(P.binsA, P.Q, false);
         if (aux)
             scatter_cursor<true>(a, P, a.keys, a.vals, a.aux_in, nullptr, nullptr, 0, dim3(P.W1, 1), P.W1, P.shiftA,
                                  255, a.k1, a.v1, a.a1, a.cur1, P.cap1, st);

@@ -44,8 +44,19 @@ struct PartPlan {
     uint64_t cap1, capQ;
 };
 
+// What an attempt's set-up does beside the passes' own (nothing when zero): clears the first
+// `words` (at most 256) words at `clear` and writes the T level-two triples of attempt r.
+struct AttemptStart {
+    uint32_t* clear;
+    uint32_t words;
+    Triple* C;
+    uint64_t seed;
+    uint32_t r, T;
+};
+
 // Inputs, scratch and outputs of one attempt (device pointers).
 struct PartArgs {
+    AttemptStart start;         // taken by the passes with cursors and by inputs without passes
     uint64_t n, G;
     bool aux;                   // an aux word travels with every key
     bool str;                   // keys are string fingerprints

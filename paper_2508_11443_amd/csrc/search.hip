@@ -507,18 +507,11 @@ static void separators(const fks_sorted* S, hipStream_t st) {
         hipLaunchKernelGGL(k_separators<false>, grid, 256, 0, st, S->keys, S->sep, S->index);
 }
 
-// pinned words for the outcome of a sort, one pair per host thread, kept for the life of the process
-static SortFlags* pinned_flags() {
-    static thread_local SortFlags* buf = nullptr;
-    if (!buf && hipHostMalloc((void**)&buf, sizeof(SortFlags), hipHostMallocDefault) != hipSuccess) buf = nullptr;
-    return buf;
-}
-
 // The map by sample sort: everything is queued before the one wait for the outcome.
 // kSortAgain: sort another way (a region overflowed, or there is no memory for the regions).
 static int build_sampled(fks_sorted* S, const uint64_t* d_keys, const uint32_t* d_vals, hipStream_t st) {
     const uint64_t n = S->n;
-    SortFlags* host = pinned_flags();
+    SortFlags* host = (SortFlags*)pinned_words();
     void* scratch = dev_alloc(sample_sort_scratch(n), st);
     SortFlags* flags = (SortFlags*)dev_alloc(sizeof(SortFlags), st);
     S->keys = (uint64_t*)dev_alloc(8 * n, st);
@@ -529,8 +522,7 @@ static int build_sampled(fks_sorted* S, const uint64_t* d_keys, const uint32_t* 
     if (rc == FKS_OK) {
         sample_sort(d_keys, d_vals, n, S->layout == 1, S->keys, S->vals, S->sep, S->index, flags, scratch, st);
         hipError_t e = hipGetLastError();
-        if (e == hipSuccess) e = hipMemcpyAsync(host, flags, sizeof(SortFlags), hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        if (e == hipSuccess) e = words_to_host(host, flags, sizeof(SortFlags), st);
         settled = e == hipSuccess;
         if (e != hipSuccess) rc = hip_fail(e);
         else if (host->overflow) rc = kSortAgain;
