@@ -474,7 +474,7 @@ __device__ __forceinline__ bool same_string(const int64_t* off, const uint8_t* b
     return true;
 }
 
-template <bool AUX>
+template <bool AUX, uint32_t BT>
 struct FinalLds {
     uint64_t key[kFinalKeyCap];
     uint32_t val[kFinalKeyCap];
@@ -491,7 +491,7 @@ struct FinalLds {
     uint64_t mag[16];             // remainder magic of s^2, s = 0..15
     Triple tri[kLdsTrials];       // the first level-two triples (larger trials are rare)
     uint32_t nhard;
-    uint32_t wsum[2][kPB / 64];
+    uint32_t wsum[2][BT / 64];
     uint32_t flags[3];   // exhausted, dup, max_t
     uint64_t c0;         // fused form: the partition's first cell, from the look-back
     uint32_t sqtot;      // the partition's sum of squared sizes
@@ -580,8 +580,9 @@ constexpr unsigned kFinalWaves = AUX ? 5u : 6u;
 // rejected before this kernel and is skipped)
 // FUSED: the single map's final pass sizes its own partition and finds its first cell by
 // the look-back above (no separate size pass and scan; grid = Q)
-template <bool AUX, bool STR, bool MULTI = false, bool FUSED = false>
-__global__ __launch_bounds__(kPB) __attribute__((amdgpu_waves_per_eu(kFinalWaves<AUX>))) void k_pfinal(const uint64_t* __restrict__ keys, const uint32_t* __restrict__ vals,
+// BT: threads of the workgroup
+template <bool AUX, bool STR, bool MULTI = false, bool FUSED = false, uint32_t BT = kPB>
+__global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(BT == kPB ? kFinalWaves<AUX> : BT / 256))) void k_pfinal(const uint64_t* __restrict__ keys, const uint32_t* __restrict__ vals,
                                                   const uint32_t* __restrict__ aux, int aux_is_pos, uint64_t n,
                                                   Triple A, uint64_t magic, const uint64_t* __restrict__ offQ,
                                                   const uint64_t* __restrict__ cbase, const uint32_t* __restrict__ sizes,
@@ -594,7 +595,7 @@ __global__ __launch_bounds__(kPB) __attribute__((amdgpu_waves_per_eu(kFinalWaves
                                                   const uint32_t* __restrict__ reject = nullptr,
                                                   uint64_t cap = ~0ull, FuseArgs fa = FuseArgs{}) {
     static_assert(!(MULTI && FUSED), "the fused pass builds one map");
-    __shared__ FinalLds<AUX> L;
+    __shared__ FinalLds<AUX, BT> L;
     const uint32_t tid = threadIdx.x;
     // an attempt already rejected by the size pass (a bucket above 15 keys) or by bad
     // string offsets is skipped (both flags are set before this kernel starts)
@@ -642,13 +643,13 @@ __global__ __launch_bounds__(kPB) __attribute__((amdgpu_waves_per_eu(kFinalWaves
     }
     bool fast = FUSED ? keys_fit : keys_fit && Sq <= kFinalCellCap;
     // the partition's records go in flight first; the set-up below overlaps their latency
-    constexpr uint32_t KPT = (kFinalKeyCap + kPB - 1) / kPB;   // record slots per thread
+    constexpr uint32_t KPT = (kFinalKeyCap + BT - 1) / BT;   // record slots per thread
     uint64_t xk[KPT];
     uint32_t vk[KPT], ak[KPT];
     if (fast) {
 #pragma unroll
         for (uint32_t k = 0; k < KPT; ++k) {
-            const uint32_t i = tid + k * kPB;
+            const uint32_t i = tid + k * BT;
             if (i < nq) {
                 // streaming loads: each record is read once here (and each cell and group
                 // record below written once), so none of them displaces the caches' other data
@@ -661,18 +662,18 @@ __global__ __launch_bounds__(kPB) __attribute__((amdgpu_waves_per_eu(kFinalWaves
     // the first kLdsTrials level-two triples are staged in LDS; larger trials read theirs
     // from global memory
     const Triple* const LC = Cg;
-    for (uint32_t t = tid; t < kLdsTrials && t < T; t += kPB) L.tri[t] = Cg[t];
+    for (uint32_t t = tid; t < kLdsTrials && t < T; t += BT) L.tri[t] = Cg[t];
     auto tri = [&](uint32_t t) { return t < kLdsTrials ? L.tri[t] : Cg[t]; };
     if (!FUSED) {
-        for (uint32_t g = tid; g < kGroupsPerPart; g += kPB)
+        for (uint32_t g = tid; g < kGroupsPerPart; g += BT)
             L.words[g] = (uint64_t)qh * kGroupsPerPart + g < G ? sizes[(uint64_t)q * kGroupsPerPart + g] : 0u;
     }
     if (tid < 3) L.flags[tid] = 0;
     if (FUSED && tid == 0) L.over = 0;
     if (FUSED || fast) {
-        for (uint32_t g = tid; g < kGroupsPerPart; g += kPB) L.cnt2[g] = 0;
-        for (uint32_t b = tid; b < kPartBuckets; b += kPB) L.tb[b] = 0;
-        for (uint32_t w = tid; w < kFinalCellCap / 32; w += kPB) L.occ[w] = 0;
+        for (uint32_t g = tid; g < kGroupsPerPart; g += BT) L.cnt2[g] = 0;
+        for (uint32_t b = tid; b < kPartBuckets; b += BT) L.tb[b] = 0;
+        for (uint32_t w = tid; w < kFinalCellCap / 32; w += BT) L.occ[w] = 0;
         if (tid < kPartBuckets / 32) L.fl[tid] = 0;
         if (tid < 16) L.mag[tid] = tid ? fastmod_magic(tid * tid) : 0;
         if (tid == 0) L.nhard = 0;
@@ -686,7 +687,7 @@ __global__ __launch_bounds__(kPB) __attribute__((amdgpu_waves_per_eu(kFinalWaves
         bool over = false;
 #pragma unroll
         for (uint32_t k = 0; k < KPT; ++k) {
-            const uint32_t i = tid + k * kPB;
+            const uint32_t i = tid + k * BT;
             if (i < nq) {
                 const uint32_t lb = bucket_of(A, magic, (uint32_t)n, xk[k]) & (kPartBuckets - 1);
                 lbk[k] = lb;
@@ -703,7 +704,7 @@ __global__ __launch_bounds__(kPB) __attribute__((amdgpu_waves_per_eu(kFinalWaves
             over = stage();
         } else {
             // too many keys to stage: their sizes from one pass over them
-            for (uint32_t i = tid; i < nq; i += kPB) {
+            for (uint32_t i = tid; i < nq; i += BT) {
                 const uint32_t lb = bucket_of(A, magic, (uint32_t)n, keys[k0 + i]) & (kPartBuckets - 1);
                 const uint32_t sh = 4 * (lb & 7u);
                 over |= ((atomicAdd(&L.cnt2[lb >> 3], 1u << sh) >> sh) & 15u) == 15u;
@@ -711,7 +712,7 @@ __global__ __launch_bounds__(kPB) __attribute__((amdgpu_waves_per_eu(kFinalWaves
         }
         if (over) atomicOr(&L.over, 1u);
         __syncthreads();
-        for (uint32_t g = tid; g < kGroupsPerPart; g += kPB) L.words[g] = L.cnt2[g];
+        for (uint32_t g = tid; g < kGroupsPerPart; g += BT) L.words[g] = L.cnt2[g];
         __syncthreads();
     }
     // group statistics: where each group's keys and cells start inside the partition
@@ -820,7 +821,7 @@ __global__ __launch_bounds__(kPB) __attribute__((amdgpu_waves_per_eu(kFinalWaves
         const Triple c0t = L.tri[0];
 #pragma unroll
         for (uint32_t k = 0; k < KPT; ++k) {
-            const uint32_t i = tid + k * kPB;
+            const uint32_t i = tid + k * BT;
             if (i < nq) {
                 const uint32_t lb = lbk[k], g = lb >> 3, kk = lb & 7u, w = L.words[g];
                 const uint32_t s = nib(w, kk);
@@ -858,7 +859,7 @@ __global__ __launch_bounds__(kPB) __attribute__((amdgpu_waves_per_eu(kFinalWaves
         // Trials: a bucket that trial 0 places keeps t = 0 (tb is zero); given trials (the
         // rounds schedule) are taken as they are
         if (given_t) {
-            for (uint32_t b = tid; b < kPartBuckets; b += kPB) {
+            for (uint32_t b = tid; b < kPartBuckets; b += BT) {
                 if (nib(L.words[b >> 3], b & 7u) < 2) continue;
                 const uint32_t t = given_t[(uint64_t)q * kPartBuckets + b];
                 L.tb[b] = (uint8_t)t;
@@ -869,7 +870,7 @@ __global__ __launch_bounds__(kPB) __attribute__((amdgpu_waves_per_eu(kFinalWaves
         // bucket j goes to lane j / 4 of wave j % 4, so that all four SIMDs search (a packed
         // list of ~80 buckets would otherwise occupy one and a half waves)
         const uint32_t nh = given_t ? 0u : L.nhard;
-        for (uint32_t j = (tid & 63u) * (kPB / 64) + (tid >> 6); j < nh; j += kPB) {
+        for (uint32_t j = (tid & 63u) * (BT / 64) + (tid >> 6); j < nh; j += BT) {
             const uint32_t b = L.hard[j];
             const uint32_t w = L.words[b >> 3];
             const uint32_t sb = nib(w, b & 7u);
@@ -905,7 +906,7 @@ __global__ __launch_bounds__(kPB) __attribute__((amdgpu_waves_per_eu(kFinalWaves
         // every key of a larger bucket writes its own cell
 #pragma unroll
         for (uint32_t k = 0; k < KPT; ++k) {
-            const uint32_t i = tid + k * kPB;
+            const uint32_t i = tid + k * BT;
             if (i < nq) {
                 const uint32_t lb = lbk[k], g = lb >> 3, kk = lb & 7u, w = L.words[g];
                 const uint32_t sb = nib(w, kk);
@@ -925,12 +926,12 @@ __global__ __launch_bounds__(kPB) __attribute__((amdgpu_waves_per_eu(kFinalWaves
         }
         // write-out: indices first (a marked cell resolves to the bucket's lowest
         // occupied cell; every bucket holds a key), then the records
-        constexpr uint32_t CPT = kFinalCellCap / kPB;
-        static_assert(kFinalCellCap % kPB == 0, "whole cells per thread");
+        constexpr uint32_t CPT = kFinalCellCap / BT;
+        static_assert(kFinalCellCap % BT == 0, "whole cells per thread");
         uint32_t idx[CPT];
 #pragma unroll
         for (uint32_t k = 0; k < CPT; ++k) {
-            const uint32_t p = tid + k * kPB;
+            const uint32_t p = tid + k * BT;
             idx[k] = p < Sq ? L.smap[p] : 0u;
         }
 #pragma unroll
@@ -943,7 +944,7 @@ __global__ __launch_bounds__(kPB) __attribute__((amdgpu_waves_per_eu(kFinalWaves
         }
 #pragma unroll
         for (uint32_t k = 0; k < CPT; ++k) {
-            const uint32_t p = tid + k * kPB;
+            const uint32_t p = tid + k * BT;
             if (p < Sq) {
                 const uint32_t i = idx[k];
                 Cell c;
@@ -961,7 +962,7 @@ __global__ __launch_bounds__(kPB) __attribute__((amdgpu_waves_per_eu(kFinalWaves
             lookback();
             if (c0 + Sq > cap) return;   // the whole block
         }
-        for (uint32_t b = tid; b < kPartBuckets; b += kPB) {
+        for (uint32_t b = tid; b < kPartBuckets; b += BT) {
             const uint32_t g = b >> 3, kk = b & 7u, w = L.words[g];
             const uint32_t s = nib(w, kk);
             const uint32_t off = L.gbase[g] + prefix_sq(w, kk);
@@ -1028,7 +1029,7 @@ __global__ __launch_bounds__(kPB) __attribute__((amdgpu_waves_per_eu(kFinalWaves
         }
         __syncthreads();
     }
-    for (uint32_t g = tid; g < kGroupsPerPart; g += kPB) {
+    for (uint32_t g = tid; g < kGroupsPerPart; g += BT) {
         const uint64_t gg = (uint64_t)qh * kGroupsPerPart + g;
         if (gg < G) {
             Group h;
@@ -1370,6 +1371,13 @@ int part_prepare(const PartArgs& a, hipStream_t st, PartOut& o) {
     return e == hipSuccess ? FKS_OK : hip_fail(e);
 }
 
+// Threads per partition.  With few partitions the pass is one workgroup's chain of about 34000
+// cycles (16 us), most of it instructions, and 512 threads shorten it; with many it is bound by
+// the instructions all waves issue, and wider workgroups add barriers.  Build, one lookup and release
+// with 256, 512 and 1024 threads: 2^16 keys 54.7, 51.4 and 50.0 us, 2^19 72.4, 70.5 and 76.7,
+// 2^20 87.0, 90.8 and 102.4, 10^7 285, 373 and 512.
+constexpr uint32_t kWideFinalThreads = 512, kWideFinalParts = 512;
+
 template <bool AUX, bool STR>
 static void launch_fused(const PartArgs& a, const PartOut& o, const Triple* C, uint32_t T, Group* header, Cell* slots,
                          uint32_t* flags, const int64_t* ctx_off, const uint8_t* ctx_bytes, const uint32_t* reject,
@@ -1383,11 +1391,14 @@ static void launch_fused(const PartArgs& a, const PartOut& o, const Triple* C, u
         if (a.ticketed) hipLaunchKernelGGL(k_zero_words, 1, 64, 0, st, a.sqQ, (uint64_t)1);
     }
     const FuseArgs fa{a.cbase, a.ticketed ? a.sqQ : nullptr, a.S_dev, a.oversize, a.stalled, Q, o.qend, o.qcap};
-    FKS_TIMED("fks_part_final", st,
-              hipLaunchKernelGGL((k_pfinal<AUX, STR, false, true>), Q, kPB, 0, st, o.keys, o.vals,
-                                 AUX ? o.aux : nullptr, AUX ? o.aux_is_pos : 1, a.n, a.A, a.magic, o.qbeg, a.cbase,
-                                 a.sizes, a.G, C, T, header, slots, flags, ctx_off, ctx_bytes, nullptr, nullptr,
-                                 reject, cap, fa));
+    auto launch = [&](auto kernel, uint32_t threads) {
+        FKS_TIMED("fks_part_final", st,
+                  hipLaunchKernelGGL(kernel, Q, threads, 0, st, o.keys, o.vals, AUX ? o.aux : nullptr,
+                                     AUX ? o.aux_is_pos : 1, a.n, a.A, a.magic, o.qbeg, a.cbase, a.sizes, a.G, C, T,
+                                     header, slots, flags, ctx_off, ctx_bytes, nullptr, nullptr, reject, cap, fa));
+    };
+    if (Q <= kWideFinalParts) launch(k_pfinal<AUX, STR, false, true, kWideFinalThreads>, kWideFinalThreads);
+    else launch(k_pfinal<AUX, STR, false, true>, kPB);
 }
 
 int part_finish(const PartArgs& a, PartOut& o, const Triple* C, uint32_t T, Group* header, Cell* slots,
