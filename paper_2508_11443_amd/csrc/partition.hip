@@ -474,24 +474,59 @@ __device__ __forceinline__ bool same_string(const int64_t* off, const uint8_t* b
     return true;
 }
 
+// Keys (14 bits: at most 15 * 1024) and cells (18 bits: at most 225 * 1024) of a partition up to some
+// point, in one word, so that one scan and one LDS read serve both.
+__device__ __forceinline__ uint32_t pos_of(uint32_t keys, uint32_t cells) { return cells << 14 | keys; }
+__device__ __forceinline__ uint32_t pos_keys(uint32_t pos) { return pos & 0x3FFFu; }
+__device__ __forceinline__ uint32_t pos_cells(uint32_t pos) { return pos >> 14; }
+// of the buckets in a size word: byte-wise dot products over its even and its odd nibbles
+__device__ __forceinline__ uint32_t word_pos(uint32_t w) {
+    const uint32_t e = w & 0x0F0F0F0Fu, o = (w >> 4) & 0x0F0F0F0Fu;
+    return pos_of(__builtin_amdgcn_udot4(e, 0x01010101u, __builtin_amdgcn_udot4(o, 0x01010101u, 0u, false), false),
+                  __builtin_amdgcn_udot4(e, e, __builtin_amdgcn_udot4(o, o, 0u, false), false));
+}
+// where bucket kk of a group starts: its group's start and the buckets before it
+__device__ __forceinline__ uint32_t bucket_pos(uint64_t gpos, uint32_t kk) {
+    return (uint32_t)(gpos >> 32) + word_pos((uint32_t)gpos & ~(~0u << (4 * kk)));
+}
+
+// inclusive prefix sums over the wave's lanes (all active)
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);   // from 1 lane to the left, by rows of 16
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);   // lane 15 of a row to rows 1 and 3
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);   // lane 31 to the upper half
+    return v;
+}
+
+// remainder magic of s^2 for s = 1..15 (fastmod_magic, whose 64-bit division is a chain of a
+// hundred instructions)
+struct SquareMagics {
+    uint64_t m[16];
+    constexpr SquareMagics() : m() {
+        for (uint32_t s = 1; s < 16; ++s) m[s] = 0xFFFFFFFFFFFFFFFFull / (s * s) + 1;
+    }
+};
+__constant__ const SquareMagics kSquareMagics{};
+
 template <bool AUX, uint32_t BT>
 struct FinalLds {
     uint64_t key[kFinalKeyCap];
     uint32_t val[kFinalKeyCap];
     uint32_t aux[AUX ? kFinalKeyCap : 1];
     uint16_t smap[kFinalCellCap];
-    uint32_t words[kGroupsPerPart];
-    uint32_t cnt2[kGroupsPerPart];
-    uint32_t gks[kGroupsPerPart];
-    uint32_t gbase[kGroupsPerPart];
-    uint8_t tb[kPartBuckets];
+    uint32_t cnt2[kGroupsPerPart];      // bucket sizes counted while ranking, 4 bits each
+    uint64_t gpos[kGroupsPerPart];      // a group's size word, and above it where its keys and cells start (pos_of)
+    alignas(4) uint8_t tb[kPartBuckets];
     uint32_t occ[kFinalCellCap / 32];   // cells taken by trial 0
     uint32_t fl[kPartBuckets / 32];     // buckets where trial 0 collides
     uint16_t hard[kFinalKeyCap / 2];   // buckets of two or more keys that trial 0 does not place
     uint64_t mag[16];             // remainder magic of s^2, s = 0..15
     Triple tri[kLdsTrials];       // the first level-two triples (larger trials are rare)
     uint32_t nhard;
-    uint32_t wsum[2][BT / 64];
+    uint32_t wsum;       // the first wave's groups
     uint32_t flags[3];   // exhausted, dup, max_t
     uint64_t c0;         // fused form: the partition's first cell, from the look-back
     uint32_t sqtot;      // the partition's sum of squared sizes
@@ -664,22 +699,25 @@ __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(BT == kPB ? 
     const Triple* const LC = Cg;
     for (uint32_t t = tid; t < kLdsTrials && t < T; t += BT) L.tri[t] = Cg[t];
     auto tri = [&](uint32_t t) { return t < kLdsTrials ? L.tri[t] : Cg[t]; };
-    if (!FUSED) {
-        for (uint32_t g = tid; g < kGroupsPerPart; g += BT)
-            L.words[g] = (uint64_t)qh * kGroupsPerPart + g < G ? sizes[(uint64_t)q * kGroupsPerPart + g] : 0u;
-    }
+    // the size words of the separate size pass (the fused form takes the counts of the ranking)
+    uint32_t word = 0;
+    if (!FUSED && tid < kGroupsPerPart && (uint64_t)qh * kGroupsPerPart + tid < G)
+        word = sizes[(uint64_t)q * kGroupsPerPart + tid];
+    static_assert(BT >= kGroupsPerPart, "a thread per group");
     if (tid < 3) L.flags[tid] = 0;
     if (FUSED && tid == 0) L.over = 0;
     if (FUSED || fast) {
-        for (uint32_t g = tid; g < kGroupsPerPart; g += BT) L.cnt2[g] = 0;
-        for (uint32_t b = tid; b < kPartBuckets; b += BT) L.tb[b] = 0;
+        if (tid < kGroupsPerPart) L.cnt2[tid] = 0;
+        if (tid < kPartBuckets / 4) reinterpret_cast<uint32_t*>(L.tb)[tid] = 0;
+        static_assert(BT >= kPartBuckets / 4, "a thread per word of trial bytes");
         for (uint32_t w = tid; w < kFinalCellCap / 32; w += BT) L.occ[w] = 0;
         if (tid < kPartBuckets / 32) L.fl[tid] = 0;
-        if (tid < 16) L.mag[tid] = tid ? fastmod_magic(tid * tid) : 0;
+        if (tid < 16) L.mag[tid] = kSquareMagics.m[tid];
         if (tid == 0) L.nhard = 0;
     }
     __syncthreads();
-    uint32_t lbk[KPT], rk[KPT], c0k[KPT];
+    uint32_t lbk[KPT], rk[KPT], c0k[KPT];   // c0k: bucket size, first cell and trial-0 cell
+    static_assert(kFinalCellCap <= 4096, "12 bits for a cell of the partition");
     // rank the partition's records (when they fit) in their buckets: ranks come from an LDS
     // histogram of the 4-bit bucket sizes, which the fused form also takes as the
     // partition's sizes.  The records stay in registers until they are grouped.
@@ -712,52 +750,25 @@ __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(BT == kPB ? 
         }
         if (over) atomicOr(&L.over, 1u);
         __syncthreads();
-        for (uint32_t g = tid; g < kGroupsPerPart; g += BT) L.words[g] = L.cnt2[g];
-        __syncthreads();
+        if (tid < kGroupsPerPart) word = L.cnt2[tid];
     }
-    // group statistics: where each group's keys and cells start inside the partition
+    // where each group's keys and cells start inside the partition
     {
-        uint32_t c = 0, s2 = 0;
-        if (tid < kGroupsPerPart) {
-            const uint32_t w = L.words[tid];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const uint32_t s = nib(w, k);
-                c += s;
-                s2 += s * s;
-            }
-        }
-        uint32_t ic = c, is = s2;
-        const int lane = tid & 63, wv = tid >> 6;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const uint32_t uc = __shfl_up(ic, d, 64), us = __shfl_up(is, d, 64);
-            if (lane >= d) {
-                ic += uc;
-                is += us;
-            }
-        }
-        if (lane == 63) {
-            L.wsum[0][wv] = ic;
-            L.wsum[1][wv] = is;
-        }
+        const uint32_t own = word_pos(word), inc = wave_scan(own);
+        static_assert(kGroupsPerPart == 128, "two waves hold the groups");
+        if (tid == 63) L.wsum = inc;
         __syncthreads();
-        uint32_t pc = 0, ps = 0;
-        for (int w = 0; w < wv; ++w) {
-            pc += L.wsum[0][w];
-            ps += L.wsum[1][w];
-        }
-        if (tid < kGroupsPerPart) {
-            L.gks[tid] = pc + ic - c;
-            L.gbase[tid] = ps + is - s2;
-        }
-        if (tid == kGroupsPerPart - 1) L.sqtot = ps + is;
+        const uint32_t all = inc + (tid >= 64 ? L.wsum : 0u);
+        if (tid < kGroupsPerPart) L.gpos[tid] = (uint64_t)(all - own) << 32 | word;
+        if (tid == kGroupsPerPart - 1) L.sqtot = pos_cells(all);
     }
     // fused form: the partition's first cell, from the predecessors' published sums back to
     // the nearest published inclusive prefix (64 per round: lane l reads partition
     // end - 1 - l); then this partition's inclusive prefix is published.  Called by the
-    // whole workgroup just before the cells are written, when the predecessors' sums, which
-    // each publishes as soon as it has sized its buckets, are there to read.
+    // whole workgroup as late as can be, when its cells are known and only their addresses are
+    // not: the predecessors' sums, which each publishes as soon as it has sized its buckets, are there
+    // to read, and the nearer an inclusive prefix is, the fewer rounds.  Final pass of 10^7 keys 139 us; before the cells'
+    // indices are read 158, and 196 by a wave of its own while the others group the records.
     auto lookback = [&]() {
         if (tid < 64) {
             const uint32_t lane = tid;
@@ -823,10 +834,10 @@ __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(BT == kPB ? 
         for (uint32_t k = 0; k < KPT; ++k) {
             const uint32_t i = tid + k * BT;
             if (i < nq) {
-                const uint32_t lb = lbk[k], g = lb >> 3, kk = lb & 7u, w = L.words[g];
-                const uint32_t s = nib(w, kk);
-                const uint32_t off = L.gbase[g] + prefix_sq(w, kk);
-                const uint32_t slot = L.gks[g] + prefix_cnt(w, kk) + rk[k];
+                const uint32_t lb = lbk[k], kk = lb & 7u;
+                const uint64_t gp = L.gpos[lb >> 3];
+                const uint32_t s = nib((uint32_t)gp, kk), pos = bucket_pos(gp, kk);
+                const uint32_t off = pos_cells(pos), slot = pos_keys(pos) + rk[k];
                 if (s >= 2) {
                     // the key of rank r marks cells [r*s, r*s + s) of its bucket with the
                     // bucket's first cell; placement below overwrites the cells keys take, and
@@ -839,7 +850,7 @@ __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(BT == kPB ? 
                 L.key[slot] = xk[k];
                 L.val[slot] = vk[k];
                 if (AUX) L.aux[slot] = ak[k];
-                c0k[k] = off;
+                c0k[k] = s << 24 | off << 12 | off;
                 const uint32_t h0 = mshash(c0t, xk[k]);   // trial 0
                 if (s == 1) {
                     L.smap[off] = (uint16_t)slot;
@@ -847,7 +858,7 @@ __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(BT == kPB ? 
                 } else {
                     if (!given_t) {
                         const uint32_t cell = off + fastmod(h0, L.mag[s], s * s);
-                        c0k[k] = cell;
+                        c0k[k] = s << 24 | off << 12 | cell;
                         const uint32_t bit = 1u << (cell & 31u), bb = 1u << (lb & 31u);
                         if ((atomicOr(&L.occ[cell >> 5], bit) & bit) && !(atomicOr(&L.fl[lb >> 5], bb) & bb))
                             L.hard[atomicAdd(&L.nhard, 1u)] = (uint16_t)lb;
@@ -860,7 +871,7 @@ __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(BT == kPB ? 
         // rounds schedule) are taken as they are
         if (given_t) {
             for (uint32_t b = tid; b < kPartBuckets; b += BT) {
-                if (nib(L.words[b >> 3], b & 7u) < 2) continue;
+                if (nib((uint32_t)L.gpos[b >> 3], b & 7u) < 2) continue;
                 const uint32_t t = given_t[(uint64_t)q * kPartBuckets + b];
                 L.tb[b] = (uint8_t)t;
                 if (t) atomicMax(&L.flags[2], t);
@@ -872,9 +883,9 @@ __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(BT == kPB ? 
         const uint32_t nh = given_t ? 0u : L.nhard;
         for (uint32_t j = (tid & 63u) * (BT / 64) + (tid >> 6); j < nh; j += BT) {
             const uint32_t b = L.hard[j];
-            const uint32_t w = L.words[b >> 3];
-            const uint32_t sb = nib(w, b & 7u);
-            const uint32_t kst = L.gks[b >> 3] + prefix_cnt(w, b & 7u);
+            const uint64_t gp = L.gpos[b >> 3];
+            const uint32_t sb = nib((uint32_t)gp, b & 7u);
+            const uint32_t kst = pos_keys(bucket_pos(gp, b & 7u));
             uint32_t t;
             if (sb <= 8) {
                 const uint32_t smax = wave_max16(sb);
@@ -908,22 +919,17 @@ __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(BT == kPB ? 
         for (uint32_t k = 0; k < KPT; ++k) {
             const uint32_t i = tid + k * BT;
             if (i < nq) {
-                const uint32_t lb = lbk[k], g = lb >> 3, kk = lb & 7u, w = L.words[g];
-                const uint32_t sb = nib(w, kk);
+                const uint32_t sb = c0k[k] >> 24;
                 if (sb >= 2) {
-                    const uint32_t t = L.tb[lb];
-                    const uint32_t cell = (t || given_t) ? L.gbase[g] + prefix_sq(w, kk) +
-                                                               fastmod(mshash(tri(t), L.key[rk[k]]), L.mag[sb], sb * sb)
-                                                         : c0k[k];
+                    const uint32_t t = L.tb[lbk[k]];
+                    uint32_t cell = c0k[k] & 0xFFFu;
+                    if (t || given_t)
+                        cell = (c0k[k] >> 12 & 0xFFFu) + fastmod(mshash(tri(t), L.key[rk[k]]), L.mag[sb], sb * sb);
                     L.smap[cell] = (uint16_t)rk[k];
                 }
             }
         }
         __syncthreads();
-        if (FUSED) {
-            lookback();
-            if (c0 + Sq > cap) return;   // the whole block
-        }
         // write-out: indices first (a marked cell resolves to the bucket's lowest
         // occupied cell; every bucket holds a key), then the records
         constexpr uint32_t CPT = kFinalCellCap / BT;
@@ -941,6 +947,10 @@ __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(BT == kPB ? 
                 for (uint32_t p2 = idx[k] & 0x7FFFu; (i = L.smap[p2]) & 0x8000u; ++p2) {}
                 idx[k] = i;
             }
+        }
+        if (FUSED) {
+            lookback();
+            if (c0 + Sq > cap) return;   // the whole block
         }
 #pragma unroll
         for (uint32_t k = 0; k < CPT; ++k) {
@@ -963,9 +973,9 @@ __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(BT == kPB ? 
             if (c0 + Sq > cap) return;   // the whole block
         }
         for (uint32_t b = tid; b < kPartBuckets; b += BT) {
-            const uint32_t g = b >> 3, kk = b & 7u, w = L.words[g];
-            const uint32_t s = nib(w, kk);
-            const uint32_t off = L.gbase[g] + prefix_sq(w, kk);
+            const uint64_t gp = L.gpos[b >> 3];
+            const uint32_t s = nib((uint32_t)gp, b & 7u);
+            const uint32_t off = pos_cells(bucket_pos(gp, b & 7u));
             uint64_t mine[kSMax];
             uint32_t pos[kSMax];
             uint32_t got = 0;
@@ -1033,8 +1043,8 @@ __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(BT == kPB ? 
         const uint64_t gg = (uint64_t)qh * kGroupsPerPart + g;
         if (gg < G) {
             Group h;
-            h.base = (uint32_t)(c0 + L.gbase[g]);
-            h.sizes = L.words[g];
+            h.base = (uint32_t)(c0 + pos_cells((uint32_t)(L.gpos[g] >> 32)));
+            h.sizes = (uint32_t)L.gpos[g];
             h.t_lo = (uint32_t)L.tb[8 * g] | ((uint32_t)L.tb[8 * g + 1] << 8) | ((uint32_t)L.tb[8 * g + 2] << 16) |
                      ((uint32_t)L.tb[8 * g + 3] << 24);
             h.t_hi = (uint32_t)L.tb[8 * g + 4] | ((uint32_t)L.tb[8 * g + 5] << 8) |
