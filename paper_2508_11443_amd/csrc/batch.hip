@@ -469,21 +469,10 @@ __global__ __launch_bounds__(BT) void k_batch_build(
     }
 }
 
-// level-two triples of attempt 0 of every wide map
-__global__ void k_wconsts(const WideSeg* __restrict__ segs, const BDesc* __restrict__ bdesc, uint32_t nseg,
-                          uint32_t T, Triple* __restrict__ Cpool) {
-    const uint64_t total = (uint64_t)nseg * T;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total;
-         i += (uint64_t)gridDim.x * blockDim.x) {
-        const uint32_t m = segs[i / T].map, t = (uint32_t)(i % T);
-        Cpool[(uint64_t)m * T + t] = level2_triple(bdesc[m].seed, 0, t);
-    }
-}
-
 // outcome of every wide map: accepted at attempt 0, or left pending (status 1) for
 // the per-workgroup kernel, which retries it from attempt 0 on
 __global__ void k_wfinish(const WideSeg* __restrict__ segs, uint32_t nseg, const uint32_t* __restrict__ flags,
-                          const uint64_t* __restrict__ cbase, uint32_t T, BDesc* __restrict__ bdesc,
+                          const uint64_t* __restrict__ S, uint32_t T, BDesc* __restrict__ bdesc,
                           LDesc* __restrict__ ldesc) {
     for (uint32_t b = blockIdx.x * blockDim.x + threadIdx.x; b < nseg; b += gridDim.x * blockDim.x) {
         const WideSeg& sg = segs[b];
@@ -491,7 +480,7 @@ __global__ void k_wfinish(const WideSeg* __restrict__ segs, uint32_t nseg, const
         BDesc d = bdesc[sg.map];
         d.status = FKS_OK;
         d.r = 0;
-        d.S = (uint32_t)cbase[(uint64_t)b * (kSegParts + 1) + kSegParts];
+        d.S = (uint32_t)S[b];
         d.max_t = flags[4 * b + 3];
         bdesc[sg.map] = d;
         LDesc ld;
@@ -667,7 +656,11 @@ namespace fks {
 // bit 8: maps of at least kWideMin keys are built by the partition passes, all of them
 // together, before the per-workgroup kernel builds the rest
 constexpr uint32_t kScheduleWide = 0x100;
-constexpr uint32_t kWideMin = 8192;
+// Builds with the limit at 8192, 4096, 2048 and 1024 keys: 4096 maps of 16-65536 keys 1008, 949, 935
+// and 929 us, 512 of them 290, 256, 247 and 234, 100 maps of 16-20000 keys 208, 158, 157 and 139,
+// but 4096 maps of 16-4096 keys 354, 356, 432 and 423 (a map's only tile and partitions are
+// mostly empty there).
+constexpr uint32_t kWideMin = 4096;
 static bool decode_schedule(uint32_t sched, int& bt, int& per_cu) {
     const uint32_t b = sched & 3u;
     per_cu = (int)((sched >> 4) & 15u);
@@ -793,6 +786,45 @@ extern "C" int fks_build_batch_u64(const uint64_t* d_keys, const uint32_t* d_val
     for (uint32_t m = 0; m < M; ++m) order[m] = m;
     std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) { return sizes[a] > sizes[b]; });
 
+    uint32_t sched = schedule;
+    if (sched == 0) {
+        std::lock_guard<std::mutex> lk(g_tune_mu);
+        sched = default_schedule();
+        const uint64_t key = batch_class_key(M, total);
+        for (auto& kv : g_tuned)
+            if (kv.first == key) sched = kv.second;
+    }
+    B->schedule = sched;
+    // large maps: attempt 0 of all of them by the partition passes, whose records lie where the
+    // per-workgroup kernel stages its own afterwards
+    std::vector<WideSeg> segs;   // lives until the host has waited
+    uint64_t parts = 0, tiles = 0;
+    if (sched & kScheduleWide) {
+        for (uint32_t m : order) {
+            const BDesc& d = B->host[m];
+            if (d.n < kWideMin || parts + kSegParts > wide_parts_max()) break;
+            WideSeg sg;
+            sg.A = level1_triple(d.seed, 0);
+            sg.magic = fastmod_magic(d.n);
+            sg.seed = d.seed;
+            sg.in_lo = d.key_off;
+            sg.in_hi = d.key_off + d.n;
+            sg.hdr_off = d.hdr_off;
+            sg.slot_off = d.slot_off;
+            sg.n = d.n;
+            sg.G = (d.n + 7) / 8;
+            sg.map = m;
+            sg.c = P.c;
+            sg.part0 = (uint32_t)parts;
+            sg.tile0 = (uint32_t)tiles;
+            sg.tiles = wide_tiles(d.n);
+            parts += (d.n + kPartBuckets - 1) / kPartBuckets;
+            tiles += sg.tiles;
+            segs.push_back(sg);
+        }
+    }
+    const uint32_t nseg = (uint32_t)segs.size();
+    const size_t staging = std::max<size_t>(16 * total, wide_scratch_bytes(nseg, parts, tiles));
     B->bdesc = (BDesc*)dev_alloc(sizeof(BDesc) * M, st);
     B->ldesc = (LDesc*)dev_alloc(sizeof(LDesc) * M, st);
     B->Cpool = (Triple*)dev_alloc(sizeof(Triple) * (uint64_t)M * P.T, st);
@@ -802,7 +834,7 @@ extern "C" int fks_build_batch_u64(const uint64_t* d_keys, const uint32_t* d_val
     uint32_t* d_queue = d_order ? d_order + M + (64 - (M % 64)) % 64 : nullptr;   // own cache line
     uint8_t* rank_s = (uint8_t*)dev_alloc(total ? total : 1, st);
     uint2* gscan_s = (uint2*)dev_alloc(8 * (groups ? groups : 1), st);
-    Cell* grouped_s = (Cell*)dev_alloc(16 * (total ? total : 1), st);
+    Cell* grouped_s = (Cell*)dev_alloc(staging ? staging : 16, st);
     std::vector<void*> wide;   // the partition passes' scratch
     auto cleanup_scratch = [&](bool settled) {
         for (void* p : {(void*)d_order, (void*)rank_s, (void*)gscan_s, (void*)grouped_s}) dev_free(p, st, settled);
@@ -823,75 +855,39 @@ extern "C" int fks_build_batch_u64(const uint64_t* d_keys, const uint32_t* d_val
         batch_release(B, st);
         return hip_fail(e);
     }
-    uint32_t sched = schedule;
-    if (sched == 0) {
-        std::lock_guard<std::mutex> lk(g_tune_mu);
-        sched = default_schedule();
-        const uint64_t key = batch_class_key(M, total);
-        for (auto& kv : g_tuned)
-            if (kv.first == key) sched = kv.second;
-    }
-    B->schedule = sched;
     int rc = FKS_OK;
     int dummy_bt, dummy_cu;
     if (!decode_schedule(sched, dummy_bt, dummy_cu)) rc = FKS_EINVAL;
-    uint32_t count = M;
-    std::vector<WideSeg> segs;   // lives until the host has waited
-    if (rc == FKS_OK && (sched & kScheduleWide)) {
-        // large maps: attempt 0 of all of them by the partition passes; the order list then
-        // holds only the small maps, and a large map that the passes reject follows below
-        uint64_t wide_keys = 0;
-        for (uint32_t m = 0; m < M; ++m) {
-            const BDesc& d = B->host[m];
-            if (d.n < kWideMin) continue;
-            WideSeg sg;
-            sg.A = level1_triple(d.seed, 0);
-            sg.magic = fastmod_magic(d.n);
-            sg.in_lo = d.key_off;
-            sg.in_hi = d.key_off + d.n;
-            sg.hdr_off = d.hdr_off;
-            sg.slot_off = d.slot_off;
-            sg.n = d.n;
-            sg.G = (d.n + 7) / 8;
-            sg.map = m;
-            sg.c = P.c;
-            segs.push_back(sg);
-            wide_keys += d.n;
+    if (rc == FKS_OK && nseg) {
+        // the order list then serves the small maps alone, which are its end, and a large map that
+        // the passes reject follows below
+        WideSeg* d_segs = (WideSeg*)dev_alloc(sizeof(WideSeg) * nseg, st);
+        uint32_t* d_flags = (uint32_t*)dev_alloc(16 * (size_t)nseg, st);
+        uint64_t* d_S = nullptr;
+        wide = {d_segs, d_flags};
+        if (!d_segs || !d_flags) rc = FKS_ENOMEM;
+        if (rc == FKS_OK) {
+            e = hipMemcpyAsync(d_segs, segs.data(), sizeof(WideSeg) * nseg, hipMemcpyHostToDevice, st);
+            if (e != hipSuccess) rc = hip_fail(e);
         }
-        if (!segs.empty()) {
-            const uint32_t nseg = (uint32_t)segs.size(), W = 2;
-            WideSeg* d_segs = (WideSeg*)dev_alloc(sizeof(WideSeg) * nseg, st);
-            uint32_t* d_flags = (uint32_t*)dev_alloc(16 * (size_t)nseg, st);
-            uint64_t* d_cbase = (uint64_t*)dev_alloc(8 * (size_t)nseg * (kSegParts + 1), st);
-            void* d_scratch = dev_alloc(wide_scratch_bytes(wide_keys, nseg, W), st);
-            if (!d_segs || !d_flags || !d_cbase || !d_scratch) rc = FKS_ENOMEM;
-            if (rc == FKS_OK) {
-                e = hipMemcpyAsync(d_segs, segs.data(), sizeof(WideSeg) * nseg, hipMemcpyHostToDevice, st);
-                if (e != hipSuccess) rc = hip_fail(e);
-            }
-            if (rc == FKS_OK) {
-                hipLaunchKernelGGL(k_wconsts, (unsigned)std::min<uint64_t>(4096, ((uint64_t)nseg * P.T + 255) / 256),
-                                   256, 0, st, d_segs, B->bdesc, nseg, P.T, B->Cpool);
-                rc = wide_build(d_keys, d_vals, d_segs, nseg, wide_keys, W, B->Cpool, P.T, B->hdr_pool,
-                                B->slot_pool, d_flags, d_cbase, d_scratch, st);
-            }
-            if (rc == FKS_OK) {
-                hipLaunchKernelGGL(k_wfinish, (nseg + 255) / 256, 256, 0, st, d_segs, nseg, d_flags, d_cbase, P.T,
-                                   B->bdesc, B->ldesc);
-                e = hipGetLastError();
-                if (e != hipSuccess) rc = hip_fail(e);
-            }
-            wide = {d_segs, d_flags, d_cbase, d_scratch};
+        if (rc == FKS_OK)
+            rc = wide_build(d_keys, d_vals, d_segs, nseg, parts, tiles, B->Cpool, P.T, B->hdr_pool, B->slot_pool, d_flags,
+                            &d_S, grouped_s, st);
+        if (rc == FKS_OK) {
+            hipLaunchKernelGGL(k_wfinish, (nseg + 255) / 256, 256, 0, st, d_segs, nseg, d_flags, d_S, P.T, B->bdesc,
+                               B->ldesc);
+            e = hipGetLastError();
+            if (e != hipSuccess) rc = hip_fail(e);
         }
-        count = M - (uint32_t)segs.size();   // the small maps are the end of the list
     }
+    const uint32_t count = M - nseg;
     if (rc == FKS_OK) rc = launch_batch(B, d_keys, d_vals, d_order + (M - count), count, d_queue, rank_s, gscan_s, grouped_s, sched, st);
     if (rc == FKS_OK) {
         e = hipMemcpyAsync(B->host.data(), B->bdesc, sizeof(BDesc) * M, hipMemcpyDeviceToHost, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);
         if (e != hipSuccess) rc = hip_fail(e);
     }
-    if (rc == FKS_OK && (sched & kScheduleWide)) {
+    if (rc == FKS_OK && nseg) {
         // large maps the partition passes left pending go through the per-workgroup kernel
         std::vector<uint32_t> pending;
         for (uint32_t m = 0; m < M; ++m)

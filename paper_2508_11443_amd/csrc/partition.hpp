@@ -12,18 +12,31 @@ constexpr uint32_t kPartBits = 10;                   // 1024 buckets per partiti
 constexpr uint32_t kPartBuckets = 1u << kPartBits;
 
 // A map of a batch built by the partition passes instead of a single workgroup
-// ("wide" map, at most 65536 keys, so at most kSegParts partitions).  Global
-// partition index = segment * kSegParts + partition within the map.
+// ("wide" map, at most 65536 keys, so at most kSegParts partitions).
 constexpr uint32_t kSegParts = 64;
 struct WideSeg {
     Triple A;            // level-one triple of attempt 0
     uint64_t magic;      // remainder magic of n
+    uint64_t seed;
     uint64_t in_lo, in_hi;   // the map's keys in the batch input
     uint64_t hdr_off;    // first group record of the map in the header pool
     uint64_t slot_off;   // first cell of the map in the cell pool
     uint32_t n, G;       // keys, groups of eight buckets
     uint32_t map;        // index of the map in the batch
     uint32_t c;          // space factor: the attempt fails when the map's cells exceed c*n
+    uint32_t part0;      // its first entry in the list of partitions (ceil(n / 1024) of them) ...
+    uint32_t tile0, tiles;   // ... and in the list of scatter tiles
+};
+
+// Device lists and scratch of wide_build.
+struct WideLists {
+    uint64_t* keys;      // records, a region per partition
+    uint32_t* vals;
+    unsigned long long* cursor;   // every partition's end
+    uint64_t* state;     // look-back words
+    uint64_t* S;         // cells of every map
+    uint2* tiles;        // segment, first record within the map
+    uint32_t* parts;     // segment * kSegParts + partition within the map
 };
 
 // Radix passes over the partition index q (bits_q bits), at most 8 bits (256 bins) each:
@@ -119,17 +132,17 @@ PartPlan part_plan(uint64_t n);
 size_t part_scratch(const PartPlan& plan, uint64_t n, bool carry, bool cursor, bool sizes, char* base, PartArgs* a);
 
 // The partition passes over the wide maps of a batch (attempt 0 of each).  Inputs:
-// d_keys/d_vals (the batch input), segs (nseg device descriptors), Cpool (the maps'
-// level-two triples, T per map, at index map*T), pools.  Scratch: as allocated by the
-// caller (see wide_scratch_bytes).  Per-map outcome words flags[4*seg + 0..3]: nonzero
-// word 0 = attempt rejected (a bucket over 15 keys, or more than c*n cells), word 1 =
-// a bucket exhausted its trials, word 2 = that bucket holds equal keys, word 3 = max trial.
-// cbase[seg*(kSegParts+1) + j] receives the partition cell offsets within the map, and
-// entry kSegParts the map's cell count S.
-size_t wide_scratch_bytes(uint64_t nkeys, uint32_t nseg, uint32_t W);
-int wide_build(const uint64_t* d_keys, const uint32_t* d_vals, const WideSeg* segs, uint32_t nseg, uint64_t nkeys,
-               uint32_t W, const Triple* Cpool, uint32_t T, Group* hdr_pool, Cell* slot_pool, uint32_t* flags,
-               uint64_t* cbase, void* scratch, hipStream_t st);
+// d_keys/d_vals (the batch input), segs (nseg device descriptors), pools; Cpool receives the maps'
+// level-two triples (T per map, at index map*T).  Per-map outcome words flags[4*seg + 0..3]: nonzero
+// word 0 = attempt rejected (a bucket over 15 keys, more than c*n cells, an overflowing region or a
+// stalled look-back), word 1 = a bucket exhausted its trials, word 2 = that bucket holds equal
+// keys, word 3 = max trial.  *S points into the scratch, to every map's cells.
+uint32_t wide_tiles(uint32_t n);      // scatter tiles of a map of n keys
+uint64_t wide_parts_max();            // most partitions of a call
+size_t wide_scratch_bytes(uint32_t nseg, uint64_t parts, uint64_t tiles);
+int wide_build(const uint64_t* d_keys, const uint32_t* d_vals, const WideSeg* segs, uint32_t nseg, uint64_t parts,
+               uint64_t tiles, Triple* Cpool, uint32_t T, Group* hdr_pool, Cell* slot_pool, uint32_t* flags,
+               uint64_t** S, void* scratch, hipStream_t st);
 uint64_t part_scan_tiles(const PartPlan& P);
 int part_prepare(const PartArgs& a, hipStream_t st, PartOut& o);
 // given_t: trial index of every bucket decided elsewhere (n bytes), or nullptr to search.
