@@ -96,6 +96,88 @@ __global__ __launch_bounds__(kBlock) void k_fingerprint(const int64_t* __restric
     if (bad) atomicOr(&ctrl->bad_input, 1u);
 }
 
+constexpr uint32_t kStageBytes = 64 * 64 + 32;   // of a wave's 64 strings
+
+// The fingerprints, and the map's copy of the offsets and bytes (both 16-byte aligned) in the
+// same pass: a wave reads the bytes of its 64 strings, which lie one after the other, as aligned 16-byte
+// pieces into LDS, writes the pieces that start inside them to the copy, and its lanes take their
+// strings from LDS.  The bytes before the first and after the last string are copied too.  2^22
+// strings of 4-64 bytes: 99 us (3.9 TB/s, and 16 steps of 64-bit products for all lanes of a
+// wave); two copies and a pass that read each string from memory by its lane took 15 + 50 + 81 us.
+__global__ __launch_bounds__(kBlock) void k_fingerprint_copy(const int64_t* __restrict__ off,
+                                                           const uint8_t* __restrict__ bytes, uint64_t nbytes,
+                                                           uint64_t n, uint64_t beta, uint64_t* __restrict__ y,
+                                                           int64_t* __restrict__ off_copy,
+                                                           uint8_t* __restrict__ bytes_copy, Ctrl* ctrl) {
+    __shared__ u32x4 stage[kBlock / 64][kStageBytes / 16];
+    u32x4* const mine = stage[threadIdx.x >> 6];
+    const uint32_t* const words = reinterpret_cast<const uint32_t*>(mine);
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint64_t wave = ((uint64_t)blockIdx.x * kBlock + threadIdx.x) >> 6, waves = (uint64_t)gridDim.x * (kBlock / 64);
+    auto copy_piece = [&](uint64_t at, const u32x4& v) {
+        if (at + 16 <= nbytes) {
+            __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(bytes_copy + at));
+        } else {
+            for (uint64_t k = at; k < nbytes; ++k) bytes_copy[k] = bytes[k];
+        }
+    };
+    bool bad = false;
+    for (uint64_t i0 = wave * 64; i0 < n; i0 += waves * 64) {   // the same for all lanes of a wave
+        const uint64_t i = i0 + lane;
+        const bool live = i < n;
+        const int64_t a = live ? off[i] : 0, b = live ? off[i + 1] : 0;
+        const bool ok = !live || (a >= 0 && b >= a && (uint64_t)b <= nbytes);
+        if (live) {
+            off_copy[i] = a;
+            if (i + 1 == n) off_copy[n] = b;
+        }
+        if (!__all(ok)) {
+            // nothing is read through these offsets: the build is refused
+            bad = true;
+            if (live) y[i] = 0;
+            continue;
+        }
+        const uint32_t count = (uint32_t)min((uint64_t)64, n - i0);
+        const uint64_t lo = (uint64_t)__shfl((unsigned long long)a, 0, 64);
+        const uint64_t hi = (uint64_t)__shfl((unsigned long long)b, (int)count - 1, 64);
+        const uint64_t first = lo & ~15ull;
+        const bool staged = hi - first <= kStageBytes;
+        // every piece holds a byte of the strings, so none lies on a page that they do not touch
+        for (uint64_t at = first + 16 * lane; at < hi; at += 64 * 16) {
+            const u32x4 v = *reinterpret_cast<const u32x4*>(bytes + at);
+            if (staged) mine[(at - first) >> 4] = v;
+            if (at >= lo) copy_piece(at, v);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (live) {
+            const uint64_t len = (uint64_t)(b - a);
+            uint32_t w[kChunkWords];
+            if (staged && len <= 4 * kChunkWords) {
+                const uint32_t at = (uint32_t)((uint64_t)a - first), sh = at & 3u;
+                const uint32_t nraw = len ? (sh + (uint32_t)len + 3) >> 2 : 0;
+                uint32_t raw[kChunkWords + 1];
+#pragma unroll
+                for (uint32_t k = 0; k <= kChunkWords; ++k) raw[k] = k < nraw ? words[(at >> 2) + k] : 0u;
+                shift_words<kChunkWords>(raw, sh, (uint32_t)len, w);
+                y[i] = below_p61(horner_words(len, w, (uint32_t)len, beta));
+            } else {
+                y[i] = fingerprint_words(bytes + a, len, beta, w);
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+    if (bad) atomicOr(&ctrl->bad_input, 1u);
+    // before the first piece and after the last
+    const int64_t o0 = off[0], on = off[n];
+    if (o0 < 0 || on < o0 || (uint64_t)on > nbytes) return;
+    const uint64_t head = min(nbytes, ((uint64_t)o0 + 15) & ~15ull), tail = min(nbytes, ((uint64_t)on + 15) & ~15ull);
+    const uint64_t at = (uint64_t)blockIdx.x * kBlock + threadIdx.x, stride = (uint64_t)gridDim.x * kBlock;
+    for (uint64_t k = at; k < head; k += stride) bytes_copy[k] = bytes[k];
+    for (uint64_t k = max(head, tail) + at; k < nbytes; k += stride) bytes_copy[k] = bytes[k];
+}
+
 // ---- host driver ------------------------------------------------------------------------
 
 static unsigned grid_for(uint64_t items, uint64_t per_block, unsigned cap = 1u << 30) {
@@ -151,8 +233,10 @@ static uint64_t cells_guess(uint64_t n, uint32_t c) {
 
 // Level-one attempts with the partitioned passes (partition.hip).
 // d_aux_in: the high halves of 64-bit values (kind 2), else nullptr.
+// d_off, d_bytes: strings that the first attempt has yet to copy into the map (d_off null: copied).
 static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uint32_t* d_vals,
-                                const uint32_t* d_aux_in, const fks_params& P, Ctrl* ctrl, Readback* host,
+                                const uint32_t* d_aux_in, const int64_t* d_off, const uint8_t* d_bytes,
+                                const fks_params& P, Ctrl* ctrl, Readback* host,
                                 uint64_t* y, hipStream_t st) {
     const uint64_t n = M->n;
     const uint64_t G = (n + 7) / 8;
@@ -230,7 +314,13 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
         const bool with_passes = !bytes && (a.cursor || plan.passes == 0);
         a.start = with_passes ? AttemptStart{(uint32_t*)ctrl, sizeof(Ctrl) / 4, M->C, M->seed, r, P.T} : AttemptStart{};
         if (!with_passes) hipLaunchKernelGGL(k_attempt_setup, 1, 256, 0, st, ctrl, M->C, M->seed, r, P.T);
-        if (bytes) {
+        if (bytes && d_off) {
+            FKS_TIMED("fks_fingerprint", st,
+                      hipLaunchKernelGGL(k_fingerprint_copy, grid_for(n, kBlock, 65536), kBlock, 0, st, d_off, d_bytes,
+                                         M->ctx_nbytes, n, beta, y, M->ctx_off, M->ctx_bytes, ctrl));
+            d_off = nullptr;
+            a.keys = y;
+        } else if (bytes) {
             FKS_TIMED("fks_fingerprint", st,
                       hipLaunchKernelGGL(k_fingerprint, grid_for(n, kBlock, 65536), kBlock, 0, st, M->ctx_off,
                                          M->ctx_bytes, M->ctx_nbytes, n, beta, y, ctrl));
@@ -407,14 +497,19 @@ static int build_common(fks_map* M, const uint64_t* d_keys_in, const uint32_t* d
         if (!M->ctx_off || !M->ctx_bytes) return fail(FKS_ENOMEM);
         M->ctx_nbytes = nbytes;
         M->device_bytes += 8 * (n + 1) + nbytes;
-        // the offsets are checked by the fingerprint pass, before any byte is read through them
-        hipError_t e = hipMemcpyAsync(M->ctx_off, d_off, 8 * (n + 1), hipMemcpyDeviceToDevice, st);
-        if (e == hipSuccess && nbytes) e = hipMemcpyAsync(M->ctx_bytes, d_bytes, nbytes, hipMemcpyDeviceToDevice, st);
-        if (e != hipSuccess) return fail(hip_fail(e));
+        // the offsets are checked by the fingerprint pass, before any byte is read through them; the
+        // first such pass copies both arrays where its 16-byte accesses are aligned
+        if (((uintptr_t)d_bytes | (uintptr_t)M->ctx_bytes) & 15) {
+            hipError_t e = hipMemcpyAsync(M->ctx_off, d_off, 8 * (n + 1), hipMemcpyDeviceToDevice, st);
+            if (e == hipSuccess && nbytes)
+                e = hipMemcpyAsync(M->ctx_bytes, d_bytes, nbytes, hipMemcpyDeviceToDevice, st);
+            if (e != hipSuccess) return fail(hip_fail(e));
+            d_off = nullptr;
+        }
     }
 
     M->magic_n = fastmod_magic((uint32_t)n);
-    rc = attempts_partitioned(M, d_keys_in, d_vals, d_aux_in, P, w.ctrl, w.host, w.y, st);
+    rc = attempts_partitioned(M, d_keys_in, d_vals, d_aux_in, d_off, d_bytes, P, w.ctrl, w.host, w.y, st);
     free_scratch(w, st, rc == FKS_OK);   // an accepted attempt's outcome was the last thing waited for
     return rc;
 }

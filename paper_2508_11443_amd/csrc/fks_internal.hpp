@@ -103,23 +103,15 @@ __host__ __device__ inline uint32_t fastmod(uint32_t a, uint64_t M, uint32_t d) 
 }
 
 // ---- string fingerprint: Horner over 32-bit words mod 2^61-1 ----------------
-__host__ __device__ inline uint64_t mulmod61(uint64_t a, uint64_t b) {
-    // a, b < 2^61: the 122-bit product folded twice (2^61 == 1 mod p)
-#if defined(__HIP_DEVICE_COMPILE__)
-    uint64_t lo = a * b;
-    uint64_t hi = __umul64hi(a, b);
-#else
-    unsigned __int128 p = (unsigned __int128)a * b;
-    uint64_t lo = (uint64_t)p, hi = (uint64_t)(p >> 64);
-#endif
-    uint64_t r = (lo & kP61) + ((lo >> 61) | (hi << 3));
-    r = (r & kP61) + (r >> 61);
-    return r >= kP61 ? r - kP61 : r;
-}
-__host__ __device__ inline uint64_t addmod61(uint64_t a, uint64_t w) {
-    uint64_t r = a + w;            // a < 2^61, w < 2^32: no overflow
-    r = (r & kP61) + (r >> 61);
-    return r >= kP61 ? r - kP61 : r;
+// len bytes from byte sh of raw's dwords on, as W little-endian words, zero past len
+template <int W>
+__device__ __forceinline__ void shift_words(const uint32_t (&raw)[W + 1], uint32_t sh, uint32_t len, uint32_t (&w)[W]) {
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+        const uint32_t v = __builtin_amdgcn_alignbyte(raw[k + 1], raw[k], sh);
+        const int rem = (int)len - 4 * k;   // bytes of the range in word k
+        w[k] = rem >= 4 ? v : rem <= 0 ? 0u : v & ((1u << (8 * rem)) - 1u);
+    }
 }
 
 // Bytes s[0..len), len <= 4*W, as W little-endian 32-bit words, zero past len.  They are
@@ -135,25 +127,32 @@ __device__ __forceinline__ void load_words(const uint8_t* s, uint32_t len, uint3
     uint32_t raw[W + 1];
 #pragma unroll
     for (int k = 0; k <= W; ++k) raw[k] = (uint32_t)k < nraw ? p[k] : 0u;
-#pragma unroll
-    for (int k = 0; k < W; ++k) {
-        const uint32_t v = __builtin_amdgcn_alignbyte(raw[k + 1], raw[k], sh);
-        const int rem = (int)len - 4 * k;   // bytes of the range in word k
-        w[k] = rem >= 4 ? v : rem <= 0 ? 0u : v & ((1u << (8 * rem)) - 1u);
-    }
+    shift_words(raw, sh, len, w);
 }
 
 constexpr int kChunkWords = 16;   // strings are read 64 bytes at a time
 
-// Horner step over the words of one chunk of c bytes (c <= 64)
+// acc * beta + w mod p up to a multiple of p: acc, below 2^61 + 8 in and out, is not brought below p
+// between the steps (the product is below 2^123 and folds to less than 2^63, so one fold of
+// that does; fewer than half the instructions of a step that reduces fully)
+__device__ __forceinline__ uint64_t horner_step(uint64_t acc, uint64_t beta, uint32_t w) {
+    const uint64_t lo = acc * beta, hi = __umul64hi(acc, beta);
+    const uint64_t r = (lo & kP61) + ((lo >> 61) | (hi << 3)) + w;
+    return (r & kP61) + (r >> 61);
+}
+
+// Horner steps over the words of one chunk of c bytes (c <= 64)
 __device__ __forceinline__ uint64_t horner_words(uint64_t acc, const uint32_t (&w)[kChunkWords], uint32_t c,
                                                  uint64_t beta) {
     const uint32_t nw = (c + 3) >> 2;
 #pragma unroll
     for (int k = 0; k < kChunkWords; ++k)
-        if ((uint32_t)k < nw) acc = addmod61(mulmod61(acc, beta), w[k]);
+        if ((uint32_t)k < nw) acc = horner_step(acc, beta, w[k]);
     return acc;
 }
+
+// acc < 2^61 + 8 mod p
+__device__ __forceinline__ uint64_t below_p61(uint64_t acc) { return acc >= kP61 ? acc - kP61 : acc; }
 
 // Fingerprint of s[0..len): len mod p, then one Horner step per 32-bit word (the last one
 // zero-padded).  For len <= 64, w holds the string's words on return.
@@ -169,7 +168,7 @@ __device__ __forceinline__ uint64_t fingerprint_words(const uint8_t* s, uint64_t
 #pragma unroll
         for (int k = 0; k < kChunkWords; ++k) w[k] = 0u;
     }
-    return acc;
+    return below_p61(acc);
 }
 
 // a[0..len) == b[0..len), 64 bytes at a time
