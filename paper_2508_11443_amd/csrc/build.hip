@@ -299,8 +299,8 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
         dev_free(slots, st);
         slots = nullptr;
     };
-    auto readback = [&]() {
-        const hipError_t e = words_to_host(host, ctrl, sizeof(Readback), st);
+    auto readback = [&](bool reported) {
+        const hipError_t e = reported ? hipStreamSynchronize(st) : words_to_host(host, ctrl, sizeof(Readback), st);
         return e == hipSuccess ? FKS_OK : hip_fail(e);
     };
     int rc = FKS_OK;
@@ -313,6 +313,8 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
         // the outcome words are cleared before the fingerprints, which may set one
         const bool with_passes = !bytes && (a.cursor || plan.passes == 0);
         a.start = with_passes ? AttemptStart{(uint32_t*)ctrl, sizeof(Ctrl) / 4, M->C, M->seed, r, P.T} : AttemptStart{};
+        a.outcome = with_passes && direct ? (uint32_t*)host : nullptr;
+        a.done = &ctrl->pad;
         if (!with_passes) hipLaunchKernelGGL(k_attempt_setup, 1, 256, 0, st, ctrl, M->C, M->seed, r, P.T);
         if (bytes && d_off) {
             FKS_TIMED("fks_fingerprint", st,
@@ -334,7 +336,7 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
             if ((rc = part_finish(a, o, M->C, P.T, M->header, slots, &ctrl->exhausted, M->ctx_off, M->ctx_bytes,
                                   nullptr, reject, cap, st)))
                 break;
-            if ((rc = readback())) break;
+            if ((rc = readback(o.reported))) break;
             if (host->bad_input) {
                 rc = FKS_EINVAL;
                 break;
@@ -371,7 +373,7 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
                 if ((rc = part_finish(a, o, M->C, P.T, M->header, slots, &ctrl->exhausted, M->ctx_off,
                                       M->ctx_bytes, nullptr, reject, cap, st)))
                     break;
-                if ((rc = readback())) break;
+                if ((rc = readback(false))) break;
             }
             if (host->exhausted) {
                 if (host->dup) {
@@ -392,7 +394,7 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
             release(true);
             return FKS_OK;
         }
-        if ((rc = readback())) break;
+        if ((rc = readback(false))) break;
         if (host->bad_input) {
             rc = FKS_EINVAL;
             break;
@@ -432,7 +434,7 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
         }
         rc = part_finish(a, o, M->C, P.T, M->header, cells, &ctrl->exhausted, M->ctx_off, M->ctx_bytes, given_t,
                          nullptr, ~0ull, st);
-        if (rc == FKS_OK) rc = readback();
+        if (rc == FKS_OK) rc = readback(false);
         if (rc) {
             dev_free(cells, st);
             break;

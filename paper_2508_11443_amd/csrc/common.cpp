@@ -74,7 +74,8 @@ void* pinned_words() {
     return buf;
 }
 
-// One small kernel in place of a copy: FIG_COPY
+// One small kernel in place of a copy, which the runtime runs as a kernel of its own behind a barrier
+// (together with one set-up launch instead of two, 2^16 keys' build, lookup and release 55 -> 53 us).
 __global__ void k_words_to_host(uint32_t* __restrict__ host, const uint32_t* __restrict__ dev, uint32_t words) {
     if (threadIdx.x < words) host[threadIdx.x] = dev[threadIdx.x];
 }

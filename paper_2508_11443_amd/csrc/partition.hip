@@ -547,6 +547,12 @@ struct FuseArgs {
     const uint64_t* qend; // partition q's records are [offQ[q], min(qend[q], offQ[q] + qcap))
     uint64_t qcap;        // 0: no cap
     const uint32_t* parts;   // a batch: segment * kSegParts + partition within the map
+    // the outcome, for the host (null: another launch brings it): outcome_words words from
+    // outcome_dev, once `done` has counted all workgroups
+    uint32_t* outcome;
+    const uint32_t* outcome_dev;
+    uint32_t outcome_words;
+    uint32_t* done;
 };
 
 // largest of a small value (below 16) over the wave's active lanes
@@ -618,9 +624,27 @@ __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(BT == kPB ? 
     static_assert(!MULTI || FUSED, "the maps of a batch are sized by the final pass");
     __shared__ FinalLds<AUX, BT> L;
     const uint32_t tid = threadIdx.x;
+    // few partitions: the last workgroup to end writes the attempt's outcome to the host (a launch
+    // less; with many, one more atomic on one word for each would cost more)
+    constexpr bool REPORT = FUSED && !MULTI && BT != kPB;
+    auto ended = [&]() {
+        if (!REPORT || !fa.outcome) return;
+        __syncthreads();
+        if (tid == 0) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this thread's outcome words are written
+            if (atomicAdd(fa.done, 1u) == gridDim.x - 1)
+                for (uint32_t k = 0; k < fa.outcome_words; ++k)
+                    fa.outcome[k] =
+                        __hip_atomic_load(fa.outcome_dev + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    };
     // an attempt already rejected by the size pass (a bucket above 15 keys) or by bad
-    // string offsets is skipped (both flags are set before this kernel starts)
-    if (reject && (reject[0] | reject[1])) return;   // the whole block
+    // string offsets is skipped (both flags are set before this kernel starts; the fused form sets
+    // the first itself, and every workgroup that others may look back to goes on)
+    if (reject && ((FUSED ? 0u : reject[0]) | reject[1])) {   // the whole block
+        ended();
+        return;
+    }
     uint32_t q = blockIdx.x;
     if (FUSED) {
         // partitions go in ticket order: every partition a look-back below waits for was
@@ -797,7 +821,7 @@ __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(BT == kPB ? 
                         if (excl + Sq > cap) atomicOr(fa.oversize, 2u);
                     }
                 } else if (q + 1 == fa.Q) {
-                    *fa.S_out = excl + Sq;
+                    __hip_atomic_store(fa.S_out, excl + Sq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
             }
         }
@@ -813,6 +837,7 @@ __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(BT == kPB ? 
         if (L.over) {
             lookback();
             if (tid == 0) atomicOr(fa.oversize, 1u);
+            ended();
             return;   // the whole block: the attempt is rejected
         }
         fast = keys_fit && Sq <= kFinalCellCap;
@@ -946,7 +971,10 @@ __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(BT == kPB ? 
         }
         if (FUSED) {
             lookback();
-            if (c0 + Sq > cap) return;   // the whole block
+            if (c0 + Sq > cap) {   // the whole block
+                ended();
+                return;
+            }
         }
 #pragma unroll
         for (uint32_t k = 0; k < CPT; ++k) {
@@ -966,7 +994,10 @@ __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(BT == kPB ? 
         __syncthreads();
         if (FUSED) {
             lookback();
-            if (c0 + Sq > cap) return;   // the whole block
+            if (c0 + Sq > cap) {   // the whole block
+                ended();
+                return;
+            }
         }
         for (uint32_t b = tid; b < kPartBuckets; b += BT) {
             const uint64_t gp = L.gpos[b >> 3];
@@ -1054,6 +1085,7 @@ __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(BT == kPB ? 
         if (L.flags[1]) atomicOr(&ctrl_flags[1], 1u);
         if (L.flags[2]) atomicMax(&ctrl_flags[2], L.flags[2]);
     }
+    ended();
 }
 
 // ---- host planning and launches ------------------------------------------------------
@@ -1218,7 +1250,7 @@ int part_prepare(const PartArgs& a, hipStream_t st, PartOut& o) {
     o.qbeg = a.offQ;
     o.qend = a.offQ + 1;
     o.qcap = 0;   // no cap: the counted passes fill their ranges exactly
-    o.prezeroed = false;
+    o.prezeroed = o.reported = false;
     auto count = [&](const uint64_t* kin, const uint64_t* ranges, dim3 grid, uint32_t W, uint32_t shift,
                      uint32_t mask) {
         FKS_TIMED("fks_part_count", st,
@@ -1369,9 +1401,12 @@ int part_prepare(const PartArgs& a, hipStream_t st, PartOut& o) {
 // with 256, 512 and 1024 threads: 2^16 keys 54.7, 51.4 and 50.0 us, 2^19 72.4, 70.5 and 76.7,
 // 2^20 87.0, 90.8 and 102.4, 10^7 285, 373 and 512.
 constexpr uint32_t kWideFinalThreads = 512, kWideFinalParts = 512;
+// Partitions up to which the pass itself writes the outcome to the host: 1000 keys 43.3 and 40.6 us,
+// 2^16 51.4 and 49.0, 2^18 (256 partitions) 56.3 and 56.2, 2^19 70.5 and 74.0.
+constexpr uint32_t kReportParts = 128;
 
 template <bool AUX, bool STR>
-static void launch_fused(const PartArgs& a, const PartOut& o, const Triple* C, uint32_t T, Group* header, Cell* slots,
+static void launch_fused(const PartArgs& a, PartOut& o, const Triple* C, uint32_t T, Group* header, Cell* slots,
                          uint32_t* flags, const int64_t* ctx_off, const uint8_t* ctx_bytes, const uint32_t* reject,
                          uint64_t cap, hipStream_t st) {
     const uint32_t Q = o.plan.Q;
@@ -1382,13 +1417,15 @@ static void launch_fused(const PartArgs& a, const PartOut& o, const Triple* C, u
                            (uint64_t)2 * Q);
         if (a.ticketed) hipLaunchKernelGGL(k_zero_words, 1, 64, 0, st, a.sqQ, (uint64_t)1);
     }
-    const FuseArgs fa{a.cbase, a.ticketed ? a.sqQ : nullptr, a.S_dev, a.oversize, a.stalled, Q, o.qend, o.qcap, nullptr};
+    const FuseArgs fa{a.cbase, a.ticketed ? a.sqQ : nullptr, a.S_dev, a.oversize, a.stalled, Q, o.qend, o.qcap, nullptr,
+                      Q <= kReportParts ? a.outcome : nullptr, a.start.clear, a.start.words, a.done};
     auto launch = [&](auto kernel, uint32_t threads) {
         FKS_TIMED("fks_part_final", st,
                   hipLaunchKernelGGL(kernel, Q, threads, 0, st, o.keys, o.vals, AUX ? o.aux : nullptr,
                                      AUX ? o.aux_is_pos : 1, a.n, a.A, a.magic, o.qbeg, a.cbase, a.sizes, a.G, C, T,
                                      header, slots, flags, ctx_off, ctx_bytes, nullptr, nullptr, reject, cap, fa));
     };
+    o.reported = fa.outcome != nullptr;
     if (Q <= kWideFinalParts) launch(k_pfinal<AUX, STR, false, true, kWideFinalThreads>, kWideFinalThreads);
     else launch(k_pfinal<AUX, STR, false, true>, kPB);
 }
@@ -1501,7 +1538,8 @@ int wide_build(const uint64_t* d_keys, const uint32_t* d_vals, const WideSeg* se
                                  kPScatterThreads, 0, st, d_keys, d_vals, nullptr, 0ull, A0, 0ull, nullptr, 1u, 0u,
                                  kSegParts - 1, nullptr, w.keys, w.vals, nullptr, segs, w.tiles, w.cursor, nullptr, cap,
                                  flags, 0ull));
-    const FuseArgs fa{w.state, nullptr, w.S, nullptr, nullptr, (uint32_t)parts, (const uint64_t*)w.cursor, cap, w.parts};
+    const FuseArgs fa{w.state, nullptr, w.S, nullptr, nullptr, (uint32_t)parts, (const uint64_t*)w.cursor, cap, w.parts,
+                      nullptr, nullptr, 0, nullptr};
     FKS_TIMED("fks_wide_final", st,
               hipLaunchKernelGGL((k_pfinal<false, false, true, true>), (unsigned)parts, kPB, 0, st, w.keys, w.vals,
                                  nullptr, 1, 0ull, A0, 0ull, nullptr, nullptr, nullptr, 0ull, Cpool, T, hdr_pool,

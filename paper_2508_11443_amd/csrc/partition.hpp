@@ -96,6 +96,8 @@ struct PartArgs {
     uint32_t* oversize;         // a bucket above 15 keys
     uint32_t* stalled;          // fused final pass: a look-back gave up
     bool ticketed;              // fused final pass: partitions go in ticket order
+    uint32_t* outcome;          // pinned: where the host reads start.clear's words, or null
+    uint32_t* done;             // one of those words, counting the final pass's workgroups
     bool fused;                 // the final pass sizes the partitions itself (no size pass and scan)
     // two passes without count passes: each tile reserves its runs on per-bin cursors in
     // fixed-capacity regions (k1/v1/a1 hold binsA * cap1 records, k2/v2/a2 Q * capQ)
@@ -116,6 +118,7 @@ struct PartOut {
     const uint64_t* qbeg;       // partition q's records are [qbeg[q], min(qend[q], qbeg[q] + qcap))
     const uint64_t* qend;
     uint64_t qcap;              // 0: no cap (counted passes)
+    bool reported;              // the final pass writes the outcome to the host itself
     bool prezeroed;             // the fused pass's look-back words and ticket are already zero
 };
 
