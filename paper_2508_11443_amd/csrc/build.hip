@@ -245,7 +245,7 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
     // the per-bucket schedule runs the final pass straight after the size pass, into cells
     // allocated from a bound on S; the paper's rounds need S on the host before their search
     const bool direct = P.schedule == 0;
-    const PartPlan plan = part_plan(n);
+    const PartPlan plan = part_plan(n, carry);
     PartArgs a{};
     a.n = n;
     a.G = G;

@@ -158,7 +158,7 @@ extern "C" int fks_build_u64_from_array(const uint64_t* d_keys, const uint32_t* 
     if (u == 0) return fks_build_u64(d_keys, d_vals, 0, seed, params, alloc, stream, out);
     AllocScope scope(alloc);
     hipStream_t st = (hipStream_t)stream;
-    const PartPlan plan = part_plan(u);
+    const PartPlan plan = part_plan(u, true);
     const bool cursor = plan.passes == 1 || plan.passes == 2;
     const size_t scratch_bytes = part_scratch(plan, u, true, cursor, false, nullptr, nullptr);
     char* scratch = (char*)dev_alloc(scratch_bytes, st);

@@ -34,6 +34,12 @@ constexpr uint32_t kPTile = kPB * kPItems;    // 4096 keys per tile
 // word travels (16-byte records, 8192-record tiles, 133 KB)
 constexpr uint32_t kPScatterThreads = 1024, kPScatterItems = 12, kPScatterItemsAux = 8;
 constexpr uint32_t kBins = 256;               // bins per scatter pass
+// Keys from which every XCD has regions of its own in the first pass's bins (with an aux word in
+// every record, and without): where the records outgrow the 256 MiB Infinity Cache, which merges
+// what the L2s write in pieces.  Build, one lookup and release with one region per bin and with
+// eight: 1.6 * 10^7 keys with 64-bit values 581 and 566 us, 3.3 * 10^7 1171 and 1091, 2^26 2336 and 2120; without
+// aux words 2.4 * 10^7 613 and 628, 3.3 * 10^7 848 and 846, 2^26 1671 and 1604.
+constexpr uint64_t kSubRegionKeysAux = 1ull << 24, kSubRegionKeys = 1ull << 25;
 constexpr uint32_t kFinalKeyCap = 1248;       // keys of one partition held in LDS (mean 1024, sd 32)
 constexpr uint32_t kLdsTrials = 16;          // level-two triples held in the final pass's LDS (larger trials are rare)
 constexpr uint32_t kFinalCellCap = 3072;      // cells of one partition staged in LDS (mean <= 2048, sd ~106)
@@ -49,21 +55,21 @@ __device__ __forceinline__ uint32_t bucket_of(const Triple& A, uint64_t magic, u
     return fastmod(mshash(A, x), magic, n);
 }
 
-// Worker blockIdx.x of W in segment blockIdx.y: segment = the whole input
+// Worker bx of W in segment by: segment = the whole input
 // (ranges == nullptr) or [ranges[s], ranges[s+1]); the worker owns one
 // contiguous chunk of it and walks the chunk in tiles, so that counting and
 // scattering see the keys in the same order.
-__device__ __forceinline__ void worker_range(const uint64_t* ranges, uint64_t n, uint32_t W, uint64_t& a,
+__device__ __forceinline__ void worker_range(uint32_t bx, uint32_t by, const uint64_t* ranges, uint64_t n, uint32_t W, uint64_t& a,
                                              uint64_t& b, const uint64_t* ranges_hi = nullptr,
                                              uint64_t hi_cap = 0) {
     uint64_t lo = 0, hi = n;
     if (ranges) {
-        lo = ranges[blockIdx.y];
+        lo = ranges[by];
         // a cursor that ran past its region's end (overflow raised) stops at the end
-        hi = ranges_hi ? min(ranges_hi[blockIdx.y], lo + hi_cap) : ranges[blockIdx.y + 1];
+        hi = ranges_hi ? min(ranges_hi[by], lo + hi_cap) : ranges[by + 1];
     }
     const uint64_t chunk = (hi - lo + W - 1) / W;
-    a = min(hi, lo + (uint64_t)blockIdx.x * chunk);
+    a = min(hi, lo + (uint64_t)bx * chunk);
     b = min(hi, a + chunk);
 }
 
@@ -73,7 +79,7 @@ __global__ __launch_bounds__(kPB) void k_dcount(const uint64_t* __restrict__ key
                                                   uint32_t shift, uint32_t mask, uint32_t* __restrict__ cnt) {
     __shared__ uint32_t bins[kBins];
     uint64_t a, b;
-    worker_range(ranges, n, W, a, b);
+    worker_range(blockIdx.x, blockIdx.y, ranges, n, W, a, b);
     for (uint32_t k = threadIdx.x; k < kBins; k += kPB) bins[k] = 0;
     __syncthreads();
     for (uint64_t ts = a; ts < b; ts += kPTile) {
@@ -140,7 +146,7 @@ __global__ __launch_bounds__(BT) void k_dscatter(const uint64_t* __restrict__ ke
                                                     unsigned long long* __restrict__ cursor = nullptr,
                                                     const uint64_t* __restrict__ ranges_hi = nullptr,
                                                     uint64_t cap = 0, uint32_t* __restrict__ overflow = nullptr,
-                                                    uint64_t in_cap = 0) {
+                                                    uint64_t in_cap = 0, uint32_t subs = 0, uint32_t in_subs = 0) {
     __shared__ uint64_t skey[(BT * ITEMS)];
     __shared__ uint32_t sval[(BT * ITEMS)];
     __shared__ uint32_t saux[AUX ? (BT * ITEMS) : 1];
@@ -148,9 +154,30 @@ __global__ __launch_bounds__(BT) void k_dscatter(const uint64_t* __restrict__ ke
     __shared__ uint32_t wsum[BT / 64];
     static_assert(BT >= kBins && BT % 64 == 0, "one bin per thread");
     __shared__ uint64_t lim[CURSOR ? kBins : 1];
-    uint64_t a, b, bin0 = (uint64_t)blockIdx.y * (mask + 1);   // bin0: the first of the bins' regions and cursors
+    // Workgroups are dealt to the XCDs in turn, and a line that several runs share is written to memory
+    // whole only if they meet in one XCD's L2.  So all workers of a bin of the first pass go to one
+    // XCD, and with subs > 0 (the first pass itself) every XCD has regions of its own in each bin.
+    // 2^26 records of 12 bytes: second pass 461 and 375 us, first pass 425 and 364.
+    uint32_t bx = blockIdx.x, by = blockIdx.y;
+    if (CURSOR && gridDim.y > 1) {
+        const uint32_t per = gridDim.x << in_subs, bins = gridDim.y >> in_subs;   // workgroups of a bin, bins
+        const uint32_t l = by * gridDim.x + bx, turn = l >> 3;
+        if (l < (bins & ~7u) * per) {
+            by = (((turn / per) * 8 + (l & 7u)) << in_subs) + turn % per / gridDim.x;
+            bx = turn % gridDim.x;
+        }
+    }
+    // the regions and cursors of the bins: bin0, bin0 + step, ...
+    uint64_t a, b, bin0 = (uint64_t)(by >> in_subs) * (mask + 1);
+    uint32_t step = 1;
+    if (CURSOR && subs) {
+        bin0 = bx & 7u;
+        step = 8;
+    }
     if (CURSOR && segs) {
-        const uint2 t = tiles[blockIdx.x];
+        // neighbours in the list, a map's tiles among them, on one XCD
+        const uint32_t each = gridDim.x >> 3, l = blockIdx.x;
+        const uint2 t = tiles[l < 8 * each ? (l & 7u) * each + (l >> 3) : l];
         const WideSeg& sg = segs[t.x];
         A = sg.A;
         magic = sg.magic;
@@ -160,11 +187,11 @@ __global__ __launch_bounds__(BT) void k_dscatter(const uint64_t* __restrict__ ke
         bin0 = sg.part0;
         overflow += 4 * t.x;
     } else {
-        worker_range(ranges, n, W, a, b, ranges_hi, in_cap);
+        worker_range(bx, by, ranges, n, W, a, b, ranges_hi, in_cap);
     }
     const uint32_t tid = threadIdx.x;
-    if (!CURSOR && tid < kBins) run[tid] = off[((uint64_t)blockIdx.y * kBins + tid) * W + blockIdx.x];
-    if (CURSOR && tid < kBins) lim[tid] = (bin0 + tid + 1) * cap;
+    if (!CURSOR && tid < kBins) run[tid] = off[((uint64_t)by * kBins + tid) * W + bx];
+    if (CURSOR && tid < kBins) lim[tid] = (bin0 + tid * step + 1) * cap;
     // a tile's records are loaded into registers one tile ahead: the loads of
     // tile i+1 are in flight while tile i is written out
     uint64_t x[ITEMS];
@@ -196,7 +223,7 @@ __global__ __launch_bounds__(BT) void k_dscatter(const uint64_t* __restrict__ ke
         if (CURSOR && tid <= mask && tcnt[tid]) {
             // this tile's run of bin tid: reserved now, written after the tile is sorted
             const unsigned long long at =
-                atomicAdd(&cursor[bin0 + tid], (unsigned long long)tcnt[tid]);
+                atomicAdd(&cursor[bin0 + tid * step], (unsigned long long)tcnt[tid]);
             run[tid] = (uint32_t)at;
             if (at + tcnt[tid] > lim[tid]) atomicOr(overflow, 1u);
         }
@@ -1099,7 +1126,7 @@ static uint64_t part_region(uint64_t B) {
     return (B + 12 * sd + 64 + 255) & ~(uint64_t)255;
 }
 
-PartPlan part_plan(uint64_t n) {
+PartPlan part_plan(uint64_t n, bool carry) {
     PartPlan P{};
     P.Q = (uint32_t)((n + kPartBuckets - 1) / kPartBuckets);
     uint32_t bits = 0;
@@ -1138,6 +1165,17 @@ PartPlan part_plan(uint64_t n) {
         P.W2 = clampu((n / P.binsA + worker - 1) / worker, 1, 64);
         P.cap1 = part_region((uint64_t)kPartBuckets << P.shiftA);
         P.capQ = part_region(kPartBuckets);
+        P.regions1 = P.binsA;
+        P.W2c = P.W2;
+        if (n >= (carry ? kSubRegionKeysAux : kSubRegionKeys)) {
+            // an eighth of a bin for every XCD: at most this many of the first pass's records, two tiles
+            // at a time
+            const uint64_t chunk = (n + P.W1 - 1) / P.W1, most = (P.W1 + 7) / 8 * chunk;
+            P.subs = 3;
+            P.cap1 = part_region((((uint64_t)kPartBuckets << P.shiftA) * most + n - 1) / n);
+            P.regions1 = P.binsA << P.subs;
+            P.W2c = clampu((most / P.binsA + worker / 2 - 1) / (worker / 2), 1, 64);
+        }
     } else {
         P.passes = 3;
         P.shiftA = bits - 8;
@@ -1164,7 +1202,7 @@ size_t part_scratch(const PartPlan& plan, uint64_t n, bool carry, bool cursor, b
     const uint64_t Q = plan.Q;
     // the cursor form keeps its records in fixed-capacity regions (binsA of them after a first
     // of two passes, Q after the last)
-    const uint64_t r1 = cursor ? std::max<uint64_t>(n, plan.cap1 * plan.binsA) : n;
+    const uint64_t r1 = cursor ? std::max<uint64_t>(n, plan.cap1 * plan.regions1) : n;
     const uint64_t r2 = cursor ? std::max<uint64_t>(n, plan.capQ * Q) : n;
     if (plan.passes >= 2) {
         carve(&PartArgs::k1, 8 * r1);
@@ -1177,9 +1215,9 @@ size_t part_scratch(const PartPlan& plan, uint64_t n, bool carry, bool cursor, b
         if (carry) carve(&PartArgs::a2, 4 * r2);
     }
     if (cursor) {
-        carve(&PartArgs::cur1, 8 * (size_t)plan.binsA);
+        carve(&PartArgs::cur1, 8 * (size_t)plan.regions1);
         carve(&PartArgs::cur2, 8 * Q);
-        carve(&PartArgs::begA, 8 * (size_t)plan.binsA);
+        carve(&PartArgs::begA, 8 * (size_t)plan.regions1);
         carve(&PartArgs::begQ, 8 * Q);
     }
     carve(&PartArgs::cnt, 4 * plan.matrix);
@@ -1221,12 +1259,13 @@ template <bool AUX>
 static void scatter_cursor(const PartArgs& a, const PartPlan& P, const uint64_t* kin, const uint32_t* vin,
                            const uint32_t* ain, const uint64_t* ranges, const uint64_t* ranges_hi, uint64_t in_cap,
                            dim3 grid, uint32_t W, uint32_t shift, uint32_t mask, uint64_t* kout, uint32_t* vout,
-                           uint32_t* aout, unsigned long long* cursor, uint64_t cap, hipStream_t st) {
+                           uint32_t* aout, unsigned long long* cursor, uint64_t cap, uint32_t subs, uint32_t in_subs,
+                           hipStream_t st) {
     auto launch = [&](auto kernel) {
         FKS_TIMED("fks_part_scatter", st,
                   hipLaunchKernelGGL(kernel, grid, kPScatterThreads, 0, st, kin, vin, ain, a.n, a.A, a.magic, ranges, W,
                                      shift, mask, nullptr, kout, vout, aout, nullptr, nullptr, cursor, ranges_hi,
-                                     cap, a.overflow, in_cap));
+                                     cap, a.overflow, in_cap, subs, in_subs));
     };
     if (P.items == 2) launch(k_dscatter<AUX, 2, kPScatterThreads, true>);
     else if (P.items == 4) launch(k_dscatter<AUX, 4, kPScatterThreads, true>);
@@ -1239,7 +1278,7 @@ static unsigned grid_for_count(uint64_t count) { return (unsigned)std::min<uint6
 // records in partition order (o.keys/vals/aux), the size words, the partition
 // sums of squares, their scan (cbase) and the total S (*S_dev).
 int part_prepare(const PartArgs& a, hipStream_t st, PartOut& o) {
-    const PartPlan P = part_plan(a.n);
+    const PartPlan P = part_plan(a.n, a.aux);
     const uint64_t n = a.n;
     const bool aux = a.aux;
     o.plan = P;
@@ -1272,10 +1311,10 @@ int part_prepare(const PartArgs& a, hipStream_t st, PartOut& o) {
         init(0, P.Q, false);
         if (aux)
             scatter_cursor<true>(a, P, a.keys, a.vals, a.aux_in, nullptr, nullptr, 0, dim3(P.W1, 1), P.W1, 0, 255, a.k2,
-                                 a.v2, a.a2, a.cur2, P.capQ, st);
+                                 a.v2, a.a2, a.cur2, P.capQ, 0, 0, st);
         else
             scatter_cursor<false>(a, P, a.keys, a.vals, nullptr, nullptr, nullptr, 0, dim3(P.W1, 1), P.W1, 0, 255,
-                                  a.k2, a.v2, a.a2, a.cur2, P.capQ, st);
+                                  a.k2, a.v2, a.a2, a.cur2, P.capQ, 0, 0, st);
         o.keys = a.k2;
         o.vals = a.v2;
         o.aux = a.a2;
@@ -1297,21 +1336,21 @@ int part_prepare(const PartArgs& a, hipStream_t st, PartOut& o) {
         o.aux_is_pos = aux ? 0 : 1;
     } else if (P.passes == 2 && a.cursor) {
         // first-level bins, then partitions, each reserved run by run on the bin's cursor
-        init(P.binsA, P.Q, false);
+        init(P.regions1, P.Q, false);
         if (aux)
             scatter_cursor<true>(a, P, a.keys, a.vals, a.aux_in, nullptr, nullptr, 0, dim3(P.W1, 1), P.W1, P.shiftA,
-                                 255, a.k1, a.v1, a.a1, a.cur1, P.cap1, st);
+                                 255, a.k1, a.v1, a.a1, a.cur1, P.cap1, P.subs, 0, st);
         else
             scatter_cursor<false>(a, P, a.keys, a.vals, nullptr, nullptr, nullptr, 0, dim3(P.W1, 1), P.W1, P.shiftA,
-                                  255, a.k1, a.v1, a.a1, a.cur1, P.cap1, st);
+                                  255, a.k1, a.v1, a.a1, a.cur1, P.cap1, P.subs, 0, st);
         const uint32_t maskB = (1u << P.bitsB) - 1;
         const uint64_t* hi1 = reinterpret_cast<const uint64_t*>(a.cur1);
         if (aux)
-            scatter_cursor<true>(a, P, a.k1, a.v1, a.a1, a.begA, hi1, P.cap1, dim3(P.W2, P.binsA), P.W2, 0, maskB, a.k2,
-                                 a.v2, a.a2, a.cur2, P.capQ, st);
+            scatter_cursor<true>(a, P, a.k1, a.v1, a.a1, a.begA, hi1, P.cap1, dim3(P.W2c, P.regions1), P.W2c, 0, maskB, a.k2,
+                                 a.v2, a.a2, a.cur2, P.capQ, 0, P.subs, st);
         else
-            scatter_cursor<false>(a, P, a.k1, a.v1, nullptr, a.begA, hi1, P.cap1, dim3(P.W2, P.binsA), P.W2, 0, maskB,
-                                  a.k2, a.v2, a.a2, a.cur2, P.capQ, st);
+            scatter_cursor<false>(a, P, a.k1, a.v1, nullptr, a.begA, hi1, P.cap1, dim3(P.W2c, P.regions1), P.W2c, 0, maskB,
+                                  a.k2, a.v2, a.a2, a.cur2, P.capQ, 0, P.subs, st);
         o.keys = a.k2;
         o.vals = a.v2;
         o.aux = a.a2;

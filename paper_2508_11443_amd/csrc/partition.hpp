@@ -53,8 +53,11 @@ struct PartPlan {
     uint32_t items;    // records per thread of a cursor pass's tile: 2, 4, or 0 for the largest tile
     uint32_t W1, W2, W3;   // workers of the first pass / per bin of the second and third passes
     uint64_t matrix;   // entries of the largest count matrix
-    // two passes with cursors: capacity of a first-level bin's region and of a partition's
+    // two passes with cursors: capacity of a first-level region and of a partition's; first-level
+    // regions, 2^subs of them (one for each XCD, or one) in a bin
     uint64_t cap1, capQ;
+    uint32_t regions1, subs;
+    uint32_t W2c;           // workers per first-level region
 };
 
 // What an attempt's set-up does beside the passes' own (nothing when zero): clears the first
@@ -127,7 +130,7 @@ struct PartOut {
 uint64_t exscan_tiles(uint64_t N);
 void exscan_u32(const uint32_t* in, uint64_t N, uint32_t* tsum, uint64_t* tpre, uint32_t* out, hipStream_t st);
 
-PartPlan part_plan(uint64_t n);
+PartPlan part_plan(uint64_t n, bool carry);   // carry: an aux word travels with every key
 
 // Bytes of the passes' scratch for n keys (carry: an aux word travels; cursor: the cursor
 // form's regions; sizes: the size words of the unfused form); with base given, a's scratch

@@ -353,7 +353,16 @@ __global__ __launch_bounds__(kSsThreads) void k_ss_scatter(
     __shared__ uint64_t to[kSsBins], room[kSsBins];   // where a bin's run goes, and its region's end
     __shared__ uint32_t tcnt[kSsBins], toff[kSsBins], wsum[kSsBins / 64];
     const uint32_t tid = threadIdx.x;
-    const uint32_t seg = blockIdx.y;
+    uint32_t seg = blockIdx.y, worker = blockIdx.x;
+    if (gridDim.y > 1) {
+        // all workers of a bucket on one XCD (workgroups are dealt to them in turn), where the lines that
+        // several of their runs share meet
+        const uint32_t l = seg * gridDim.x + worker, turn = l >> 3;
+        if (l < (gridDim.y & ~7u) * gridDim.x) {
+            seg = turn / gridDim.x * 8 + (l & 7u);
+            worker = turn % gridDim.x;
+        }
+    }
     uint64_t lo = 0, hi = n;
     if (end) {
         lo = seg * in_cap;
@@ -361,7 +370,7 @@ __global__ __launch_bounds__(kSsThreads) void k_ss_scatter(
         spl += (uint64_t)seg * kSsBins;
     }
     const uint64_t chunk = (hi - lo + gridDim.x - 1) / gridDim.x;
-    const uint64_t a = min(hi, lo + blockIdx.x * chunk), b = min(hi, a + chunk);
+    const uint64_t a = min(hi, lo + worker * chunk), b = min(hi, a + chunk);
     if (tid < kSsBins) {
         cut[tid] = spl[tid];
         room[tid] = ((uint64_t)seg * bins + tid + 1) * cap;
