@@ -21,7 +21,7 @@ constexpr uint64_t kEmpty = ~0ull;            // slot marker; the key ~0 itself 
 constexpr uint32_t kDdThreads = 512;
 constexpr uint32_t kDdParts = 2;              // partitions per workgroup
 constexpr uint32_t kDdSlots = 4096;           // slots of a workgroup's table (about 2048 records without repeats)
-constexpr uint32_t kDdUnroll = 4;             // records per thread in flight
+constexpr uint32_t kDdHeld = 6;               // records per thread held in registers (3072; two regions hold 2944)
 constexpr uint32_t kDdAttempts = 16;          // partition hashes tried before the build gives up
 
 // what the host reads back
@@ -41,7 +41,8 @@ __global__ void k_dd_clear(DdCtrl* c) {
 // address take 11.4 ns each (65536 of them 747 us), which is why a workgroup takes two
 // partitions (8192 partitions of 2^23 records: 47 us of atomics instead of 93).  A table in
 // device memory with a compare-and-swap per record and a list position per occupied slot took
-// 0.83 + 3.0 ms for 2^23 records of 2^22 keys; the two passes and this kernel take 0.2 ms.
+// 0.83 + 3.0 ms for 2^23 records of 2^22 keys; the two passes and this kernel take 0.2 ms.  Records
+// held in registers between the table's two uses: 73 us, read and looked up twice 99.
 __global__ __launch_bounds__(kDdThreads) void k_dd_distinct(
     const uint64_t* __restrict__ keys, const uint32_t* __restrict__ vals, const uint32_t* __restrict__ idx,
     const uint64_t* __restrict__ qbeg, const uint64_t* __restrict__ qend, uint64_t qcap, uint32_t Q, Triple H,
@@ -64,85 +65,107 @@ __global__ __launch_bounds__(kDdThreads) void k_dd_distinct(
     auto slot_of = [&](uint64_t x) { return mshash(H, x) >> (32 - 12); };
     static_assert(kDdSlots == 1u << 12, "the slot hash takes 12 bits");
     uint32_t claimed = 0;
-    for (uint32_t q = q0; q < q1; ++q) {
-        const uint64_t lo = qbeg[q], hi = qcap ? min(qend[q], lo + qcap) : qend[q];
-        for (uint64_t i0 = lo; i0 < hi; i0 += kDdThreads * kDdUnroll) {
-            uint64_t x[kDdUnroll];
-            uint32_t at[kDdUnroll];
-#pragma unroll
-            for (uint32_t k = 0; k < kDdUnroll; ++k) {
-                const uint64_t i = i0 + tid + (uint64_t)k * kDdThreads;
-                x[k] = i < hi ? keys[i] : 0;
-                at[k] = i < hi ? (idx ? idx[i] : (uint32_t)i) : 0;
+    // the record's slot (kDdSlots: the key kEmpty), which keeps its key's smallest index; false: no room
+    auto insert = [&](uint64_t x, uint32_t at, uint32_t& s) {
+        if (x == kEmpty) {
+            s = kDdSlots;
+            if (atomicMin(&side, at) == 0xFFFFFFFFu) ++claimed;
+            return true;
+        }
+        s = slot_of(x);
+        for (uint32_t probe = 0; probe < kDdSlots; ++probe) {
+            // a slot's key never changes once it is set: read before the swap
+            unsigned long long old = tkey[s];
+            if (old == kEmpty) {
+                old = atomicCAS(reinterpret_cast<unsigned long long*>(&tkey[s]), (unsigned long long)kEmpty,
+                                (unsigned long long)x);
+                if (old == kEmpty) ++claimed;
             }
+            if (old == kEmpty || old == x) {
+                atomicMin(&tidx[s], at);
+                return true;
+            }
+            s = (s + 1) & (kDdSlots - 1);
+        }
+        return false;
+    };
+    // the place of the workgroup's distinct keys in the list, once all are in the table
+    auto reserve = [&]() {
+        if (claimed) atomicAdd(&distinct, claimed);
+        __syncthreads();
+        if (tid == 0) {
+            base = 0;
+            if (full) atomicOr(&ctrl->full, 1u);
+            else if (distinct) base = atomicAdd(&ctrl->count, distinct);
+        }
+        __syncthreads();
+    };
+    // the record that is its key's first occurrence goes to the list
+    auto emit = [&](uint64_t x, uint32_t at, uint32_t v, uint32_t s) {
+        if ((s == kDdSlots ? side : tidx[s]) != at) return;
+        const uint64_t pos = (uint64_t)base + atomicAdd(&put, 1u);
+        if (pos < out_cap) {
+            out_keys[pos] = x;
+            out_vals[pos] = v;
+        }
+    };
+    auto end_of = [&](uint32_t q) { return qcap ? min(qend[q], qbeg[q] + qcap) : qend[q]; };
+    uint64_t lo[kDdParts];
+    uint32_t upto[kDdParts + 1];
+    upto[0] = 0;
+    bool small = true;
 #pragma unroll
-            for (uint32_t k = 0; k < kDdUnroll; ++k) {
-                if (i0 + tid + (uint64_t)k * kDdThreads >= hi) continue;
-                if (x[k] == kEmpty) {
-                    if (atomicMin(&side, at[k]) == 0xFFFFFFFFu) ++claimed;
-                    continue;
-                }
-                uint32_t s = slot_of(x[k]);
-                uint32_t probe = 0;
-                for (; probe < kDdSlots; ++probe) {
-                    // a slot's key never changes once it is set: read before the swap
-                    unsigned long long old = tkey[s];
-                    if (old == kEmpty) {
-                        old = atomicCAS(reinterpret_cast<unsigned long long*>(&tkey[s]), (unsigned long long)kEmpty,
-                                        (unsigned long long)x[k]);
-                        if (old == kEmpty) ++claimed;
-                    }
-                    if (old == kEmpty || old == x[k]) {
-                        atomicMin(&tidx[s], at[k]);
-                        break;
-                    }
-                    s = (s + 1) & (kDdSlots - 1);
-                }
-                if (probe == kDdSlots) full = 1;
+    for (uint32_t p = 0; p < kDdParts; ++p) {
+        lo[p] = q0 + p < q1 ? qbeg[q0 + p] : 0;
+        const uint64_t n = q0 + p < q1 ? end_of(q0 + p) - lo[p] : 0;
+        small &= n <= kDdThreads * kDdHeld;
+        upto[p + 1] = upto[p] + (uint32_t)n;
+    }
+    if (small && upto[kDdParts] <= kDdThreads * kDdHeld) {
+        // the records stay in registers, with their slots, between the two halves
+        uint64_t x[kDdHeld];
+        uint32_t at[kDdHeld], v[kDdHeld], slot[kDdHeld];
+#pragma unroll
+        for (uint32_t k = 0; k < kDdHeld; ++k) {
+            const uint32_t j = tid + k * kDdThreads;
+            if (j < upto[kDdParts]) {
+                uint64_t i = lo[0] + j;
+#pragma unroll
+                for (uint32_t p = 1; p < kDdParts; ++p)
+                    if (j >= upto[p]) i = lo[p] + (j - upto[p]);
+                x[k] = keys[i];
+                at[k] = idx ? idx[i] : (uint32_t)i;
+                v[k] = vals[i];
             }
         }
+#pragma unroll
+        for (uint32_t k = 0; k < kDdHeld; ++k)
+            if (tid + k * kDdThreads < upto[kDdParts] && !insert(x[k], at[k], slot[k])) full = 1;
+        reserve();
+        if (full) return;   // the whole block: the host tries another hash
+#pragma unroll
+        for (uint32_t k = 0; k < kDdHeld; ++k)
+            if (tid + k * kDdThreads < upto[kDdParts]) emit(x[k], at[k], v[k], slot[k]);
+        return;
     }
-    if (claimed) atomicAdd(&distinct, claimed);
-    __syncthreads();
-    if (tid == 0) {
-        base = 0;
-        if (full) atomicOr(&ctrl->full, 1u);
-        else if (distinct) base = atomicAdd(&ctrl->count, distinct);
-    }
-    __syncthreads();
-    if (full) return;   // the whole block: the host tries another hash
-    // the record that is its key's first occurrence goes to the list
+    // crowded partitions (a key repeated very often): the records are read twice
     for (uint32_t q = q0; q < q1; ++q) {
-        const uint64_t lo = qbeg[q], hi = qcap ? min(qend[q], lo + qcap) : qend[q];
-        for (uint64_t i0 = lo; i0 < hi; i0 += kDdThreads * kDdUnroll) {
-            uint64_t x[kDdUnroll];
-            uint32_t at[kDdUnroll], v[kDdUnroll];
-#pragma unroll
-            for (uint32_t k = 0; k < kDdUnroll; ++k) {
-                const uint64_t i = i0 + tid + (uint64_t)k * kDdThreads;
-                x[k] = i < hi ? keys[i] : 0;
-                at[k] = i < hi ? (idx ? idx[i] : (uint32_t)i) : 0;
-                v[k] = i < hi ? vals[i] : 0;
-            }
-#pragma unroll
-            for (uint32_t k = 0; k < kDdUnroll; ++k) {
-                if (i0 + tid + (uint64_t)k * kDdThreads >= hi) continue;
-                bool first;
-                if (x[k] == kEmpty) {
-                    first = side == at[k];
-                } else {
-                    uint32_t s = slot_of(x[k]);
-                    while (tkey[s] != x[k]) s = (s + 1) & (kDdSlots - 1);
-                    first = tidx[s] == at[k];
-                }
-                if (first) {
-                    const uint64_t pos = (uint64_t)base + atomicAdd(&put, 1u);
-                    if (pos < out_cap) {
-                        out_keys[pos] = x[k];
-                        out_vals[pos] = v[k];
-                    }
-                }
-            }
+        const uint64_t hi = end_of(q);
+        for (uint64_t i = qbeg[q] + tid; i < hi; i += kDdThreads) {
+            uint32_t s;
+            if (!insert(keys[i], idx ? idx[i] : (uint32_t)i, s)) full = 1;
+        }
+    }
+    reserve();
+    if (full) return;   // the whole block: the host tries another hash
+    for (uint32_t q = q0; q < q1; ++q) {
+        const uint64_t hi = end_of(q);
+        for (uint64_t i = qbeg[q] + tid; i < hi; i += kDdThreads) {
+            const uint64_t x = keys[i];
+            uint32_t s = kDdSlots;
+            if (x != kEmpty)
+                for (s = slot_of(x); tkey[s] != x;) s = (s + 1) & (kDdSlots - 1);
+            emit(x, idx ? idx[i] : (uint32_t)i, vals[i], s);
         }
     }
 }
