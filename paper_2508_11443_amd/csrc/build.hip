@@ -232,10 +232,10 @@ static uint64_t cells_guess(uint64_t n, uint32_t c) {
 }
 
 // Level-one attempts with the partitioned passes (partition.hip).
-// d_aux_in: the high halves of 64-bit values (kind 2), else nullptr.
+// d_vals64: the values of a map with 64-bit values (kind 2; d_vals is null then), else nullptr.
 // d_off, d_bytes: strings that the first attempt has yet to copy into the map (d_off null: copied).
 static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uint32_t* d_vals,
-                                const uint32_t* d_aux_in, const int64_t* d_off, const uint8_t* d_bytes,
+                                const uint64_t* d_vals64, const int64_t* d_off, const uint8_t* d_bytes,
                                 const fks_params& P, Ctrl* ctrl, Readback* host,
                                 uint64_t* y, hipStream_t st) {
     const uint64_t n = M->n;
@@ -251,8 +251,8 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
     a.G = G;
     a.aux = carry;
     a.str = bytes;
-    a.aux_in = d_aux_in;
     a.vals = d_vals;
+    a.pairs = d_vals64;
     // scratch, carved from one allocation (one allocation and one release per build), freed
     // when the attempts are over; buffers allocated later (the rounds schedule's trials) join
     // the owned list
@@ -280,6 +280,25 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
     // the tickets
     a.ticketed = M->has_alloc;
     a.cursor = cursor;
+    // 64-bit values: the first cursor pass takes them whole; everything else takes their low halves as
+    // values and the high halves as aux words, from arrays of their own
+    auto split_values = [&]() {
+        if (!a.pairs) return true;
+        uint32_t* lo = (uint32_t*)dev_alloc(4 * n, st);
+        uint32_t* hi = (uint32_t*)dev_alloc(4 * n, st);
+        owned.push_back(lo);
+        owned.push_back(hi);
+        if (!lo || !hi) return false;
+        hipLaunchKernelGGL(k_split_u64, grid_for(n, kBlock, 65536), kBlock, 0, st, d_vals64, n, lo, hi);
+        a.vals = lo;
+        a.aux_in = hi;
+        a.pairs = nullptr;
+        return true;
+    };
+    if (!cursor && !split_values()) {
+        release(false);
+        return FKS_ENOMEM;
+    }
     const uint32_t* const reject = &ctrl->oversize;   // followed by bad_input
     if (direct) {
         cap = std::min<uint64_t>(P.c, 4) * n;
@@ -354,6 +373,10 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
                 // a region of the cursor passes overflowed (keys far from uniform over the
                 // partitions): the same attempt again with counted passes
                 a.cursor = false;
+                if (!split_values()) {
+                    rc = FKS_ENOMEM;
+                    break;
+                }
                 --r;
                 continue;
             }
@@ -470,7 +493,7 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
 }
 
 // keys: device u64 keys (or fingerprints); vals; aux_is_index for string maps
-static int build_common(fks_map* M, const uint64_t* d_keys_in, const uint32_t* d_vals, const uint32_t* d_aux_in,
+static int build_common(fks_map* M, const uint64_t* d_keys_in, const uint32_t* d_vals, const uint64_t* d_vals64,
                         const int64_t* d_off, const uint8_t* d_bytes, uint64_t nbytes,
                         const fks_params& P, hipStream_t st) {
     const uint64_t n = M->n;
@@ -511,7 +534,7 @@ static int build_common(fks_map* M, const uint64_t* d_keys_in, const uint32_t* d
     }
 
     M->magic_n = fastmod_magic((uint32_t)n);
-    rc = attempts_partitioned(M, d_keys_in, d_vals, d_aux_in, d_off, d_bytes, P, w.ctrl, w.host, w.y, st);
+    rc = attempts_partitioned(M, d_keys_in, d_vals, d_vals64, d_off, d_bytes, P, w.ctrl, w.host, w.y, st);
     free_scratch(w, st, rc == FKS_OK);   // an accepted attempt's outcome was the last thing waited for
     return rc;
 }
@@ -588,17 +611,7 @@ extern "C" int fks_build_u64_v64(const uint64_t* d_keys, const uint64_t* d_vals,
     if (n == 0) {
         rc = build_empty(M, P, st);
     } else {
-        // the construction carries the low halves as values and the high halves as aux words
-        uint32_t* lo = (uint32_t*)dev_alloc(4 * n, st);
-        uint32_t* hi = (uint32_t*)dev_alloc(4 * n, st);
-        if (!lo || !hi) {
-            rc = FKS_ENOMEM;
-        } else {
-            hipLaunchKernelGGL(k_split_u64, grid_for(n, kBlock, 65536), kBlock, 0, st, d_vals, n, lo, hi);
-            rc = build_common(M, d_keys, lo, hi, nullptr, nullptr, 0, P, st);
-        }
-        dev_free(lo, st, rc == FKS_OK);
-        dev_free(hi, st, rc == FKS_OK);
+        rc = build_common(M, d_keys, nullptr, d_vals, nullptr, nullptr, 0, P, st);
     }
     if (rc) {
         release_partial(M, st);

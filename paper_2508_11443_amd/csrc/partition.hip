@@ -146,7 +146,8 @@ __global__ __launch_bounds__(BT) void k_dscatter(const uint64_t* __restrict__ ke
                                                     unsigned long long* __restrict__ cursor = nullptr,
                                                     const uint64_t* __restrict__ ranges_hi = nullptr,
                                                     uint64_t cap = 0, uint32_t* __restrict__ overflow = nullptr,
-                                                    uint64_t in_cap = 0, uint32_t subs = 0, uint32_t in_subs = 0) {
+                                                    uint64_t in_cap = 0, uint32_t subs = 0, uint32_t in_subs = 0,
+                                                    const uint64_t* __restrict__ pairs = nullptr) {
     __shared__ uint64_t skey[(BT * ITEMS)];
     __shared__ uint32_t sval[(BT * ITEMS)];
     __shared__ uint32_t saux[AUX ? (BT * ITEMS) : 1];
@@ -197,6 +198,17 @@ __global__ __launch_bounds__(BT) void k_dscatter(const uint64_t* __restrict__ ke
     uint64_t x[ITEMS];
     uint32_t v[ITEMS], u[AUX ? ITEMS : 1];
     auto load = [&](uint64_t ts) {
+        if (AUX && pairs) {   // 64-bit values: low halves as values, high as aux words
+#pragma unroll
+            for (uint32_t k = 0; k < ITEMS; ++k) {
+                const uint64_t i = ts + tid + (uint64_t)k * BT;
+                x[k] = i < b ? keys[i] : 0;
+                const uint64_t p = i < b ? pairs[i] : 0;
+                v[k] = (uint32_t)p;
+                u[AUX ? k : 0] = (uint32_t)(p >> 32);
+            }
+            return;
+        }
 #pragma unroll
         for (uint32_t k = 0; k < ITEMS; ++k) {
             const uint64_t i = ts + tid + (uint64_t)k * BT;
@@ -1265,7 +1277,8 @@ static void scatter_cursor(const PartArgs& a, const PartPlan& P, const uint64_t*
         FKS_TIMED("fks_part_scatter", st,
                   hipLaunchKernelGGL(kernel, grid, kPScatterThreads, 0, st, kin, vin, ain, a.n, a.A, a.magic, ranges, W,
                                      shift, mask, nullptr, kout, vout, aout, nullptr, nullptr, cursor, ranges_hi,
-                                     cap, a.overflow, in_cap, subs, in_subs));
+                                     cap, a.overflow, in_cap, subs, in_subs,
+                                     kin == a.keys ? a.pairs : nullptr));
     };
     if (P.items == 2) launch(k_dscatter<AUX, 2, kPScatterThreads, true>);
     else if (P.items == 4) launch(k_dscatter<AUX, 4, kPScatterThreads, true>);

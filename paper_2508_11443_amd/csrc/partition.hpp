@@ -77,6 +77,7 @@ struct PartArgs {
     bool aux;                   // an aux word travels with every key
     bool str;                   // keys are string fingerprints
     const uint32_t* aux_in;     // the input's aux words, or nullptr for the key index
+    const uint64_t* pairs;      // passes with cursors: values and aux words as the halves of 64-bit words, or nullptr
     Triple A;
     uint64_t magic;
     const uint64_t* keys;       // the integers the construction hashes
