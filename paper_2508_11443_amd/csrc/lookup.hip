@@ -96,7 +96,7 @@ OrdScratch::OrdScratch(uint64_t m, uint32_t bins, bool ids, uint32_t val_bytes, 
         return;
     }
     if (cap != hipStreamCaptureStatusNone) return;
-    a_.tile = ord_tile(ids);
+    a_.tile = ord_tile(m, ids);
     a_.bins = bins;
     const size_t tiles = (m + a_.tile - 1) / a_.tile;
     size_t total = 0;

@@ -71,8 +71,8 @@ __global__ __launch_bounds__(kOrdThreads) void k_ord_group(Part part, const uint
     __shared__ uint32_t cnt[kOrdBins], at[kOrdBins], wsum[kOrdBins / 64];
     __shared__ uint64_t own[Part::kLds ? Part::kLds : 1];
     const uint32_t tid = threadIdx.x;
-    const uint64_t base = (uint64_t)blockIdx.x * TILE;
-    const uint32_t count = (uint32_t)min((uint64_t)TILE, o.m - base);
+    const uint64_t base = (uint64_t)blockIdx.x * o.tile;
+    const uint32_t count = (uint32_t)min((uint64_t)o.tile, o.m - base);   // at most TILE
     uint64_t x[ITEMS];
     uint32_t id[IDS ? ITEMS : 1];
 #pragma unroll
@@ -184,8 +184,8 @@ __global__ __launch_bounds__(kOrdThreads) void k_ord_return(OrdArgs o, V* __rest
     constexpr uint32_t ITEMS = TILE / kOrdThreads;
     __shared__ V sv[TILE];
     __shared__ uint8_t sf[TILE];
-    const uint64_t base = (uint64_t)blockIdx.x * TILE;
-    const uint32_t count = (uint32_t)min((uint64_t)TILE, o.m - base), tid = threadIdx.x;
+    const uint64_t base = (uint64_t)blockIdx.x * o.tile;
+    const uint32_t count = (uint32_t)min((uint64_t)o.tile, o.m - base), tid = threadIdx.x;   // at most TILE
     const V* val = (const V*)o.val + base;
     uint16_t slot[ITEMS];
 #pragma unroll
@@ -212,7 +212,16 @@ __global__ __launch_bounds__(kOrdThreads) void k_ord_return(OrdArgs o, V* __rest
 // ---- host side ---------------------------------------------------------------------------
 
 constexpr uint64_t kOrdSlice = 1ull << 27;   // needles at a time: 2 GB of scratch
-constexpr uint32_t ord_tile(bool ids) { return kOrdThreads * (ids ? kOrdItemsIds : kOrdItems); }
+constexpr uint32_t ord_tile_max(bool ids) { return kOrdThreads * (ids ? kOrdItemsIds : kOrdItems); }
+// Tiles of a size that gives all 256 CUs equally many (a CU holds one workgroup of the grouping
+// pass): 2^22 needles 84 us (88 with tiles of 15360), 10^7 239 (243), 2^24 358 (368).  With map ids the
+// tiles are smaller to begin with, and shorter runs cost what even rounds gain.
+inline uint32_t ord_tile(uint64_t m, bool ids) {
+    if (ids) return ord_tile_max(ids);
+    const uint64_t round = 256ull * ord_tile_max(ids), rounds = (m + round - 1) / round;
+    const uint64_t tile = (m + 256 * rounds - 1) / (256 * rounds);
+    return (uint32_t)((tile + 63) & ~63ull);
+}
 
 // Scratch of one call on stream s, given back in stream order when it goes out of scope.
 class OrdScratch {
@@ -249,7 +258,7 @@ void ord_group(const Part& part, const uint64_t* q, const uint32_t* ids, const O
 template <typename V, bool IDS>
 void ord_return(const OrdArgs& a, V* vals, uint8_t* found, hipStream_t st) {
     FKS_TIMED("fks_order_return", st,
-              hipLaunchKernelGGL((k_ord_return<V, ord_tile(IDS)>), a.tiles, kOrdThreads, 0, st, a, vals, found));
+              hipLaunchKernelGGL((k_ord_return<V, ord_tile_max(IDS)>), a.tiles, kOrdThreads, 0, st, a, vals, found));
 }
 
 }  // namespace fks
