@@ -1148,10 +1148,8 @@ PartPlan part_plan(uint64_t n, bool carry) {
     // Tiles of the cursor form and keys per worker, so that a small input is not left to a few
     // CUs.  Build, one lookup and release with tiles of 12288 keys, two per worker, and here: 2^16 keys
     // (three workers) 69 and 56 us with tiles of 2048 (57 of 4096), 2^18 75 and 62, 2^20 107
-    // and 98 with tiles of 4096 (104 of 2048), 3 * 10^6 156 and 153 with one large tile per
-    // worker (157 and 172 with tiles of 4096 and 2048).  One large tile per worker as long as
-    // every worker has a CU of its own: the passes over 2^22 keys take 31 + 23 us with 171
-    // workers of two tiles, 34 + 26 with 342 of one.
+    // and 98 with tiles of 4096 (104 of 2048); 3 * 10^6 156, 157 and 172 with tiles of 12288, 4096
+    // and 2048.
     uint64_t worker = 2ull * kPScatterThreads * kPScatterItems;
     if (n <= 256ull * kPartBuckets) {
         P.items = 2;
@@ -1159,10 +1157,12 @@ PartPlan part_plan(uint64_t n, bool carry) {
     } else if (n < (1ull << 21)) {
         P.items = 4;
         worker = (uint64_t)kPScatterThreads * P.items;
-    } else if (n <= 256ull * kPScatterThreads * kPScatterItems) {
-        worker = (uint64_t)kPScatterThreads * kPScatterItems;
     }
     P.W1 = clampu((n + worker - 1) / worker, 1, 4096);
+    // the large tiles leave a CU to one worker: as many workers as fill all 256 CUs the same number of
+    // times.  First pass of 2^23 records with an aux word 76 us with 342 workers and 63 with 512, of
+    // 2^22 39 with 171 and 32 with 256, of 10^7 without 65 with 407 and 62 with 512.
+    if (P.items == 0) P.W1 = (P.W1 + 255) & ~255u;
     if (P.Q <= 1) {
         P.passes = 0;
     } else if (bits <= 8) {
