@@ -10,6 +10,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "fks_internal.hpp"
 #include "ordered.hpp"
@@ -18,7 +19,7 @@
 namespace fks {
 
 constexpr int kLBlock = 256;
-constexpr int kQ = 4;   // needles in flight per thread
+constexpr int kQ = 4;   // needles in flight per thread (integer needles: many of them)
 
 __global__ void k_fill_outputs(uint64_t m, uint32_t* __restrict__ vals, uint64_t* __restrict__ vals64,
                                uint8_t* __restrict__ found, uint32_t missing, uint64_t missing64) {
@@ -31,7 +32,8 @@ __global__ void k_fill_outputs(uint64_t m, uint32_t* __restrict__ vals, uint64_t
 }
 
 // V64: 64-bit values, the high half in the cell's aux word
-template <bool WANT_VALS, bool WANT_FOUND, bool V64 = false>
+// Q: needles in flight per thread
+template <bool WANT_VALS, bool WANT_FOUND, bool V64, int Q>
 __global__ __launch_bounds__(kLBlock) void k_lookup_u64(const Group* __restrict__ header,
                                                           const Cell* __restrict__ slots, Triple A,
                                                           uint64_t magic, uint32_t n,
@@ -42,30 +44,34 @@ __global__ __launch_bounds__(kLBlock) void k_lookup_u64(const Group* __restrict_
                                                           uint64_t* __restrict__ vals64 = nullptr,
                                                           uint64_t missing64 = 0) {
     __shared__ Triple C[kTMax];
-    for (uint32_t t = threadIdx.x; t < T; t += kLBlock) C[t] = Cg[t];
-    __syncthreads();
-    const uint64_t stride = (uint64_t)gridDim.x * kLBlock * kQ;
-    for (uint64_t base = (uint64_t)blockIdx.x * kLBlock * kQ; base < m; base += stride) {
-        uint64_t x[kQ];
-        Group h[kQ];
-        uint32_t kk[kQ];
+    const uint64_t stride = (uint64_t)gridDim.x * kLBlock * Q, first = (uint64_t)blockIdx.x * kLBlock * Q;
+    uint64_t x[Q];
+    auto load = [&](uint64_t base) {
 #pragma unroll
-        for (int k = 0; k < kQ; ++k) {
+        for (int k = 0; k < Q; ++k) {
             const uint64_t i = base + threadIdx.x + (uint64_t)k * kLBlock;
             x[k] = i < m ? __builtin_nontemporal_load(q + i) : 0;   // needles and answers stream
         }
+    };
+    load(first);   // under way while the triples are staged
+    for (uint32_t t = threadIdx.x; t < T; t += kLBlock) C[t] = Cg[t];
+    __syncthreads();
+    for (uint64_t base = first; base < m; base += stride) {
+        if (base != first) load(base);
+        Group h[Q];
+        uint32_t kk[Q];
 #pragma unroll
-        for (int k = 0; k < kQ; ++k) {
+        for (int k = 0; k < Q; ++k) {
             const uint64_t i = base + threadIdx.x + (uint64_t)k * kLBlock;
             const uint32_t j = fastmod(mshash(A, x[k]), magic, n);
             kk[k] = j & 7u;
             if (i < m) h[k] = header[j >> 3];
             else h[k] = Group{0, 0, 0, 0};
         }
-        Cell c[kQ];
-        uint32_t s[kQ];
+        Cell c[Q];
+        uint32_t s[Q];
 #pragma unroll
-        for (int k = 0; k < kQ; ++k) {
+        for (int k = 0; k < Q; ++k) {
             uint32_t p;
             s[k] = cell_of(h[k], kk[k], C, x[k], p) ? 1u : 0u;
             // read once per needle: a streaming load, so that the cells do not push the group
@@ -73,7 +79,7 @@ __global__ __launch_bounds__(kLBlock) void k_lookup_u64(const Group* __restrict_
             c[k] = s[k] ? load_cell_once(slots + p) : Cell{~x[k], 0, 0};
         }
 #pragma unroll
-        for (int k = 0; k < kQ; ++k) {
+        for (int k = 0; k < Q; ++k) {
             const uint64_t i = base + threadIdx.x + (uint64_t)k * kLBlock;
             if (i < m) {
                 const bool hit = s[k] && c[k].key == x[k];
@@ -293,6 +299,30 @@ static unsigned lookup_grid(uint64_t m, uint64_t per_block) {
     return (unsigned)g;
 }
 
+// A lookup in the needles' own order.
+template <bool V64>
+static void launch_lookup(const fks_map* map, const uint64_t* q, uint64_t m, uint32_t* vals, uint64_t* vals64,
+                          uint8_t* found, uint32_t missing, uint64_t missing64, hipStream_t st) {
+    const bool want_vals = V64 ? vals64 != nullptr : vals != nullptr;
+    auto launch = [&](auto kernel, uint64_t needles) {
+        FKS_TIMED(V64 ? "fks_lookup_u64_v64" : want_vals ? "fks_lookup_u64" : "fks_contains_u64", st,
+                  hipLaunchKernelGGL(kernel, lookup_grid(m, (uint64_t)kLBlock * needles), kLBlock, 0, st, map->header,
+                                     map->slots, map->A, map->magic_n, (uint32_t)map->n, map->C, map->T, q, m, vals,
+                                     found, missing, vals64, missing64));
+    };
+    auto with = [&](auto q_) {
+        constexpr int Q = decltype(q_)::value;
+        if (want_vals && found) launch(k_lookup_u64<true, true, V64, Q>, Q);
+        else if (want_vals) launch(k_lookup_u64<true, false, V64, Q>, Q);
+        else launch(k_lookup_u64<false, true, V64, Q>, Q);
+    };
+    // few needles are one thread's chain of dependent reads: one needle each, on as many CUs as there
+    // are (kernel over 2^16 keys with one and four needles per thread: 1000 needles 2.5 and 5.0 us,
+    // 2^16 3.3 and 6.2, 2^18 5.3 and 7.2, 2^19 8.9 and 8.7, 2^21 over 2^20 keys 38.4 and 37.7)
+    if (m <= (1u << 19)) with(std::integral_constant<int, 1>{});
+    else with(std::integral_constant<int, kQ>{});
+}
+
 }  // namespace fks
 
 using namespace fks;
@@ -308,19 +338,7 @@ extern "C" int fks_lookup_u64(const fks_map* map, const uint64_t* d_queries, uin
         FKS_TIMED("fks_fill_outputs", st, hipLaunchKernelGGL(k_fill_outputs, lookup_grid(m, kLBlock), kLBlock, 0, st, m, d_vals_out, nullptr, d_found_out,
                            missing, 0ull));
     } else if (!ordered_lookup<false, uint32_t>(map, d_queries, m, d_vals_out, d_found_out, missing, st)) {
-        const unsigned grid = lookup_grid(m, (uint64_t)kLBlock * kQ);
-        if (d_vals_out && d_found_out)
-            FKS_TIMED("fks_lookup_u64", st, hipLaunchKernelGGL((k_lookup_u64<true, true>), grid, kLBlock, 0, st, map->header, map->slots, map->A,
-                               map->magic_n, (uint32_t)map->n, map->C, map->T, d_queries, m, d_vals_out,
-                               d_found_out, missing));
-        else if (d_vals_out)
-            FKS_TIMED("fks_lookup_u64", st, hipLaunchKernelGGL((k_lookup_u64<true, false>), grid, kLBlock, 0, st, map->header, map->slots, map->A,
-                               map->magic_n, (uint32_t)map->n, map->C, map->T, d_queries, m, d_vals_out,
-                               d_found_out, missing));
-        else
-            FKS_TIMED("fks_contains_u64", st, hipLaunchKernelGGL((k_lookup_u64<false, true>), grid, kLBlock, 0, st, map->header, map->slots, map->A,
-                               map->magic_n, (uint32_t)map->n, map->C, map->T, d_queries, m, d_vals_out,
-                               d_found_out, missing));
+        launch_lookup<false>(map, d_queries, m, d_vals_out, nullptr, d_found_out, missing, 0, st);
     }
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? FKS_OK : hip_fail(e);
@@ -342,17 +360,7 @@ extern "C" int fks_lookup_u64_v64(const fks_map* map, const uint64_t* d_queries,
                   hipLaunchKernelGGL(k_fill_outputs, lookup_grid(m, kLBlock), kLBlock, 0, st, m, nullptr, d_vals_out,
                                      d_found_out, 0u, missing));
     } else if (!ordered_lookup<true, uint64_t>(map, d_queries, m, d_vals_out, d_found_out, missing, st)) {
-        const unsigned grid = lookup_grid(m, (uint64_t)kLBlock * kQ);
-        if (d_found_out)
-            FKS_TIMED("fks_lookup_u64_v64", st,
-                      hipLaunchKernelGGL((k_lookup_u64<true, true, true>), grid, kLBlock, 0, st, map->header,
-                                         map->slots, map->A, map->magic_n, (uint32_t)map->n, map->C, map->T,
-                                         d_queries, m, nullptr, d_found_out, 0u, d_vals_out, missing));
-        else
-            FKS_TIMED("fks_lookup_u64_v64", st,
-                      hipLaunchKernelGGL((k_lookup_u64<true, false, true>), grid, kLBlock, 0, st, map->header,
-                                         map->slots, map->A, map->magic_n, (uint32_t)map->n, map->C, map->T,
-                                         d_queries, m, nullptr, nullptr, 0u, d_vals_out, missing));
+        launch_lookup<true>(map, d_queries, m, nullptr, d_vals_out, d_found_out, 0u, missing, st);
     }
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? FKS_OK : hip_fail(e);
