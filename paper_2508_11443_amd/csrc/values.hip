@@ -88,13 +88,31 @@ __device__ __forceinline__ uint64_t block_fold(uint64_t v, uint32_t op, uint64_t
     return red[0];
 }
 
+// sum of v over the threads before this one; wsum: a word per wave (used up to the next barrier)
+__device__ __forceinline__ uint32_t before_me(uint32_t v, uint32_t* wsum) {
+    const uint32_t lane = threadIdx.x & 63u, w = threadIdx.x >> 6;
+    uint32_t inc = v;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t u = __shfl_up(inc, d, 64);
+        if (lane >= (uint32_t)d) inc += u;
+    }
+    if (lane == 63) wsum[w] = inc;
+    __syncthreads();
+    uint32_t pre = inc - v;
+    for (uint32_t k = 0; k < w; ++k) pre += wsum[k];
+    return pre;
+}
+
 // first pass: each workgroup takes ranges of kVBlock consecutive groups (one group record
-// per lane, staged in LDS with an LDS map from each of the range's cells to its bucket),
-// then streams the range's cells, consecutive cells on consecutive lanes.  A cell holds its
+// per lane, staged in LDS), then streams the range's cells, consecutive cells on consecutive lanes.
+// A bit at every bucket's first cell, counts of the bits before every word and a list of the
+// buckets that have cells give each cell its bucket.  A cell holds its
 // own key exactly when the key's level-two hash in the cell's bucket lands on the cell; a
 // fill copy of a bucket's lowest key sits elsewhere and is skipped, so each key is folded
-// once.  A range with more cells than the LDS map holds (far beyond the ~15 cells of eight
+// once.  A range with more cells than the bits (far beyond the ~15 cells of eight
 // buckets of random keys) is walked bucket by bucket instead.
+// 2^24 keys (0.57 GB): 118 us; with every cell's bucket written to a map by the lane of its group 138.
 constexpr uint32_t kRMapCells = 8192;   // cells of one range mapped in LDS
 constexpr uint32_t kRUnroll = 4;        // cells per lane in flight
 
@@ -105,9 +123,11 @@ __global__ __launch_bounds__(kVBlock) void k_reduce_ranges(const Group* __restri
                                                              uint64_t ident, uint64_t* __restrict__ partial) {
     extern __shared__ Triple C[];            // the map's T level-two triples
     __shared__ Group rec[kVBlock];
-    // (group in the range << 3) | bucket of each of the range's cells; at the end, the
-    // workgroup's fold (the map is no longer read then)
-    __shared__ __align__(16) uint16_t owner[kRMapCells];
+    // (group in the range << 3) | bucket of each bucket with cells, in order; at the end, the
+    // workgroup's fold (the list is no longer read then)
+    __shared__ __align__(16) uint16_t owner[8 * kVBlock];
+    __shared__ uint32_t starts[kRMapCells / 32], ahead[kRMapCells / 32], wsum[2][kVBlock / 64];
+    static_assert(kRMapCells / 32 == kVBlock, "a word of bits per thread");
     __shared__ uint64_t mag[16];
     __shared__ uint32_t span[2];
     static_assert(sizeof(owner) >= kVBlock * sizeof(uint64_t), "the fold fits the map");
@@ -121,32 +141,45 @@ __global__ __launch_bounds__(kVBlock) void k_reduce_ranges(const Group* __restri
         Group h{0, 0, 0, 0};
         if (tid < ng) h = header[g0 + tid];
         rec[tid] = h;
+        starts[tid] = 0;
         if (tid == 0) span[0] = h.base;
         if (tid == ng - 1) span[1] = h.base + prefix_sq(h.sizes, 8);   // end of the range's cells
         __syncthreads();
         const uint32_t c0 = span[0], nc = span[1] - span[0];
         if (nc <= kRMapCells) {
-            // every cell of the lane's group gets its bucket
-            if (tid < ng) {
-                for (uint32_t k = 0; k < 8; ++k) {
-                    const uint32_t sb = nib(h.sizes, k);
-                    const uint32_t at = h.base - c0 + prefix_sq(h.sizes, k);
-                    for (uint32_t p = 0; p < sb * sb; ++p) owner[at + p] = (uint16_t)((tid << 3) | k);
-                }
-            }
-            __syncthreads();
-            for (uint32_t e0 = 0; e0 < nc; e0 += kVBlock * kRUnroll) {
-                Cell x[kRUnroll];
+            Cell x[kRUnroll], next[kRUnroll];
+            auto load = [&](Cell (&y)[kRUnroll], uint32_t e0) {
 #pragma unroll
                 for (uint32_t u = 0; u < kRUnroll; ++u) {
                     const uint32_t e = e0 + u * kVBlock + tid;
-                    x[u] = e < nc && (uint64_t)c0 + e < S ? load_cell_once(slots + c0 + e) : Cell{0, 0, 0};
+                    y[u] = e < nc && (uint64_t)c0 + e < S ? load_cell_once(slots + c0 + e) : Cell{0, 0, 0};
                 }
+            };
+            load(x, 0);   // under way while the buckets are marked
+            const uint32_t some = (h.sizes | h.sizes >> 1 | h.sizes >> 2 | h.sizes >> 3) & 0x11111111u;
+            uint32_t place = before_me((uint32_t)__popc(some), wsum[0]), at = h.base - c0;
+            if (tid < ng) {
+#pragma unroll
+                for (uint32_t k = 0; k < 8; ++k) {
+                    const uint32_t sb = nib(h.sizes, k);
+                    if (sb) {
+                        atomicOr(&starts[at >> 5], 1u << (at & 31u));
+                        owner[place++] = (uint16_t)((tid << 3) | k);
+                        at += sb * sb;
+                    }
+                }
+            }
+            __syncthreads();
+            ahead[tid] = before_me((uint32_t)__popc(starts[tid]), wsum[1]);
+            __syncthreads();
+            for (uint32_t e0 = 0; e0 < nc; e0 += kVBlock * kRUnroll) {
+                load(next, e0 + kVBlock * kRUnroll);
 #pragma unroll
                 for (uint32_t u = 0; u < kRUnroll; ++u) {
                     const uint32_t e = e0 + u * kVBlock + tid;
                     if (e >= nc || (uint64_t)c0 + e >= S) continue;
-                    const uint32_t o = owner[e];
+                    const uint32_t upto = starts[e >> 5] & (0xFFFFFFFFu >> (31u - (e & 31u)));
+                    const uint32_t o = owner[ahead[e >> 5] + (uint32_t)__popc(upto) - 1];
                     const Group& r = rec[o >> 3];
                     const uint32_t k = o & 7u, sb = nib(r.sizes, k);
                     const uint32_t t = sb == 1 ? 0u : group_t(r, k);   // a one-key bucket's byte is a tag
@@ -155,6 +188,8 @@ __global__ __launch_bounds__(kVBlock) void k_reduce_ranges(const Group* __restri
                     if (fastmod(mshash(C[t], x[u].key), mag[sb], sb * sb) == local)
                         acc = combine(op, acc, cell_value(x[u], V64));
                 }
+#pragma unroll
+                for (uint32_t u = 0; u < kRUnroll; ++u) x[u] = next[u];
             }
         } else if (tid < ng) {
             // a range too large for the map: the lane walks its own group's buckets
