@@ -22,9 +22,16 @@
  *   - `stream` is a hipStream_t passed as void*; NULL is the default stream.
  *     Builds are ordered on the stream and synchronise the host with it
  *     once per level-one attempt, to read its outcome (twice when the table
- *     needs more cells than the bound the build allocates first, or under
+ *     needs more cells than the build allocates first, or under
  *     params.schedule = 1, which reads the table size before its search).
- *     Lookups are fully asynchronous.
+ *     Without an allocator that first allocation is 4n cells, up to 8 GiB, and
+ *     what the table leaves of it is given back; a map, and a build's scratch,
+ *     then come from a pool of the library's own, which keeps at most an
+ *     eighth of the device's memory free for the next call.
+ *     Lookups are fully asynchronous.  Those of 2^22 and more needles may take
+ *     15 to 20 bytes per needle from that pool until the stream is done with
+ *     them; where it has none, under capture, and on maps built with an
+ *     allocator they take nothing.
  *   - Return value 0 (FKS_OK) is success; negative values are the FKS_E*
  *     codes below.  Out-parameters are written only on success.
  *   - Maps are immutable after their build and may be read by any number of
