@@ -9,8 +9,8 @@
 // order, tile by tile (k_ord_return).  The two extra passes move about 30 bytes per needle,
 // all of it in streams.
 //
-// 10^7 needles over as many keys: 347 us in their own order, 246 us so (grouping 44, answers 156,
-// return 41); 2^26 over 2^26: 2.10 and 1.47 ms.  Runs are kept long (large tiles, few parts): with 512
+// 10^7 needles over as many keys: 347 us in their own order, 234 us so (grouping 44, answers 156,
+// return 22); 2^26 over 2^26: 2.10 and 1.38 ms.  Runs are kept long (large tiles, few parts): with 512
 // parts a run is 30 needles, and its partial lines cost more than the smaller parts gain
 // (264 us, 1.60 ms).  Part w mod 8 on each XCD rather than a stretch of neighbours: parts differ
 // in needles where keys are clustered, and neighbours alike (a sorted map 632 us instead of 516).
@@ -177,35 +177,83 @@ __device__ __forceinline__ uint64_t ord_place(const OrdRuns& R, uint32_t i) {
     return R.src[r] + i;
 }
 
-// One tile of answers back in the caller's order.
+// One tile of answers back in the caller's order.  Four neighbours per thread and access, all
+// loads in flight before the first is used: 2^26 answers 129 us, 215 with one access of 1, 2 or 4
+// bytes per needle; 10^7 22 and 35.  Bound by its streams, 12 bytes per needle.  The caller's arrays may start
+// anywhere their type allows: whole vectors are stored where they are aligned.
+template <typename T>
+using OrdVec4 = T __attribute__((ext_vector_type(4)));
+
 template <typename V, uint32_t TILE>
 __global__ __launch_bounds__(kOrdThreads) void k_ord_return(OrdArgs o, V* __restrict__ vals,
                                                            uint8_t* __restrict__ found) {
-    constexpr uint32_t ITEMS = TILE / kOrdThreads;
-    __shared__ V sv[TILE];
-    __shared__ uint8_t sf[TILE];
-    const uint64_t base = (uint64_t)blockIdx.x * o.tile;
+    constexpr uint32_t ITEMS = (TILE / 4 + kOrdThreads - 1) / kOrdThreads;
+    __shared__ __attribute__((aligned(16))) V sv[TILE];
+    __shared__ __attribute__((aligned(16))) uint8_t sf[TILE];
+    const uint64_t base = (uint64_t)blockIdx.x * o.tile;   // a multiple of 64
     const uint32_t count = (uint32_t)min((uint64_t)o.tile, o.m - base), tid = threadIdx.x;   // at most TILE
+    const uint32_t fours = count / 4;
     const V* val = (const V*)o.val + base;
-    uint16_t slot[ITEMS];
+    const OrdVec4<uint16_t>* slot4 = (const OrdVec4<uint16_t>*)(o.slot + base);
+    const OrdVec4<V>* val4 = (const OrdVec4<V>*)val;
+    const uint32_t* found4 = (const uint32_t*)(o.found + base);
+    OrdVec4<uint16_t> slot[ITEMS];
+    OrdVec4<V> v[ITEMS];
+    uint32_t f[ITEMS];
+    if (fours) {
 #pragma unroll
-    for (uint32_t k = 0; k < ITEMS; ++k) {
-        const uint32_t i = tid + k * kOrdThreads;
-        slot[k] = 0;
-        if (i < count) {
-            slot[k] = __builtin_nontemporal_load(o.slot + base + i);
-            if (vals) sv[i] = __builtin_nontemporal_load(val + i);
-            if (found) sf[i] = __builtin_nontemporal_load(o.found + base + i);
+        for (uint32_t k = 0; k < ITEMS; ++k) {
+            const uint32_t i = min(tid + k * kOrdThreads, fours - 1);
+            slot[k] = __builtin_nontemporal_load(slot4 + i);
+            if (vals) v[k] = __builtin_nontemporal_load(val4 + i);
+            if (found) f[k] = __builtin_nontemporal_load(found4 + i);
+        }
+#pragma unroll
+        for (uint32_t k = 0; k < ITEMS; ++k) {
+            const uint32_t i = tid + k * kOrdThreads;
+            if (i < fours) {
+                if (vals) ((OrdVec4<V>*)sv)[i] = v[k];
+                if (found) ((uint32_t*)sf)[i] = f[k];
+            }
         }
     }
+    const uint32_t rest = fours * 4 + tid;   // fewer than four, by as many threads
+    if (rest < count) {
+        if (vals) sv[rest] = val[rest];
+        if (found) sf[rest] = o.found[base + rest];
+    }
     __syncthreads();
+    V* const vout = vals ? vals + base : nullptr;
+    uint8_t* const fout = found ? found + base : nullptr;
+    const bool whole_v = ((uintptr_t)vout & (sizeof(OrdVec4<V>) - 1)) == 0, whole_f = ((uintptr_t)fout & 3u) == 0;
 #pragma unroll
     for (uint32_t k = 0; k < ITEMS; ++k) {
         const uint32_t i = tid + k * kOrdThreads;
-        if (i < count) {
-            if (vals) __builtin_nontemporal_store(sv[slot[k]], vals + base + i);
-            if (found) __builtin_nontemporal_store(sf[slot[k]], found + base + i);
+        if (i >= fours) break;
+        const OrdVec4<uint16_t> e = slot[k];
+        if (vals) {
+            const OrdVec4<V> r = {sv[e.x], sv[e.y], sv[e.z], sv[e.w]};
+            if (whole_v) {
+                __builtin_nontemporal_store(r, (OrdVec4<V>*)vout + i);
+            } else {
+#pragma unroll
+                for (uint32_t c = 0; c < 4; ++c) __builtin_nontemporal_store(r[c], vout + 4 * i + c);
+            }
         }
+        if (found) {
+            const uint32_t r = sf[e.x] | (uint32_t)sf[e.y] << 8 | (uint32_t)sf[e.z] << 16 | (uint32_t)sf[e.w] << 24;
+            if (whole_f) {
+                __builtin_nontemporal_store(r, (uint32_t*)fout + i);
+            } else {
+#pragma unroll
+                for (uint32_t c = 0; c < 4; ++c) __builtin_nontemporal_store((uint8_t)(r >> (8 * c)), fout + 4 * i + c);
+            }
+        }
+    }
+    if (rest < count) {
+        const uint32_t e = o.slot[base + rest];
+        if (vals) vout[rest] = sv[e];
+        if (found) fout[rest] = sf[e];
     }
 }
 
