@@ -561,8 +561,9 @@ struct FinalLds {
 
 // look-back polls of one predecessor's word before the fused pass gives up (far beyond any
 // real wait: every predecessor publishes its sum without waiting on anything); without tickets
-// sooner, as the build then starts again with them
-constexpr uint32_t kSpinLimit = 1u << 24, kSpinLimitUnticketed = 1u << 18;
+// sooner, as the build then starts again with them: after some milliseconds, a thousand times
+// what a workgroup takes, where the second attempt costs a final pass and less than the wait
+constexpr uint32_t kSpinLimit = 1u << 24, kSpinLimitUnticketed = 1u << 13;
 
 // The fused final pass (single map, level-two search in partition order): each partition
 // sizes its buckets itself, publishes its sum of squared sizes, and finds
