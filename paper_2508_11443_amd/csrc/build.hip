@@ -32,7 +32,7 @@ constexpr int kBlock = 256;
 // control words of one attempt (device), read back through Readback
 struct Ctrl {
     uint64_t S;
-    uint32_t oversize, bad_input, exhausted, dup, max_t, stalled, overflow, pad;   // same layout as Readback
+    uint32_t oversize, bad_input, exhausted, dup, max_t, overflow, done, pad;   // same layout as Readback
 };
 static_assert(sizeof(Ctrl) == sizeof(Readback), "read back as one block");
 // the final pass reads its two reject words from &oversize
@@ -59,7 +59,7 @@ __global__ void k_split_u64(const uint64_t* __restrict__ v, uint64_t n, uint32_t
 __global__ void k_zero_ctrl(Ctrl* c) {
     if (threadIdx.x == 0) {
         c->S = 0;
-        c->oversize = c->bad_input = c->exhausted = c->dup = c->max_t = c->stalled = c->overflow = c->pad = 0;
+        c->oversize = c->bad_input = c->exhausted = c->dup = c->max_t = c->overflow = c->done = c->pad = 0;
     }
 }
 
@@ -68,7 +68,7 @@ __global__ void k_zero_ctrl(Ctrl* c) {
 __global__ void k_attempt_setup(Ctrl* c, Triple* C, uint64_t seed, uint32_t r, uint32_t T) {
     if (threadIdx.x == 0) {
         c->S = 0;
-        c->oversize = c->bad_input = c->exhausted = c->dup = c->max_t = c->stalled = c->overflow = c->pad = 0;
+        c->oversize = c->bad_input = c->exhausted = c->dup = c->max_t = c->overflow = c->done = c->pad = 0;
     }
     for (uint32_t t = threadIdx.x; t < T; t += blockDim.x) C[t] = level2_triple(seed, r, t);
 }
@@ -273,12 +273,8 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
     a.overflow = &ctrl->overflow;
     a.S_dev = &ctrl->S;
     a.oversize = &ctrl->oversize;
-    a.stalled = &ctrl->stalled;
     // the direct form runs the fused final pass: it sizes the partitions itself
     a.fused = direct;
-    // maps in a caller's memory (the server's builds, several at a time beside its lookups) keep
-    // the tickets
-    a.ticketed = M->has_alloc;
     a.cursor = cursor;
     // 64-bit values: the first cursor pass takes them whole; everything else takes their low halves as
     // values and the high halves as aux words, from arrays of their own
@@ -333,7 +329,7 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
         const bool with_passes = !bytes && (a.cursor || plan.passes == 0);
         a.start = with_passes ? AttemptStart{(uint32_t*)ctrl, sizeof(Ctrl) / 4, M->C, M->seed, r, P.T} : AttemptStart{};
         a.outcome = with_passes && direct ? (uint32_t*)host : nullptr;
-        a.done = &ctrl->pad;
+        a.done = &ctrl->done;
         if (!with_passes) hipLaunchKernelGGL(k_attempt_setup, 1, 256, 0, st, ctrl, M->C, M->seed, r, P.T);
         if (bytes && d_off) {
             FKS_TIMED("fks_fingerprint", st,
@@ -358,15 +354,6 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
             if ((rc = readback(o.reported))) break;
             if (host->bad_input) {
                 rc = FKS_EINVAL;
-                break;
-            }
-            if (host->stalled) {
-                if (!a.ticketed) {   // workgroups out of order: the same attempt again with tickets
-                    a.ticketed = true;
-                    --r;
-                    continue;
-                }
-                rc = hip_fail(hipErrorLaunchFailure);
                 break;
             }
             if (host->overflow) {

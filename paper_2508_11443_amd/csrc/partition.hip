@@ -12,7 +12,7 @@
 // partition granularity) cross partitions: either a size pass and a scan turn them into
 // cell bases and the table size S, or the final pass publishes each total and finds its
 // own base by a look-back over its predecessors'.  Device-scope atomics serve only the
-// cursors, the final pass's tickets and look-back words, and an attempt's outcome flags;
+// cursors, the final pass's look-back words, and an attempt's outcome flags;
 // every per-key access is a coalesced stream or LDS.
 #include <hip/hip_runtime.h>
 
@@ -275,13 +275,12 @@ __global__ __launch_bounds__(BT) void k_dscatter(const uint64_t* __restrict__ ke
 // The set-up of an attempt in one launch: the outcome words cleared and the level-two triples
 // written (start), the cursor of fixed-capacity region i of either pass at i * cap (begin[i] keeps
 // that start), the one partition of an input without passes, and the fused final pass's look-back
-// words and ticket (nzw words) at zero.  A launch costs a small build more than its work does: these
+// words (nzw words) at zero.  A launch costs a small build more than its work does: these
 // were one to four of its four to seven.
 __global__ void k_attempt_init(AttemptStart start, unsigned long long* __restrict__ cur1, uint64_t* __restrict__ beg1,
                                uint64_t count1, uint64_t cap1, unsigned long long* __restrict__ cur2,
                                uint64_t* __restrict__ beg2, uint64_t count2, uint64_t cap2,
-                               uint64_t* __restrict__ one, uint64_t n, uint32_t* __restrict__ zw, uint64_t nzw,
-                               uint32_t* __restrict__ ticket) {
+                               uint64_t* __restrict__ one, uint64_t n, uint32_t* __restrict__ zw, uint64_t nzw) {
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count1 + count2 + nzw; i += stride) {
         if (i < count1) {
@@ -298,12 +297,9 @@ __global__ void k_attempt_init(AttemptStart start, unsigned long long* __restric
     if (blockIdx.x != 0) return;
     if (threadIdx.x < start.words) start.clear[threadIdx.x] = 0;
     for (uint32_t t = threadIdx.x; t < start.T; t += blockDim.x) start.C[t] = level2_triple(start.seed, start.r, t);
-    if (threadIdx.x == 0) {
-        if (ticket) *ticket = 0;
-        if (one) {
-            one[0] = 0;
-            one[1] = n;
-        }
+    if (threadIdx.x == 0 && one) {
+        one[0] = 0;
+        one[1] = n;
     }
 }
 
@@ -555,15 +551,13 @@ struct FinalLds {
     uint32_t flags[3];   // exhausted, dup, max_t
     uint64_t c0;         // fused form: the partition's first cell, from the look-back
     uint32_t sqtot;      // the partition's sum of squared sizes
-    uint32_t ticket;     // fused form: the partition this workgroup works on
     uint32_t over;       // fused form: a bucket above 15 keys
 };
 
-// look-back polls of one predecessor's word before the fused pass gives up (far beyond any
-// real wait: every predecessor publishes its sum without waiting on anything); without tickets
-// sooner, as the build then starts again with them: after some milliseconds, a thousand times
-// what a workgroup takes, where the second attempt costs a final pass and less than the wait
-constexpr uint32_t kSpinLimit = 1u << 24, kSpinLimitUnticketed = 1u << 13;
+// Polls of a predecessor's look-back word (about 0.1 ms) before its sum is taken from its records
+// instead (of the calling thread's builds).
+static thread_local uint32_t tl_patience = 128;
+void part_patience(uint32_t polls) { tl_patience = polls; }
 
 // The fused final pass (single map, level-two search in partition order): each partition
 // sizes its buckets itself, publishes its sum of squared sizes, and finds
@@ -572,18 +566,19 @@ constexpr uint32_t kSpinLimit = 1u << 24, kSpinLimitUnticketed = 1u << 13;
 // ends it).  state holds one word per partition: value << 2 | 1 (the partition's own sum)
 // or value << 2 | 2 (the inclusive prefix); zero means not yet published.
 //
-// A look-back ends only if the workgroups of the partitions before it run.  Workgroups are
-// dispatched in the order of their numbers, each XCD taking every eighth, so the lowest unfinished one
-// always runs and the partition is the workgroup's number.  Should that not hold, the look-back gives up and
-// the build runs again with tickets, which need no such order but are atomics on one word, at
+// A partition is its workgroup's number.  Workgroups are dispatched in the order of their numbers, so
+// with one such grid on the device the sums before a running workgroup's are there or on their way.
+// Two grids on two streams can keep each other's earlier workgroups off the CUs, each waiting for a
+// sum that cannot come; so a look-back that has polled a word long enough takes the sum from that
+// partition's records (which are all in place), and ends whether or not its workgroup ever runs.
+// Partitions from a ticket counter need no such order either, but are atomics on one word, at
 // 11.4 ns each: final pass of 10^7 keys 166 us with tickets, 141 without; 2^26 keys 939 and 874.
 struct FuseArgs {
     uint64_t* state;      // Q words, zero before the launch
-    uint32_t* ticket;     // zero before the launch; or null: no tickets
     uint64_t* S_out;      // the table's S, written by the last partition
     uint32_t* oversize;   // set when some bucket holds more than 15 keys
-    uint32_t* stalled;    // set when a look-back gave up
     uint32_t Q;
+    uint32_t patience;    // polls of a word before its sum is taken from the records (0: always so)
     const uint64_t* qend; // partition q's records are [offQ[q], min(qend[q], offQ[q] + qcap))
     uint64_t qcap;        // 0: no cap
     const uint32_t* parts;   // a batch: segment * kSegParts + partition within the map
@@ -685,16 +680,7 @@ __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(BT == kPB ? 
         ended();
         return;
     }
-    uint32_t q = blockIdx.x;
-    if (FUSED) {
-        // partitions go in ticket order: every partition a look-back below waits for was
-        // taken by a workgroup that is already running
-        if (fa.ticket) {
-            if (tid == 0) L.ticket = atomicAdd(fa.ticket, 1u);
-            __syncthreads();
-            q = L.ticket;
-        }
-    }
+    const uint32_t q = blockIdx.x;
     uint32_t qh = q;       // the partition's place among its map's partitions
     uint32_t q0 = 0;       // the map's first partition
     uint32_t seg = 0;
@@ -712,11 +698,14 @@ __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(BT == kPB ? 
         header += sg.hdr_off;
         slots += sg.slot_off;
         cap = (uint64_t)sg.c * sg.n;
-        fa.oversize = fa.stalled = ctrl_flags + 4 * seg;
+        fa.oversize = ctrl_flags + 4 * seg;
         ctrl_flags += 4 * seg + 1;
     }
-    const uint64_t k0 = MULTI ? q * fa.qcap : offQ[q];
-    const uint64_t k1 = !FUSED ? offQ[q + 1] : fa.qcap ? min(fa.qend[q], k0 + fa.qcap) : fa.qend[q];
+    auto begin_of = [&](uint32_t p) { return MULTI ? p * fa.qcap : offQ[p]; };
+    auto end_of = [&](uint32_t p, uint64_t from) {
+        return !FUSED ? offQ[p + 1] : fa.qcap ? min(fa.qend[p], from + fa.qcap) : fa.qend[p];
+    };
+    const uint64_t k0 = begin_of(q), k1 = end_of(q, k0);
     const uint32_t nq = (uint32_t)(k1 - k0);
     const bool keys_fit = nq <= kFinalKeyCap;
     // a partition whose cells would end beyond the cells allocated is skipped (the attempt
@@ -822,6 +811,25 @@ __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(BT == kPB ? 
     // not: the predecessors' sums, which each publishes as soon as it has sized its buckets, are there
     // to read, and the nearer an inclusive prefix is, the fewer rounds.  Final pass of 10^7 keys 139 us; before the cells'
     // indices are read 158, and 196 by a wave of its own while the others group the records.
+    // partition p's sum of squared sizes, as its own workgroup publishes it, counted by the first wave
+    // alone (the others wait for the look-back); cnt2 has been read by then
+    auto squares_of = [&](uint32_t p) {
+        for (uint32_t g = tid; g < kGroupsPerPart; g += 64) L.cnt2[g] = 0;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const uint64_t from = begin_of(p), to = end_of(p, from);
+        for (uint64_t i = from + tid; i < to; i += 64) {
+            const uint32_t lb = bucket_of(A, magic, (uint32_t)n, keys[i]) & (kPartBuckets - 1);
+            atomicAdd(&L.cnt2[lb >> 3], 1u << (4 * (lb & 7u)));
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        uint32_t sq = 0;
+        for (uint32_t g = tid; g < kGroupsPerPart; g += 64) sq += pos_cells(word_pos(L.cnt2[g]));
+        for (int d = 32; d >= 1; d >>= 1) sq += __shfl_xor(sq, d, 64);
+        __builtin_amdgcn_wave_barrier();
+        return sq;
+    };
     auto lookback = [&]() {
         if (tid < 64) {
             const uint32_t lane = tid;
@@ -831,19 +839,24 @@ __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(BT == kPB ? 
                 const int64_t idx = end - 1 - (int64_t)lane;
                 uint64_t v = 2;   // before the map's first partition: an inclusive prefix of 0
                 if (idx >= (int64_t)q0) {
-                    uint32_t spins = 0;
-                    for (;;) {
+                    v = 0;
+                    for (uint32_t polls = 0; polls < fa.patience; ++polls) {
                         v = __hip_atomic_load(&fa.state[idx], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         if (v & 3u) break;
-                        if (++spins > (fa.ticket ? kSpinLimit : kSpinLimitUnticketed)) {
-                            atomicOr(fa.stalled, 1u);
-                            v = 2;
-                            break;
-                        }
                         __builtin_amdgcn_s_sleep(1);
                     }
                 }
                 const uint64_t incl = __ballot((v & 3u) == 2u);
+                // sums that did not come, nearer than the nearest inclusive prefix
+                for (uint64_t miss = __ballot((v & 3u) == 0u) & ((incl & (0 - incl)) - 1); miss; miss &= miss - 1) {
+                    const uint32_t l = (uint32_t)__ffsll((long long)miss) - 1;
+                    const uint32_t sq = squares_of((uint32_t)(end - 1 - l));
+                    if (lane == l) {
+                        v = (uint64_t)sq << 2 | 1u;
+                        // for the other look-backs, unless the partition itself has published by now
+                        atomicCAS(reinterpret_cast<unsigned long long*>(&fa.state[idx]), 0ull, (unsigned long long)v);
+                    }
+                }
                 uint64_t take = v >> 2;
                 const bool last = incl != 0;
                 if (last && lane > (uint32_t)(__ffsll((long long)incl) - 1)) take = 0;
@@ -1314,7 +1327,7 @@ int part_prepare(const PartArgs& a, hipStream_t st, PartOut& o) {
         const uint64_t nzw = a.fused ? 2 * (uint64_t)P.Q : 0;
         hipLaunchKernelGGL(k_attempt_init, grid_for_count(std::max<uint64_t>(1, bins1 + parts + nzw)), 256, 0, st, a.start,
                            a.cur1, a.begA, bins1, P.cap1, a.cur2, a.begQ, parts, P.capQ, one ? a.offQ : nullptr, n,
-                           reinterpret_cast<uint32_t*>(a.cbase), nzw, a.fused ? a.sqQ : nullptr);
+                           reinterpret_cast<uint32_t*>(a.cbase), nzw);
         o.prezeroed = a.fused;
     };
     if (P.passes == 0) {
@@ -1463,14 +1476,12 @@ static void launch_fused(const PartArgs& a, PartOut& o, const Triple* C, uint32_
                          uint32_t* flags, const int64_t* ctx_off, const uint8_t* ctx_bytes, const uint32_t* reject,
                          uint64_t cap, hipStream_t st) {
     const uint32_t Q = o.plan.Q;
-    // the look-back words (in the cell-base scratch) and the ticket (in the partition-sum
-    // scratch) start at zero (the cursor passes' set-up has cleared them already)
-    if (!o.prezeroed) {
+    // the look-back words (in the cell-base scratch) start at zero (the cursor passes' set-up has
+    // cleared them already)
+    if (!o.prezeroed)
         hipLaunchKernelGGL(k_zero_words, (2 * Q + 255) / 256, 256, 0, st, reinterpret_cast<uint32_t*>(a.cbase),
                            (uint64_t)2 * Q);
-        if (a.ticketed) hipLaunchKernelGGL(k_zero_words, 1, 64, 0, st, a.sqQ, (uint64_t)1);
-    }
-    const FuseArgs fa{a.cbase, a.ticketed ? a.sqQ : nullptr, a.S_dev, a.oversize, a.stalled, Q, o.qend, o.qcap, nullptr,
+    const FuseArgs fa{a.cbase, a.S_dev, a.oversize, Q, tl_patience, o.qend, o.qcap, nullptr,
                       Q <= kReportParts ? a.outcome : nullptr, a.start.clear, a.start.words, a.done};
     auto launch = [&](auto kernel, uint32_t threads) {
         FKS_TIMED("fks_part_final", st,
@@ -1591,7 +1602,7 @@ int wide_build(const uint64_t* d_keys, const uint32_t* d_vals, const WideSeg* se
                                  kPScatterThreads, 0, st, d_keys, d_vals, nullptr, 0ull, A0, 0ull, nullptr, 1u, 0u,
                                  kSegParts - 1, nullptr, w.keys, w.vals, nullptr, segs, w.tiles, w.cursor, nullptr, cap,
                                  flags, 0ull));
-    const FuseArgs fa{w.state, nullptr, w.S, nullptr, nullptr, (uint32_t)parts, (const uint64_t*)w.cursor, cap, w.parts,
+    const FuseArgs fa{w.state, w.S, nullptr, (uint32_t)parts, tl_patience, (const uint64_t*)w.cursor, cap, w.parts,
                       nullptr, nullptr, 0, nullptr};
     FKS_TIMED("fks_wide_final", st,
               hipLaunchKernelGGL((k_pfinal<false, false, true, true>), (unsigned)parts, kPB, 0, st, w.keys, w.vals,

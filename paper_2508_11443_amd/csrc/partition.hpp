@@ -98,8 +98,6 @@ struct PartArgs {
     uint32_t* sizes;            // G size words (the headers' second word)
     uint64_t* S_dev;            // total cells
     uint32_t* oversize;         // a bucket above 15 keys
-    uint32_t* stalled;          // fused final pass: a look-back gave up
-    bool ticketed;              // fused final pass: partitions go in ticket order
     uint32_t* outcome;          // pinned: where the host reads start.clear's words, or null
     uint32_t* done;             // one of those words, counting the final pass's workgroups
     bool fused;                 // the final pass sizes the partitions itself (no size pass and scan)
@@ -123,7 +121,7 @@ struct PartOut {
     const uint64_t* qend;
     uint64_t qcap;              // 0: no cap (counted passes)
     bool reported;              // the final pass writes the outcome to the host itself
-    bool prezeroed;             // the fused pass's look-back words and ticket are already zero
+    bool prezeroed;             // the fused pass's look-back words are already zero
 };
 
 // Exclusive prefix sum of N u32 counts whose total is below 2^32 (three launches):
@@ -141,8 +139,7 @@ size_t part_scratch(const PartPlan& plan, uint64_t n, bool carry, bool cursor, b
 // The partition passes over the wide maps of a batch (attempt 0 of each).  Inputs:
 // d_keys/d_vals (the batch input), segs (nseg device descriptors), pools; Cpool receives the maps'
 // level-two triples (T per map, at index map*T).  Per-map outcome words flags[4*seg + 0..3]: nonzero
-// word 0 = attempt rejected (a bucket over 15 keys, more than c*n cells, an overflowing region or a
-// stalled look-back), word 1 = a bucket exhausted its trials, word 2 = that bucket holds equal
+// word 0 = attempt rejected (a bucket over 15 keys, more than c*n cells or an overflowing region), word 1 = a bucket exhausted its trials, word 2 = that bucket holds equal
 // keys, word 3 = max trial.  *S points into the scratch, to every map's cells.
 uint32_t wide_tiles(uint32_t n);      // scatter tiles of a map of n keys
 uint64_t wide_parts_max();            // most partitions of a call
@@ -151,6 +148,9 @@ int wide_build(const uint64_t* d_keys, const uint32_t* d_vals, const WideSeg* se
                uint64_t tiles, Triple* Cpool, uint32_t T, Group* hdr_pool, Cell* slot_pool, uint32_t* flags,
                uint64_t** S, void* scratch, hipStream_t st);
 uint64_t part_scan_tiles(const PartPlan& P);
+// Polls of a predecessor's look-back word before the fused pass takes that sum from the records, for
+// the calling thread's builds (0: at once; the table is the same).
+void part_patience(uint32_t polls);
 int part_prepare(const PartArgs& a, hipStream_t st, PartOut& o);
 // given_t: trial index of every bucket decided elsewhere (n bytes), or nullptr to search.
 // reject: two device words (a bucket above 15 keys, bad string offsets); when either is set
