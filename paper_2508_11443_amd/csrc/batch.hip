@@ -580,18 +580,20 @@ __global__ __launch_bounds__(kOrdBlock) void k_ord_batch(const LDesc* __restrict
                                                        const Triple* __restrict__ Cpool, uint32_t M, OrdArgs o,
                                                        uint32_t missing) {
     __shared__ OrdRuns R;
+    if (ord_idle(o)) return;   // the whole block
     uint32_t part;
-    const uint32_t total = ord_runs(o, R, part);
+    OrdSide side;
+    const uint32_t total = ord_runs(o, R, side, part);
     constexpr uint32_t Q = 2;
-    for (uint32_t i0 = 0; i0 < total; i0 += kOrdBlock * Q) {
+    for (uint32_t i0 = side.begin; i0 < total; i0 += kOrdBlock * Q) {
         uint64_t x[Q], at[Q];
         uint32_t id[Q];
 #pragma unroll
         for (uint32_t k = 0; k < Q; ++k) {
             const uint32_t i = i0 + threadIdx.x + k * kOrdBlock;
             at[k] = i < total ? ord_place(R, i) : 0;
-            x[k] = i < total ? __builtin_nontemporal_load(o.x + at[k]) : 0;
-            id[k] = i < total ? __builtin_nontemporal_load(o.id + at[k]) : 0xFFFFFFFFu;
+            x[k] = i < total ? __builtin_nontemporal_load(side.x + at[k]) : 0;
+            id[k] = i < total ? __builtin_nontemporal_load(side.id + at[k]) : 0xFFFFFFFFu;
         }
         LDesc d[Q];
         Group h[Q];
@@ -619,8 +621,8 @@ __global__ __launch_bounds__(kOrdBlock) void k_ord_batch(const LDesc* __restrict
         for (uint32_t k = 0; k < Q; ++k) {
             if (i0 + threadIdx.x + k * kOrdBlock < total) {
                 const bool hit = c[k].key == x[k];
-                if (o.val) ((uint32_t*)o.val)[at[k]] = hit ? c[k].val : missing;
-                if (o.found) o.found[at[k]] = hit ? 1 : 0;
+                if (side.val) ((uint32_t*)side.val)[at[k]] = hit ? c[k].val : missing;
+                if (side.found) side.found[at[k]] = hit ? 1 : 0;
             }
         }
     }
@@ -1012,12 +1014,13 @@ static bool ordered_batch(const fks_batch* B, const uint32_t* ids, const uint64_
     hipLaunchKernelGGL(k_batch_parts, std::min(1024u, (B->M + 255) / 256), 256, 0, st, B->ldesc, B->M, B->total_groups,
                        bins, (uint8_t*)s.more());
     for (uint64_t at = 0; at < m; at += slice) {
-        const OrdArgs a = s.part(std::min(slice, m - at));
-        ord_group<BatchPart, true>(part, q + at, ids + at, a, st);
+        const OrdArgs a = s.part(std::min(slice, m - at), q + at, ids + at, vals ? vals + at : nullptr,
+                                 found ? found + at : nullptr);
+        ord_group<BatchPart, true>(part, a, st);
         FKS_TIMED("fks_order_batch", st,
                   hipLaunchKernelGGL(k_ord_batch, ord_grid(a), kOrdBlock, 0, st, B->ldesc, B->hdr_pool, B->slot_pool,
                                      B->Cpool, B->M, a, missing));
-        ord_return<uint32_t, true>(a, vals ? vals + at : nullptr, found ? found + at : nullptr, st);
+        ord_return<uint32_t, true>(a, st);
     }
     return true;
 }

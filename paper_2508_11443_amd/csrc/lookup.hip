@@ -112,7 +112,7 @@ OrdScratch::OrdScratch(uint64_t m, uint32_t bins, bool ids, uint32_t val_bytes, 
         return at;
     };
     const size_t x = carve(8 * m), id = carve(ids ? 4 * m : 0), slot = carve(2 * m),
-                 start = carve(2 * tiles * (bins + 1)), val = carve((size_t)val_bytes * m),
+                 start = carve(2 * tiles * (bins + 2)), val = carve((size_t)val_bytes * m),
                  fnd = carve(found ? m : 0), own = carve(more);
     base_ = pool_take(total, s);
     if (!base_) return;
@@ -167,11 +167,13 @@ __global__ __launch_bounds__(kOrdBlock) void k_ord_lookup(const Group* __restric
                                                         OrdArgs o, uint64_t missing) {
     __shared__ Triple C[kTMax];
     __shared__ OrdRuns R;
+    if (ord_idle(o)) return;   // the whole block
     for (uint32_t t = threadIdx.x; t < T; t += kOrdBlock) C[t] = Cg[t];
     uint32_t part;
-    const uint32_t total = ord_runs(o, R, part);
+    OrdSide side;
+    const uint32_t total = ord_runs(o, R, side, part);
     constexpr uint32_t Q = 2;
-    for (uint32_t i0 = 0; i0 < total; i0 += kOrdBlock * Q) {
+    for (uint32_t i0 = side.begin; i0 < total; i0 += kOrdBlock * Q) {
         uint64_t x[Q], at[Q];
         Group h[Q];
         uint32_t kk[Q];
@@ -179,7 +181,7 @@ __global__ __launch_bounds__(kOrdBlock) void k_ord_lookup(const Group* __restric
         for (uint32_t k = 0; k < Q; ++k) {
             const uint32_t i = i0 + threadIdx.x + k * kOrdBlock;
             at[k] = i < total ? ord_place(R, i) : 0;
-            x[k] = i < total ? __builtin_nontemporal_load(o.x + at[k]) : 0;
+            x[k] = i < total ? __builtin_nontemporal_load(side.x + at[k]) : 0;
         }
 #pragma unroll
         for (uint32_t k = 0; k < Q; ++k) {
@@ -199,11 +201,11 @@ __global__ __launch_bounds__(kOrdBlock) void k_ord_lookup(const Group* __restric
             if (i0 + threadIdx.x + k * kOrdBlock < total) {
                 const bool hit = c[k].key == x[k];
                 if (V64) {
-                    if (o.val) ((uint64_t*)o.val)[at[k]] = hit ? ((uint64_t)c[k].aux << 32) | c[k].val : missing;
+                    if (side.val) ((uint64_t*)side.val)[at[k]] = hit ? ((uint64_t)c[k].aux << 32) | c[k].val : missing;
                 } else {
-                    if (o.val) ((uint32_t*)o.val)[at[k]] = hit ? c[k].val : (uint32_t)missing;
+                    if (side.val) ((uint32_t*)side.val)[at[k]] = hit ? c[k].val : (uint32_t)missing;
                 }
-                if (o.found) o.found[at[k]] = hit ? 1 : 0;
+                if (side.found) side.found[at[k]] = hit ? 1 : 0;
             }
         }
     }
@@ -221,12 +223,13 @@ static bool ordered_lookup(const fks_map* map, const uint64_t* q, uint64_t m, V*
     if (!s) return false;
     const BucketPart part{map->A, map->magic_n, n, (uint32_t)(((uint64_t)bins << 32) / n)};
     for (uint64_t at = 0; at < m; at += slice) {
-        const OrdArgs a = s.part(std::min(slice, m - at));
-        ord_group<BucketPart, false>(part, q + at, nullptr, a, st);
+        const OrdArgs a = s.part(std::min(slice, m - at), q + at, nullptr, vals ? vals + at : nullptr,
+                                 found ? found + at : nullptr);
+        ord_group<BucketPart, false>(part, a, st);
         FKS_TIMED("fks_order_lookup", st,
                   hipLaunchKernelGGL(k_ord_lookup<V64>, ord_grid(a), kOrdBlock, 0, st, map->header, map->slots, map->A,
                                      map->magic_n, n, map->C, map->T, a, (uint64_t)missing));
-        ord_return<V, false>(a, vals ? vals + at : nullptr, found ? found + at : nullptr, st);
+        ord_return<V, false>(a, st);
     }
     return true;
 }

@@ -15,6 +15,16 @@
 // (264 us, 1.60 ms).  Part w mod 8 on each XCD rather than a stretch of neighbours: parts differ
 // in needles where keys are clustered, and neighbours alike (a sorted map 632 us instead of 516).
 // Reading the next part's lines ahead of their use changed nothing (253 us) or lost (1.74 ms).
+//
+// Needles that crowd few parts (a key asked again and again, one map of a batch) would leave the
+// work to the few workgroups of those parts, on one XCD each, though their lines stay in every L2.  So a
+// part's workgroup leaves out runs of more than a kOrdCrowd-th of a tile (twenty times a part's share of
+// evenly spread needles), and workgroups of the tile's own answer them, on any XCD.  A tile with more than
+// half of its needles in such runs is not grouped at all: its workgroups answer it in the caller's order.
+// 10^7 needles over as many keys, one key asked by all of them 701 us and so 95 (41 without grouping), by a
+// tenth 253 and 235 (317); a sorted map's 3157 and 272 (137), 426 and 325 (1880); 2^24 needles of a batch
+// of 64 maps that all ask one map 2018 and 292 (371), four maps evenly 732 and 366 (434).  The tiles'
+// workgroups, idle for evenly spread needles, cost those up to 1 %.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -31,6 +41,11 @@ constexpr uint32_t kOrdItems = 15;          // needles per thread of a tile: 8 b
 constexpr uint32_t kOrdItemsIds = 12;       // ... or 12 with a map id
 constexpr uint32_t kOrdRunTiles = 32;        // tiles whose runs of one part a workgroup answers
 constexpr uint32_t kOrdBlock = 1024;        // its threads
+constexpr uint32_t kOrdCrowd = 12;
+constexpr uint32_t kOrdTileBlocks = 2;      // workgroups for a tile's crowded runs ...
+constexpr uint32_t kOrdTileShare = 2048;    // ... where they are longer than this
+// what a tile leaves to them
+enum OrdState : uint16_t { kOrdEven, kOrdCrowded, kOrdDirect };
 
 // Device arrays of one call (m needles in `tiles` tiles of `tile`, the last one short).
 struct OrdArgs {
@@ -39,10 +54,24 @@ struct OrdArgs {
     uint64_t* x;        // needles, every tile grouped by part
     uint32_t* id;       // their map ids (batches)
     uint16_t* slot;     // the place in its tile of every needle of the caller's order
-    uint16_t* start;    // tiles x (bins + 1): where a part's run starts in its tile
+    uint16_t* start;    // tiles x (bins + 2): where a part's run starts in its tile; its end; OrdState
     void* val;          // answers at the needles' places
     uint8_t* found;
+    // the caller's arrays
+    const uint64_t* q;
+    const uint32_t* ids;
+    void* vals_out;
+    uint8_t* found_out;
 };
+
+__host__ __device__ inline uint32_t ord_crowd(const OrdArgs& o) { return o.tile / kOrdCrowd; }   // longest run of an even tile
+// (the same for all lanes, and kept so: what depends on it stays in scalar registers)
+__device__ __forceinline__ uint32_t ord_state(const OrdArgs& o, uint32_t tile) {
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)o.start[(uint64_t)tile * (o.bins + 2) + o.bins + 1]);
+}
+__device__ __forceinline__ uint16_t* ord_row(const OrdArgs& o, uint32_t tile) {
+    return o.start + (uint64_t)tile * (o.bins + 2);
+}
 
 // exclusive scan of one value per thread over the block's first kOrdBins threads
 __device__ __forceinline__ uint32_t ord_exscan(uint32_t v, uint32_t* wsum) {
@@ -63,13 +92,14 @@ __device__ __forceinline__ uint32_t ord_exscan(uint32_t v, uint32_t* wsum) {
 
 // One tile of needles grouped by part.  Part: setup(lds) once (512 words of LDS), then of(lds, x, id).
 template <typename Part, bool IDS>
-__global__ __launch_bounds__(kOrdThreads) void k_ord_group(Part part, const uint64_t* __restrict__ q,
-                                                          const uint32_t* __restrict__ ids, OrdArgs o) {
+__global__ __launch_bounds__(kOrdThreads) void k_ord_group(Part part, OrdArgs o) {
     constexpr uint32_t ITEMS = IDS ? kOrdItemsIds : kOrdItems, TILE = kOrdThreads * ITEMS;
     __shared__ uint64_t sx[TILE];
     __shared__ uint32_t sid[IDS ? TILE : 1];
-    __shared__ uint32_t cnt[kOrdBins], at[kOrdBins], wsum[kOrdBins / 64];
+    __shared__ uint32_t cnt[kOrdBins], at[kOrdBins], wsum[kOrdBins / 64], crowded;   // crowded: needles in long runs
     __shared__ uint64_t own[Part::kLds ? Part::kLds : 1];
+    const uint64_t* const __restrict__ q = o.q;
+    const uint32_t* const __restrict__ ids = o.ids;
     const uint32_t tid = threadIdx.x;
     const uint64_t base = (uint64_t)blockIdx.x * o.tile;
     const uint32_t count = (uint32_t)min((uint64_t)o.tile, o.m - base);   // at most TILE
@@ -83,6 +113,7 @@ __global__ __launch_bounds__(kOrdThreads) void k_ord_group(Part part, const uint
     }
     part.setup(own);
     if (tid < kOrdBins) cnt[tid] = 0;
+    if (tid == 0) crowded = 0;
     __syncthreads();
     uint32_t bin[ITEMS], rank[ITEMS];
 #pragma unroll
@@ -105,11 +136,18 @@ __global__ __launch_bounds__(kOrdThreads) void k_ord_group(Part part, const uint
         }
     }
     __syncthreads();
+    bool direct;
     {
-        const uint32_t e = ord_exscan(tid < kOrdBins ? cnt[tid] : 0u, wsum);
+        const uint32_t c = tid < kOrdBins ? cnt[tid] : 0u;
+        if (c > ord_crowd(o)) atomicAdd(&crowded, c);
+        const uint32_t e = ord_exscan(c, wsum);   // with a barrier
         if (tid < kOrdBins) at[tid] = e;
-        if (tid <= o.bins) o.start[(uint64_t)blockIdx.x * (o.bins + 1) + tid] = (uint16_t)(tid < o.bins ? e : count);
+        direct = 2 * crowded > count;
+        uint16_t* const row = ord_row(o, blockIdx.x);
+        if (tid <= o.bins) row[tid] = (uint16_t)(direct ? 0u : tid < o.bins ? e : count);
+        if (tid == 0) row[o.bins + 1] = direct ? kOrdDirect : crowded ? kOrdCrowded : kOrdEven;
     }
+    if (direct) return;   // the whole block
     __syncthreads();
 #pragma unroll
     for (uint32_t k = 0; k < ITEMS; ++k) {
@@ -132,28 +170,84 @@ __global__ __launch_bounds__(kOrdThreads) void k_ord_group(Part part, const uint
     }
 }
 
-// The runs of one part in kOrdRunTiles consecutive tiles, as one sequence.  Workgroups are dealt
-// to the eight XCDs in turn, so workgroup w answers a part of number w mod 8 (mod 8).
+// What a workgroup answers, as one sequence: the runs of one part in kOrdRunTiles consecutive tiles, or
+// the crowded runs of one tile, or all of a tile in the caller's order.
 struct OrdRuns {
     uint32_t pre[kOrdRunTiles + 1];
     uint64_t src[kOrdRunTiles];
 };
+static_assert(kOrdCrowd <= kOrdRunTiles, "the crowded runs of a tile are such a sequence");
+// where the needles of the sequence are, and their answers go
+struct OrdSide {
+    const uint64_t* x;
+    const uint32_t* id;
+    void* val;
+    uint8_t* found;
+    uint32_t begin;   // where in the sequence the workgroup starts
+    bool all_parts;   // the sequence may belong to any part
+};
 __host__ __device__ inline uint32_t ord_chunks(uint32_t tiles) { return (tiles + kOrdRunTiles - 1) / kOrdRunTiles; }
+__host__ __device__ inline uint32_t ord_grouped(const OrdArgs& o) { return ((o.bins + 7) / 8) * 8 * ord_chunks(o.tiles); }
 // workgroups of the answering kernel
-inline unsigned ord_grid(const OrdArgs& o) { return ((o.bins + 7) / 8) * 8 * ord_chunks(o.tiles); }
-// the part of this workgroup; its runs in R, their total length returned (after a barrier)
-__device__ __forceinline__ uint32_t ord_runs(const OrdArgs& o, OrdRuns& R, uint32_t& part) {
-    const uint32_t chunks = ord_chunks(o.tiles), g = blockIdx.x >> 3;
-    part = (g / chunks) * 8 + (blockIdx.x & 7u);
-    if (threadIdx.x < 64) {
-        const uint32_t t = threadIdx.x, tile = (g % chunks) * kOrdRunTiles + t;
-        uint32_t len = 0;
-        uint64_t at = 0;
+inline unsigned ord_grid(const OrdArgs& o) { return ord_grouped(o) + o.tiles * kOrdTileBlocks; }
+// a tile's workgroup with nothing to do (asked before anything else, as most of them are)
+__device__ __forceinline__ bool ord_idle(const OrdArgs& o) {
+    const uint32_t grouped = ord_grouped(o);
+    return blockIdx.x >= grouped && ord_state(o, (blockIdx.x - grouped) % o.tiles) == kOrdEven;
+}
+// this workgroup's sequence in R (and its part), from side.begin up to the end that is returned (after a
+// barrier); not of an idle one
+__device__ __forceinline__ uint32_t ord_runs(const OrdArgs& o, OrdRuns& R, OrdSide& side, uint32_t& part) {
+    const uint32_t grouped = ord_grouped(o), crowd = ord_crowd(o), t = threadIdx.x;
+    uint32_t len = 0;
+    uint64_t at = 0;
+    const bool own = blockIdx.x >= grouped;   // a tile's
+    const uint32_t tile_of = own ? (blockIdx.x - grouped) % o.tiles : 0;
+    const bool direct = own && ord_state(o, tile_of) == kOrdDirect;
+    side = OrdSide{direct ? o.q : o.x, direct ? o.ids : o.id, direct ? o.vals_out : o.val,
+                   direct ? o.found_out : o.found, 0, own};
+    if (!own) {
+        // workgroups are dealt to the eight XCDs in turn: all of a part on one of them, the parts of eight
+        // in an order that changes, so that parts a constant distance apart do not meet on one
+        const uint32_t chunks = ord_chunks(o.tiles), g = blockIdx.x >> 3, eight = g / chunks;
+        part = eight * 8 + ((blockIdx.x + eight + (eight >> 3)) & 7u);
+        const uint32_t tile = (g % chunks) * kOrdRunTiles + t;
         if (t < kOrdRunTiles && tile < o.tiles && part < o.bins) {
-            const uint16_t* s = o.start + (uint64_t)tile * (o.bins + 1) + part;
-            at = (uint64_t)tile * o.tile + s[0];
-            len = (uint32_t)s[1] - s[0];
+            const uint16_t* const row = ord_row(o, tile);
+            at = (uint64_t)tile * o.tile + row[part];
+            len = (uint32_t)row[part + 1] - row[part];
+            if (len > crowd) len = 0;
         }
+    } else {
+        const uint16_t* const row = ord_row(o, tile_of);
+        const uint64_t base = (uint64_t)tile_of * o.tile;
+        part = 0;
+        if (direct) {
+            at = base;
+            len = t == 0 ? (uint32_t)min((uint64_t)o.tile, o.m - base) : 0u;
+        } else if (t < 64) {
+            uint32_t k = 0;
+            for (uint32_t p0 = 0; p0 < o.bins; p0 += 64) {
+                const uint32_t p = p0 + t, s = p < o.bins ? row[p] : 0u, l = p < o.bins ? row[p + 1] - s : 0u;
+                const uint64_t long_runs = __ballot(l > crowd);
+                if (l > crowd) {
+                    const uint32_t e = k + (uint32_t)__popcll(long_runs & ((1ull << t) - 1));
+                    R.pre[e] = l;
+                    R.src[e] = base + s;
+                }
+                k += (uint32_t)__popcll(long_runs);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            if (t < k) {
+                len = R.pre[t];
+                at = R.src[t];
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+    if (t < 64) {
         uint32_t inc = len;
 #pragma unroll
         for (int d = 1; d < (int)kOrdRunTiles; d <<= 1) {
@@ -167,7 +261,11 @@ __device__ __forceinline__ uint32_t ord_runs(const OrdArgs& o, OrdRuns& R, uint3
         if (t == 0) R.pre[0] = 0;
     }
     __syncthreads();
-    return R.pre[kOrdRunTiles];
+    const uint32_t all = (uint32_t)__builtin_amdgcn_readfirstlane((int)R.pre[kOrdRunTiles]);
+    if (!own) return all;
+    const uint32_t share = max(kOrdTileShare, (all + kOrdTileBlocks - 1) / kOrdTileBlocks);
+    side.begin = min(all, (blockIdx.x - grouped) / o.tiles * share);
+    return min(all, side.begin + share);
 }
 // the place of needle i of the sequence
 __device__ __forceinline__ uint64_t ord_place(const OrdRuns& R, uint32_t i) {
@@ -185,8 +283,10 @@ template <typename T>
 using OrdVec4 = T __attribute__((ext_vector_type(4)));
 
 template <typename V, uint32_t TILE>
-__global__ __launch_bounds__(kOrdThreads) void k_ord_return(OrdArgs o, V* __restrict__ vals,
-                                                           uint8_t* __restrict__ found) {
+__global__ __launch_bounds__(kOrdThreads) void k_ord_return(OrdArgs o) {
+    if (ord_state(o, blockIdx.x) == kOrdDirect) return;   // the whole block
+    V* const __restrict__ vals = (V*)o.vals_out;
+    uint8_t* const __restrict__ found = o.found_out;
     constexpr uint32_t ITEMS = (TILE / 4 + kOrdThreads - 1) / kOrdThreads;
     __shared__ __attribute__((aligned(16))) V sv[TILE];
     __shared__ __attribute__((aligned(16))) uint8_t sf[TILE];
@@ -281,11 +381,16 @@ class OrdScratch {
     OrdScratch(const OrdScratch&) = delete;
     OrdScratch& operator=(const OrdScratch&) = delete;
     explicit operator bool() const { return base_ != nullptr; }
-    // for a slice of m needles
-    OrdArgs part(uint64_t m) const {
+    // for a slice of m needles; vals, found may be null
+    template <typename V>
+    OrdArgs part(uint64_t m, const uint64_t* q, const uint32_t* ids, V* vals, uint8_t* found) const {
         OrdArgs a = a_;
         a.m = m;
         a.tiles = (uint32_t)((m + a.tile - 1) / a.tile);
+        a.q = q;
+        a.ids = ids;
+        a.vals_out = vals;
+        a.found_out = found;
         return a;
     }
 
@@ -299,14 +404,14 @@ class OrdScratch {
 uint32_t ord_parts(uint64_t m, uint64_t table_bytes);
 
 template <typename Part, bool IDS>
-void ord_group(const Part& part, const uint64_t* q, const uint32_t* ids, const OrdArgs& a, hipStream_t st) {
+void ord_group(const Part& part, const OrdArgs& a, hipStream_t st) {
     FKS_TIMED("fks_order_group", st,
-              hipLaunchKernelGGL((k_ord_group<Part, IDS>), a.tiles, kOrdThreads, 0, st, part, q, ids, a));
+              hipLaunchKernelGGL((k_ord_group<Part, IDS>), a.tiles, kOrdThreads, 0, st, part, a));
 }
 template <typename V, bool IDS>
-void ord_return(const OrdArgs& a, V* vals, uint8_t* found, hipStream_t st) {
+void ord_return(const OrdArgs& a, hipStream_t st) {
     FKS_TIMED("fks_order_return", st,
-              hipLaunchKernelGGL((k_ord_return<V, ord_tile_max(IDS)>), a.tiles, kOrdThreads, 0, st, a, vals, found));
+              hipLaunchKernelGGL((k_ord_return<V, ord_tile_max(IDS)>), a.tiles, kOrdThreads, 0, st, a));
 }
 
 }  // namespace fks

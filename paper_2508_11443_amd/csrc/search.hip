@@ -405,24 +405,33 @@ __global__ __launch_bounds__(kSepBlock) void k_ord_sep(const uint64_t* __restric
                                                      const uint32_t* __restrict__ vals, uint64_t n,
                                                      const uint64_t* __restrict__ index, SepIndex sep, uint32_t level,
                                                      OrdArgs o, uint32_t missing) {
-    __shared__ uint64_t cut[kStretch];
+    __shared__ uint64_t cut[kTopSeps + 1];   // at most kStretch of them for a part
     __shared__ OrdRuns R;
+    if (ord_idle(o)) return;   // the whole block
     uint32_t part;
-    const uint32_t total = ord_runs(o, R, part);
-    if (total == 0) return;   // the whole block
+    OrdSide side;
+    const uint32_t total = ord_runs(o, R, side, part);
+    if (side.begin == total) return;   // the whole block
     const uint32_t ntop = (uint32_t)sep.count[sep.levels], up = 4 * (sep.levels - level);
-    const uint32_t c0 = part_start(part, ntop, o.bins) << up;
-    const uint32_t c1 = (uint32_t)min((uint64_t)part_start(part + 1, ntop, o.bins) << up, sep.count[level] + 1) - 1;
-    uint32_t step0 = 1;   // smallest power of two above the stretch's length, at most kStretch
+    // the part's stretch of `level`, or all of the top level for needles of any part
+    uint32_t c0 = part_start(part, ntop, o.bins) << up;
+    uint32_t c1 = (uint32_t)min((uint64_t)part_start(part + 1, ntop, o.bins) << up, sep.count[level] + 1) - 1;
+    if (side.all_parts) {
+        level = sep.levels;
+        c0 = 0;
+        c1 = ntop;
+    }
+    uint32_t step0 = 1;   // smallest power of two above the stretch's length
     while (step0 <= c1 - c0) step0 <<= 1;
     for (uint32_t i = threadIdx.x; i < step0; i += kSepBlock)
         cut[i] = i < c1 - c0 ? index[sep.at[level] + c0 + i] : ~0ull;
     __syncthreads();
     const uint32_t g8 = threadIdx.x & 56u;
-    for (uint32_t i0 = threadIdx.x & ~63u; i0 < total; i0 += kSepBlock) {   // the same for all lanes of a wave
+    // the same for all lanes of a wave
+    for (uint32_t i0 = side.begin + (threadIdx.x & ~63u); i0 < total; i0 += kSepBlock) {
         const uint32_t mine = i0 + (threadIdx.x & 63u);
         const uint64_t place = mine < total ? ord_place(R, mine) : 0;
-        const uint64_t xm = mine < total ? o.x[place] : 0;
+        const uint64_t xm = mine < total ? side.x[place] : 0;
         uint64_t x[8];
 #pragma unroll
         for (uint32_t s = 0; s < 8; ++s) x[s] = (uint64_t)__shfl((unsigned long long)xm, (int)(g8 + s), 64);
@@ -431,8 +440,8 @@ __global__ __launch_bounds__(kSepBlock) void k_ord_sep(const uint64_t* __restric
         uint64_t at;
         const bool hit = sep_descend<EYTZ>(keys, n, index, sep, level, xm, c0 + jm, x, at);
         if (mine < total) {
-            if (o.val) ((uint32_t*)o.val)[place] = hit ? vals[at] : missing;
-            o.found[place] = (uint8_t)hit;
+            if (side.val) ((uint32_t*)side.val)[place] = hit ? vals[at] : missing;
+            side.found[place] = (uint8_t)hit;
         }
     }
 }
@@ -485,8 +494,8 @@ static bool ordered_search(const fks_sorted* S, const uint64_t* q, uint64_t m, u
     uint32_t level = S->sep.levels;
     while (level > 1 && ((ntop + bins) / bins << 4 * (S->sep.levels - level + 1)) <= kStretch) --level;
     for (uint64_t at = 0; at < m; at += slice) {
-        const OrdArgs a = s.part(std::min(slice, m - at));
-        ord_group<SepPart, false>(part, q + at, nullptr, a, st);
+        const OrdArgs a = s.part(std::min(slice, m - at), q + at, nullptr, vals ? vals + at : nullptr, found + at);
+        ord_group<SepPart, false>(part, a, st);
         auto launch = [&](auto kernel) {
             FKS_TIMED("fks_order_search", st,
                       hipLaunchKernelGGL(kernel, ord_grid(a), kSepBlock, 0, st, S->keys, S->vals, S->n, S->index,
@@ -494,7 +503,7 @@ static bool ordered_search(const fks_sorted* S, const uint64_t* q, uint64_t m, u
         };
         if (S->layout == 1) launch(k_ord_sep<true>);
         else launch(k_ord_sep<false>);
-        ord_return<uint32_t, false>(a, vals ? vals + at : nullptr, found + at, st);
+        ord_return<uint32_t, false>(a, st);
     }
     return true;
 }
