@@ -24,13 +24,19 @@
  *     once per level-one attempt, to read its outcome (twice when the table
  *     needs more cells than the build allocates first, or under
  *     params.schedule = 1, which reads the table size before its search).
- *     Without an allocator that first allocation is 4n cells, up to 8 GiB, and
- *     what the table leaves of it is given back; a map, and a build's scratch,
- *     then come from a pool of the library's own, which keeps at most an
- *     eighth of the device's memory free for the next call.
+ *     Without an allocator a map, and a build's scratch, come from a pool of
+ *     the library's own.  It keeps at most an eighth of the device's memory
+ *     free for the next calls, and gives the rest back to the driver when a
+ *     build or a release call leaves more.  That first allocation is then 4n
+ *     cells, up to 8 GiB, and what the table leaves of it is given back; it
+ *     stays beside the table, for scratch alone, until the map is released, so
+ *     only as long as such ends hold no more than a 64th of the device's memory
+ *     is it more than the table is likely to need.
  *     Lookups are fully asynchronous.  Those of 2^22 and more needles may take
  *     15 to 20 bytes per needle from that pool until the stream is done with
- *     them; where it has none, under capture, and on maps built with an
+ *     them; the pool may ask the driver for that memory, as a call to
+ *     hipMalloc does, but waits for no work on the device and gives nothing back
+ *     meanwhile.  Where there is none, under capture, and on maps built with an
  *     allocator they take nothing.
  *   - Return value 0 (FKS_OK) is success; negative values are the FKS_E*
  *     codes below.  Out-parameters are written only on success.

@@ -827,11 +827,11 @@ extern "C" int fks_build_batch_u64(const uint64_t* d_keys, const uint32_t* d_val
     }
     const uint32_t nseg = (uint32_t)segs.size();
     const size_t staging = std::max<size_t>(16 * total, wide_scratch_bytes(nseg, parts, tiles));
-    B->bdesc = (BDesc*)dev_alloc(sizeof(BDesc) * M, st);
-    B->ldesc = (LDesc*)dev_alloc(sizeof(LDesc) * M, st);
-    B->Cpool = (Triple*)dev_alloc(sizeof(Triple) * (uint64_t)M * P.T, st);
-    B->hdr_pool = (Group*)dev_alloc(16 * (groups ? groups : 1), st);
-    B->slot_pool = (Cell*)dev_alloc(16 * (B->pool_cells ? B->pool_cells : 1), st);
+    B->bdesc = (BDesc*)dev_alloc(sizeof(BDesc) * M, st, kKept);
+    B->ldesc = (LDesc*)dev_alloc(sizeof(LDesc) * M, st, kKept);
+    B->Cpool = (Triple*)dev_alloc(sizeof(Triple) * (uint64_t)M * P.T, st, kKept);
+    B->hdr_pool = (Group*)dev_alloc(16 * (groups ? groups : 1), st, kKept);
+    B->slot_pool = (Cell*)dev_alloc(16 * (B->pool_cells ? B->pool_cells : 1), st, kKept);
     uint32_t* d_order = (uint32_t*)dev_alloc(4 * M + 256, st);
     uint32_t* d_queue = d_order ? d_order + M + (64 - (M % 64)) % 64 : nullptr;   // own cache line
     uint8_t* rank_s = (uint8_t*)dev_alloc(total ? total : 1, st);

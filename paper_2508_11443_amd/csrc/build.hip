@@ -223,7 +223,8 @@ static int check_params(uint64_t n, const fks_params* p, fks_params& out) {
 // S was 1.75n to 3.2n over 60 hashes and above it for 11 of them, and the second final pass
 // takes 0.93 ms of the 3.5 ms of 2^26 keys' build and lookup.  So 4n cells are taken from the library's
 // own pool, and what S leaves goes back once the host knows it; up to kRoomyCells, so that
-// what a build needs for a moment stays a small part of the device's memory.
+// what a build needs for a moment stays a small part of the device's memory, and as long as the pool
+// has room: an end given back stays beside its table, of use to scratch alone.
 constexpr uint64_t kRoomyCells = 1ull << 29;   // 8 GiB
 static uint64_t cells_guess(uint64_t n, uint32_t c) {
     const uint64_t g = 2 * n + (uint64_t)(8.0 * std::sqrt(11.0 * (double)n)) + 64;
@@ -297,13 +298,13 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
     }
     const uint32_t* const reject = &ctrl->oversize;   // followed by bad_input
     if (direct) {
-        cap = std::min<uint64_t>(P.c, 4) * n;
-        roomy = !M->has_alloc && cap <= kRoomyCells;
-        if (roomy) slots = (Cell*)dev_alloc(16 * cap, st);
-        if (!slots) {
-            roomy = false;
-            cap = cells_guess(n, P.c);
-            slots = (Cell*)dev_alloc(16 * cap, st);
+        const uint64_t guess = cells_guess(n, P.c), room = std::min<uint64_t>(P.c, 4) * n;
+        cap = room;
+        if (!M->has_alloc && room <= kRoomyCells) slots = (Cell*)pool_take_room(16 * room, 16 * guess, st);
+        roomy = slots != nullptr;
+        if (!roomy) {
+            cap = guess;
+            slots = (Cell*)dev_alloc(16 * cap, st, kKept);
         }
         if (!slots) {
             release(false);
@@ -374,7 +375,7 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
                 // more cells than the guess: the same pass again into an exact allocation
                 drop_slots();
                 cap = S;
-                slots = (Cell*)dev_alloc(16 * cap, st);
+                slots = (Cell*)dev_alloc(16 * cap, st, kKept);
                 if (!slots) {
                     rc = FKS_ENOMEM;
                     break;
@@ -412,7 +413,7 @@ static int attempts_partitioned(fks_map* M, const uint64_t* d_keys_in, const uin
         if (host->oversize) continue;
         const uint64_t S = host->S;
         if (S > (uint64_t)P.c * n) continue;
-        Cell* cells = (Cell*)dev_alloc(16 * (S ? S : 1), st);
+        Cell* cells = (Cell*)dev_alloc(16 * (S ? S : 1), st, kKept);
         if (!cells) {
             rc = FKS_ENOMEM;
             break;
@@ -497,15 +498,15 @@ static int build_common(fks_map* M, const uint64_t* d_keys_in, const uint32_t* d
     if (!w.ctrl || (bytes && !w.y)) return fail(FKS_ENOMEM);
     w.host = (Readback*)pinned_words();
     if (!w.host) return fail(FKS_ENOMEM);
-    M->header = (Group*)dev_alloc(16 * G, st);
-    M->C = (Triple*)dev_alloc(sizeof(Triple) * P.T, st);
+    M->header = (Group*)dev_alloc(16 * G, st, kKept);
+    M->C = (Triple*)dev_alloc(sizeof(Triple) * P.T, st, kKept);
     if (!M->header || !M->C) return fail(FKS_ENOMEM);
     M->device_bytes = 16 * G + sizeof(Triple) * P.T;
 
     if (bytes) {
         // the map keeps its own copy of the context (Section 3.1)
-        M->ctx_off = (int64_t*)dev_alloc(8 * (n + 1), st);
-        M->ctx_bytes = (uint8_t*)dev_alloc(nbytes ? nbytes : 1, st);
+        M->ctx_off = (int64_t*)dev_alloc(8 * (n + 1), st, kKept);
+        M->ctx_bytes = (uint8_t*)dev_alloc(nbytes ? nbytes : 1, st, kKept);
         if (!M->ctx_off || !M->ctx_bytes) return fail(FKS_ENOMEM);
         M->ctx_nbytes = nbytes;
         M->device_bytes += 8 * (n + 1) + nbytes;
@@ -554,7 +555,7 @@ static int build_empty(fks_map* M, const fks_params& P, hipStream_t st) {
     Triple Ch[kTMax];
     M->A = level1_triple(M->seed, 0);
     M->beta = level1_beta(M->seed, 0);
-    M->C = (Triple*)dev_alloc(sizeof(Triple) * P.T, st);
+    M->C = (Triple*)dev_alloc(sizeof(Triple) * P.T, st, kKept);
     if (!M->C) return FKS_ENOMEM;
     for (uint32_t t = 0; t < P.T; ++t) Ch[t] = level2_triple(M->seed, 0, t);
     FKS_HIP(hipMemcpyAsync(M->C, Ch, sizeof(Triple) * P.T, hipMemcpyHostToDevice, st));
@@ -625,8 +626,8 @@ extern "C" int fks_build_bytes(const int64_t* d_offsets, const uint8_t* d_bytes,
         // keep a copy of the (empty) context too
         rc = build_empty(M, P, st);
         if (!rc) {
-            M->ctx_off = (int64_t*)dev_alloc(8, st);
-            M->ctx_bytes = (uint8_t*)dev_alloc(nbytes ? nbytes : 1, st);
+            M->ctx_off = (int64_t*)dev_alloc(8, st, kKept);
+            M->ctx_bytes = (uint8_t*)dev_alloc(nbytes ? nbytes : 1, st, kKept);
             if (!M->ctx_off || !M->ctx_bytes) rc = FKS_ENOMEM;
             else {
                 hipError_t e = hipMemcpyAsync(M->ctx_off, d_offsets, 8, hipMemcpyDeviceToDevice, st);

@@ -23,14 +23,14 @@ static thread_local const fks_allocator* tl_alloc = nullptr;
 AllocScope::AllocScope(const fks_allocator* a) : prev_(tl_alloc) { tl_alloc = a; }
 AllocScope::~AllocScope() { tl_alloc = prev_; }
 
-void* dev_alloc(size_t bytes, hipStream_t s) {
+void* dev_alloc(size_t bytes, hipStream_t s, PoolUse use) {
     if (bytes == 0) bytes = 16;
     if (tl_alloc) {
         void* p = tl_alloc->alloc((uint64_t)bytes, (void*)s, tl_alloc->user);
         if (!p) set_hip_error(hipErrorOutOfMemory);
         return p;
     }
-    return pool_take(bytes, s);
+    return pool_take(bytes, s, use);
 }
 
 // per-workgroup LDS histogram of the 4-bit bucket sizes, folded into 16 global counters
@@ -89,7 +89,7 @@ hipError_t words_to_host(void* pinned, const void* dev, size_t bytes, hipStream_
 void dev_free(void* p, hipStream_t s, bool settled) {
     if (!p) return;
     if (tl_alloc) tl_alloc->free(p, (void*)s, tl_alloc->user);
-    else pool_give(p, s, settled);
+    else pool_give(p, s, settled, kBrief);
 }
 
 }  // namespace fks

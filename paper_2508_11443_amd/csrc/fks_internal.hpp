@@ -273,10 +273,18 @@ int hip_fail(hipError_t e);
 // scope with the caller's allocator (or, to release an object, the allocator
 // the object was built with), so all of a call's memory comes from one place.
 // settled: the host has waited for the block's last use.
-void* dev_alloc(size_t bytes, hipStream_t s);
+enum PoolUse {
+    kBrief,   // scratch: comes back when the call is over
+    kKept,    // lives on in an object
+    kTry,     // scratch that a lookup can do without: nothing is waited for
+};
+void* dev_alloc(size_t bytes, hipStream_t s, PoolUse use = kBrief);
 void dev_free(void* p, hipStream_t s, bool settled = false);
-void* pool_take(size_t bytes, hipStream_t s);
-void pool_give(void* p, hipStream_t s, bool settled);
+void* pool_take(size_t bytes, hipStream_t s, PoolUse use);
+void pool_give(void* p, hipStream_t s, bool settled, PoolUse use);
+// A block that lives on, of `most` bytes, for a table that is likely to need `least` of them: the end
+// comes back by pool_trim.  Null: no memory for it, or such ends hold as much as they may already.
+void* pool_take_room(size_t most, size_t least, hipStream_t s);
 // the bytes of the pool's block from `bytes` on come back; nothing may be using them (false: not
 // a block of the pool)
 bool pool_trim(void* p, size_t bytes);

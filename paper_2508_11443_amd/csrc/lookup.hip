@@ -114,7 +114,7 @@ OrdScratch::OrdScratch(uint64_t m, uint32_t bins, bool ids, uint32_t val_bytes, 
     const size_t x = carve(8 * m), id = carve(ids ? 4 * m : 0), slot = carve(2 * m),
                  start = carve(2 * tiles * (bins + 2)), val = carve((size_t)val_bytes * m),
                  fnd = carve(found ? m : 0), own = carve(more);
-    base_ = pool_take(total, s);
+    base_ = pool_take(total, s, kTry);
     if (!base_) return;
     char* p = (char*)base_;
     a_.x = (uint64_t*)(p + x);
@@ -127,7 +127,7 @@ OrdScratch::OrdScratch(uint64_t m, uint32_t bins, bool ids, uint32_t val_bytes, 
 }
 
 OrdScratch::~OrdScratch() {
-    if (base_) pool_give(base_, st_, false);
+    if (base_) pool_give(base_, st_, false, kTry);
 }
 
 // Needles in their own order against ordered, 50 % hits: over 4 * 10^6 keys 52 and 58 us for 2^21

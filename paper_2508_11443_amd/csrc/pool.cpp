@@ -15,10 +15,19 @@
 // stream that needs a block of its size is made to wait for the event.  No kept stream handle
 // is used: a stream may be destroyed after the call.
 //
-// Bounds.  Free memory above an eighth of the device's is given back to the driver, whole
-// segments at a time (hipFree waits for the device, so nothing queued still uses them); when the
-// driver has none left every free segment is given back before an allocation fails.  Small
-// blocks have segments of their own, so that a small map does not pin a large segment.
+// Segments.  A block that lives on (a map's) has a segment to itself, so that its memory can go back
+// to the driver when it comes back; a free segment is taken for it only if it is at most an eighth
+// larger.  Scratch, which comes back when its call is over, is cut from any free memory.  Blocks of
+// up to kSmall bytes of either kind share segments of kSmallSegment.  A build that cannot know its
+// table's size yet takes room for a larger one (take_room) and gives back the end; such ends, which
+// only scratch can use while the table lives, hold at most a 64th of the device's memory, and beyond
+// that no room is to be had.  (When every table had room and later tables' blocks were cut from the ends
+// of earlier ones, 44 maps of 2^25 keys held 43 GB more than their tables, and none of it could go back.)
+//
+// Bounds.  Of free memory, at most an eighth of the device's is kept: whole free segments go back to
+// the driver, largest first, when a build or a release call leaves more than 7/64 of the device's memory
+// in them (hipFree waits for the device, so nothing queued still uses them), and all of them before an
+// allocation fails.  Lookups (kTry) neither wait for anything nor give anything to the driver.
 // One mutex per device; streams under capture take hipMallocAsync, which a graph can record.
 #include <hip/hip_runtime.h>
 
@@ -34,9 +43,10 @@ namespace fks {
 namespace {
 
 constexpr size_t kAlign = 512;
-constexpr size_t kSmall = 1 << 20;           // largest block of a small segment
-constexpr size_t kSmallSegment = 32 << 20;
-constexpr size_t kPage = 2 << 20;            // large segments are whole pages of this size
+constexpr size_t kSmall = 256 << 10;         // largest block of a small segment
+constexpr size_t kSmallSegment = 4 << 20;
+constexpr size_t kPage = 64 << 10, kLargePage = 2 << 20;   // segments are whole pages, large ones from kLarge on
+constexpr size_t kLarge = 64 << 20;
 constexpr int kMaxDevices = 64;
 
 // hipMalloc and hipFree are refused, and spoil the capture, while another thread captures a
@@ -49,34 +59,51 @@ struct RelaxedCapture {
 
 class Pool {
   public:
-    explicit Pool(int dev) : dev_(dev) {
+    Pool() {
         size_t free_now = 0, total = 0;
-        if (hipMemGetInfo(&free_now, &total) == hipSuccess) keep_ = total / 8;
+        if (hipMemGetInfo(&free_now, &total) == hipSuccess) eighth_ = total / 8;
     }
 
-    void* take(size_t bytes, hipStream_t s) {
-        bytes = (bytes + kAlign - 1) & ~(kAlign - 1);
-        std::lock_guard<std::mutex> lk(mu_);
+    void* take(size_t bytes, hipStream_t s, PoolUse use) {
+        bytes = round_up(bytes, kAlign);
+        std::unique_lock<std::mutex> lk(mu_);
         collect(false);
-        const bool small = bytes <= kSmall;
-        if (void* p = fit(bytes, small, s)) return p;
-        if (void* p = small ? nullptr : adopt(bytes, s)) return p;
-        const size_t seg = small ? kSmallSegment : (bytes + kPage - 1) & ~(kPage - 1);
-        if (!grow(seg, small)) {
-            // the driver has no more: wait for what is on its way back, then return every free segment
-            collect(true);
-            if (void* p = fit(bytes, small, s)) return p;
-            shrink(0);
-            if (!grow(seg, small)) return nullptr;
+        if (void* p = find(bytes, s, use)) return p;
+        if (grow(bytes)) return fit(bytes, s, use);
+        if (use == kTry) return nullptr;
+        // the driver has no more: wait for what is on its way back, then return every free segment
+        collect(true);
+        if (void* p = fit(bytes, s, use)) return p;
+        const std::vector<char*> freed = shrink(0);
+        lk.unlock();
+        to_driver(freed);
+        lk.lock();
+        return grow(bytes) ? fit(bytes, s, use) : nullptr;
+    }
+
+    // a block that lives on, of `most` bytes, of which about `least` will be used and the rest trimmed
+    void* take_room(size_t most, size_t least, hipStream_t s) {
+        most = round_up(most, kAlign);
+        const size_t spare = most <= kSmall ? 0 : most - std::min(most, least);
+        std::lock_guard<std::mutex> lk(mu_);
+        if (ends_ + spare > eighth_ / 8) return nullptr;
+        collect(false);
+        void* p = find(most, s, kKept);
+        if (!p && grow(most)) p = fit(most, s, kKept);
+        if (p) {
+            chunks_.find((char*)p)->second.end = spare;
+            ends_ += spare;
         }
-        return fit(bytes, small, s);
+        return p;
     }
 
     // false: the pointer is not one of this pool's
-    bool give(void* p, hipStream_t s, bool settled) {
-        std::lock_guard<std::mutex> lk(mu_);
+    bool give(void* p, hipStream_t s, bool settled, PoolUse use) {
+        std::unique_lock<std::mutex> lk(mu_);
         auto it = chunks_.find((char*)p);
         if (it == chunks_.end() || it->second.state != kUsed) return false;
+        ends_ -= it->second.end;
+        it->second.end = 0;
         if (settled) {
             release(it, kIdle);
         } else if (s == nullptr) {
@@ -98,43 +125,63 @@ class Pool {
                 release(it, kIdle);
             }
         }
-        if (free_bytes_ > keep_) shrink(keep_);
+        if (use != kTry && whole_bytes_ > eighth_ - eighth_ / 8) {
+            const std::vector<char*> freed = shrink(eighth_ - eighth_ / 8);
+            lk.unlock();
+            to_driver(freed);
+        }
         return true;
     }
 
     // the end of a block, from `bytes` on, is not needed and nothing uses it
     bool trim(void* p, size_t bytes) {
-        bytes = (bytes + kAlign - 1) & ~(kAlign - 1);
+        bytes = round_up(bytes, kAlign);
         std::lock_guard<std::mutex> lk(mu_);
         auto it = chunks_.find((char*)p);
         if (it == chunks_.end() || it->second.state != kUsed) return false;
-        if (it->second.size < bytes + kAlign) return true;
-        Chunk rest{it->second.size - bytes, kUsed, false, it->second.small};
+        const size_t end = it->second.size < bytes + kAlign ? 0 : it->second.size - bytes;
+        if (!it->second.small) {
+            ends_ += end - it->second.end;
+            it->second.end = end;
+        }
+        if (!end) return true;
         it->second.size = bytes;
+        Chunk rest{end, 0, kUsed, false, it->second.small};
         release(chunks_.emplace_hint(std::next(it), it->first + bytes, rest), kIdle);
         return true;
     }
 
   private:
     enum State { kUsed, kIdle, kNull, kPending };
+    enum Kind { kInSmall, kPart, kWhole };   // of free memory: of a small segment, part of a segment, all of it
     struct Chunk {
         size_t size;
+        size_t end;          // used blocks: what was or will be trimmed of it, in ends_
         State state;
         bool first, small;   // first: a segment starts here
     };
     using Chunks = std::map<char*, Chunk>;
     using Index = std::set<std::pair<size_t, char*>>;
+    using Found = std::pair<Index*, Index::iterator>;
 
-    Index& index(State st, bool small) { return free_[st == kNull ? 1 : 0][small ? 1 : 0]; }
+    static size_t round_up(size_t n, size_t to) { return (n + to - 1) & ~(to - 1); }
 
+    // all of a segment
+    bool whole(Chunks::iterator it) const {
+        auto next = std::next(it);
+        return it->second.first && (next == chunks_.end() || next->second.first);
+    }
+    Index& index(Chunks::iterator it) {
+        return free_[it->second.state == kNull][it->second.small ? kInSmall : whole(it) ? kWhole : kPart];
+    }
     void list(Chunks::iterator it, State st) {
         it->second.state = st;
-        index(st, it->second.small).insert({it->second.size, it->first});
-        free_bytes_ += it->second.size;
+        index(it).insert({it->second.size, it->first});
+        if (whole(it)) whole_bytes_ += it->second.size;
     }
     void unlist(Chunks::iterator it) {
-        index(it->second.state, it->second.small).erase({it->second.size, it->first});
-        free_bytes_ -= it->second.size;
+        index(it).erase({it->second.size, it->first});
+        if (whole(it)) whole_bytes_ -= it->second.size;
     }
     static bool is_free(const Chunk& c) { return c.state == kIdle || c.state == kNull; }
 
@@ -160,24 +207,42 @@ class Pool {
         list(it, st);
     }
 
-    void* fit(size_t bytes, bool small, hipStream_t s) {
-        auto a = index(kIdle, small).lower_bound({bytes, nullptr});
-        auto b = index(kNull, small).lower_bound({bytes, nullptr});
-        const bool has_a = a != index(kIdle, small).end(), has_b = b != index(kNull, small).end();
-        if (!has_a && !has_b) return nullptr;
+    // The smallest free memory for a block, of one order.  (Scratch from the ends of tables before whole
+    // segments: 10^7 keys' build, lookup and release 504 us instead of 497, as the lookup's then was not
+    // what the build had just used.)
+    Found best(size_t bytes, bool null_ordered, PoolUse use) {
+        Index* const kinds = free_[null_ordered];
+        auto in = [&](Kind k, size_t most) -> Found {
+            auto it = kinds[k].lower_bound({bytes, nullptr});
+            return it != kinds[k].end() && it->first <= most ? Found{&kinds[k], it} : Found{nullptr, {}};
+        };
+        if (bytes <= kSmall) return in(kInSmall, ~(size_t)0);
+        if (use == kKept) return in(kWhole, std::max(bytes + bytes / 8, segment(bytes)));
+        const Found a = in(kPart, ~(size_t)0), b = in(kWhole, ~(size_t)0);
+        return !a.first || (b.first && b.second->first < a.second->first) ? b : a;
+    }
+
+    void* fit(size_t bytes, hipStream_t s, PoolUse use) {
+        const Found a = best(bytes, false, use), b = best(bytes, true, use);
+        if (!a.first && !b.first) return nullptr;
         // a block that another stream has to wait for only when there is no other
-        const bool from_b = !has_a || (has_b && s == nullptr && b->first < a->first);
+        const bool from_b = !a.first || (b.first && s == nullptr && b.second->first < a.second->first);
         if (from_b && s != nullptr && !after_null(s)) return nullptr;
-        auto it = chunks_.find(from_b ? b->second : a->second);
+        auto it = chunks_.find(from_b ? b.second->second : a.second->second);
+        const State st = it->second.state;
         unlist(it);
-        if (it->second.size - bytes >= kAlign) {
-            Chunk rest{it->second.size - bytes, it->second.state, false, small};
-            it->second.size = bytes;
-            auto r = chunks_.emplace_hint(std::next(it), it->first + bytes, rest);
-            list(r, rest.state);
-        }
         it->second.state = kUsed;
+        if (it->second.size - bytes >= kAlign && (it->second.small || use != kKept)) {
+            Chunk rest{it->second.size - bytes, 0, kUsed, false, it->second.small};
+            it->second.size = bytes;
+            list(chunks_.emplace_hint(std::next(it), it->first + bytes, rest), st);
+        }
         return it->first;
+    }
+
+    void* find(size_t bytes, hipStream_t s, PoolUse use) {
+        if (void* p = fit(bytes, s, use)) return p;
+        return bytes <= kSmall ? nullptr : adopt(bytes, s, use);
     }
 
     // stream s waits for everything queued on the null stream so far
@@ -215,11 +280,12 @@ class Pool {
     // came back on a stream of the same handle (nothing is waited for unless the stream is a
     // new one), or any, once more waits on its way back than the pool keeps free.  So calls queued
     // one behind the other share a block, and calls on many streams cannot pile up memory.
-    void* adopt(size_t bytes, hipStream_t s) {
+    void* adopt(size_t bytes, hipStream_t s, PoolUse use) {
         for (size_t i = 0; i < pending_.size(); ++i) {
             auto it = chunks_.find(pending_[i].block);
-            if (it->second.small || it->second.size < bytes || it->second.size / 2 > bytes) continue;
-            if (pending_[i].stream != s && pending_bytes_ <= keep_) continue;
+            if (it->second.small || it->second.size < bytes) continue;
+            if (use == kKept ? !whole(it) || it->second.size > bytes + bytes / 8 : it->second.size / 2 > bytes) continue;
+            if (pending_[i].stream != s && pending_bytes_ <= eighth_) continue;
             if (hipStreamWaitEvent(s, pending_[i].done, 0) != hipSuccess) {
                 (void)hipGetLastError();
                 continue;
@@ -231,43 +297,52 @@ class Pool {
         return nullptr;
     }
 
-    bool grow(size_t seg, bool small) {
+    // bytes of a segment for such a block
+    static size_t segment(size_t bytes) {
+        return bytes <= kSmall ? kSmallSegment : round_up(bytes, bytes >= kLarge ? kLargePage : kPage);
+    }
+    bool grow(size_t bytes) {
         RelaxedCapture relaxed;
         void* p = nullptr;
-        const hipError_t e = hipMalloc(&p, seg);
-        if (e != hipSuccess) {
+        if (hipMalloc(&p, segment(bytes)) != hipSuccess) {
             (void)hipGetLastError();
             return false;
         }
-        list(chunks_.emplace((char*)p, Chunk{seg, kIdle, true, small}).first, kIdle);
+        list(chunks_.emplace((char*)p, Chunk{segment(bytes), 0, kUsed, true, bytes <= kSmall}).first, kIdle);
         return true;
     }
 
-    // gives back whole free segments, the largest first, until at most `keep` free bytes are left
-    void shrink(size_t keep) {
-        RelaxedCapture relaxed;
-        for (bool more = true; more && free_bytes_ > keep;) {
-            more = false;
-            auto best = chunks_.end();
-            for (auto it = chunks_.begin(); it != chunks_.end(); ++it) {
-                auto next = std::next(it);
-                const bool whole = it->second.first && (next == chunks_.end() || next->second.first);
-                if (whole && is_free(it->second) && (best == chunks_.end() || it->second.size > best->second.size))
-                    best = it;
-            }
-            if (best != chunks_.end() && hipFree(best->first) == hipSuccess) {
-                unlist(best);
-                chunks_.erase(best);
-                more = true;
-            }
+    // whole free segments, the largest first, until at most `keep` bytes of them are left; they are the
+    // caller's, to be given to the driver without the lock (hipFree waits)
+    std::vector<char*> shrink(size_t keep) {
+        std::vector<char*> out;
+        while (whole_bytes_ > keep) {
+            auto largest = chunks_.end();
+            for (Index(&kinds)[3] : free_)
+                for (int k : {kWhole, kInSmall}) {   // a free small segment is the largest of its kind
+                    if (kinds[k].empty()) continue;
+                    auto it = chunks_.find(kinds[k].rbegin()->second);
+                    if (whole(it) && (largest == chunks_.end() || it->second.size > largest->second.size)) largest = it;
+                }
+            if (largest == chunks_.end()) break;
+            out.push_back(largest->first);
+            unlist(largest);
+            chunks_.erase(largest);
         }
+        return out;
+    }
+    static void to_driver(const std::vector<char*>& segments) {
+        RelaxedCapture relaxed;
+        for (char* p : segments)
+            if (hipFree(p) != hipSuccess) (void)hipGetLastError();
     }
 
-    const int dev_;
     std::mutex mu_;
-    size_t keep_ = 4ull << 30, free_bytes_ = 0;
-    Chunks chunks_;                 // every block, by address
-    Index free_[2][2];              // free blocks by size: [settled, null-ordered][large, small]
+    size_t eighth_ = 4ull << 30;   // of the device's memory
+    size_t whole_bytes_ = 0;       // of free segments
+    size_t ends_ = 0;              // trimmed, or to be trimmed, of blocks in use
+    Chunks chunks_;                // every block, by address
+    Index free_[2][3];             // free memory by size: [settled, null-ordered][Kind]
     struct Pending {
         char* block;
         hipEvent_t done;
@@ -283,20 +358,20 @@ Pool* g_pool[kMaxDevices];   // never destroyed: objects may outlive static dest
 Pool* pool_of(int dev, bool create) {
     if (dev < 0 || dev >= kMaxDevices) return nullptr;
     std::lock_guard<std::mutex> lk(g_mu);
-    if (!g_pool[dev] && create) g_pool[dev] = new Pool(dev);
+    if (!g_pool[dev] && create) g_pool[dev] = new Pool;
     return g_pool[dev];
 }
 
 }  // namespace
 
-void* pool_take(size_t bytes, hipStream_t s) {
+void* pool_take(size_t bytes, hipStream_t s, PoolUse use) {
     int dev = 0;
     (void)hipGetDevice(&dev);
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (s != nullptr && hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
     Pool* pool = cap == hipStreamCaptureStatusNone ? pool_of(dev, true) : nullptr;
-    void* p = pool ? pool->take(bytes, s) : nullptr;
-    if (p) return p;
+    void* p = pool ? pool->take(bytes, s, use) : nullptr;
+    if (p || use == kTry) return p;
     const hipError_t e = hipMallocAsync(&p, bytes, s);
     if (e != hipSuccess) {
         set_hip_error(e);
@@ -306,11 +381,20 @@ void* pool_take(size_t bytes, hipStream_t s) {
     return p;
 }
 
-void pool_give(void* p, hipStream_t s, bool settled) {
+void* pool_take_room(size_t most, size_t least, hipStream_t s) {
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (s != nullptr && hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
+    Pool* pool = cap == hipStreamCaptureStatusNone ? pool_of(dev, true) : nullptr;
+    return pool ? pool->take_room(most, least, s) : nullptr;
+}
+
+void pool_give(void* p, hipStream_t s, bool settled, PoolUse use) {
     int dev = 0;
     (void)hipGetDevice(&dev);
     Pool* pool = pool_of(dev, false);
-    if (pool && pool->give(p, s, settled)) return;
+    if (pool && pool->give(p, s, settled, use)) return;
     (void)hipFreeAsync(p, s);
 }
 

@@ -523,9 +523,9 @@ static int build_sampled(fks_sorted* S, const uint64_t* d_keys, const uint32_t* 
     SortFlags* host = (SortFlags*)pinned_words();
     void* scratch = dev_alloc(sample_sort_scratch(n), st);
     SortFlags* flags = (SortFlags*)dev_alloc(sizeof(SortFlags), st);
-    S->keys = (uint64_t*)dev_alloc(8 * n, st);
-    S->vals = (uint32_t*)dev_alloc(4 * n, st);
-    S->index = (uint64_t*)dev_alloc(8 * S->sep.total, st);
+    S->keys = (uint64_t*)dev_alloc(8 * n, st, kKept);
+    S->vals = (uint32_t*)dev_alloc(4 * n, st, kKept);
+    S->index = (uint64_t*)dev_alloc(8 * S->sep.total, st, kKept);
     int rc = host && scratch && flags && S->keys && S->vals && S->index ? FKS_OK : kSortAgain;
     bool settled = false;
     if (rc == FKS_OK) {
@@ -555,8 +555,8 @@ static int build_radix(fks_sorted* S, const uint64_t* d_keys, const uint32_t* d_
     const uint32_t layout = S->layout;
     const uint32_t W = (uint32_t)std::min<uint64_t>(4096, std::max<uint64_t>(1, n / (4 * (uint64_t)kRTile)));
     const uint64_t N = 256ull * W;
-    uint64_t* kb[2] = {(uint64_t*)dev_alloc(8 * n, st), (uint64_t*)dev_alloc(8 * n, st)};
-    uint32_t* vb[2] = {(uint32_t*)dev_alloc(4 * n, st), (uint32_t*)dev_alloc(4 * n, st)};
+    uint64_t* kb[2] = {(uint64_t*)dev_alloc(8 * n, st, kKept), (uint64_t*)dev_alloc(8 * n, st, kKept)};   // a pair is kept
+    uint32_t* vb[2] = {(uint32_t*)dev_alloc(4 * n, st, kKept), (uint32_t*)dev_alloc(4 * n, st, kKept)};
     uint32_t* cnt = (uint32_t*)dev_alloc(4 * N, st);
     uint32_t* off = (uint32_t*)dev_alloc(4 * N, st);
     uint32_t* tsum = (uint32_t*)dev_alloc(4 * exscan_tiles(N), st);
@@ -621,7 +621,7 @@ static int build_radix(fks_sorted* S, const uint64_t* d_keys, const uint32_t* d_
         cleanup(false);
         return rc;
     }
-    S->index = (uint64_t*)dev_alloc(8 * S->sep.total, st);
+    S->index = (uint64_t*)dev_alloc(8 * S->sep.total, st, kKept);
     if (!S->index) {
         cleanup(false);
         return FKS_ENOMEM;

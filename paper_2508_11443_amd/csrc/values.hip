@@ -254,12 +254,12 @@ extern "C" int fks_map_values(const fks_map* map, uint32_t op, uint64_t a, uint6
     M->ctx_off = nullptr;
     M->ctx_bytes = nullptr;
     bool ok = true;
-    if (G) ok = ok && (M->header = (Group*)dev_alloc(16 * G, st));
-    if (map->S) ok = ok && (M->slots = (Cell*)dev_alloc(16 * map->S, st));
-    ok = ok && (M->C = (Triple*)dev_alloc(sizeof(Triple) * map->T, st));
+    if (G) ok = ok && (M->header = (Group*)dev_alloc(16 * G, st, kKept));
+    if (map->S) ok = ok && (M->slots = (Cell*)dev_alloc(16 * map->S, st, kKept));
+    ok = ok && (M->C = (Triple*)dev_alloc(sizeof(Triple) * map->T, st, kKept));
     if (ctx) {
-        ok = ok && (M->ctx_off = (int64_t*)dev_alloc(8 * (map->n + 1), st));
-        ok = ok && (M->ctx_bytes = (uint8_t*)dev_alloc(map->ctx_nbytes ? map->ctx_nbytes : 1, st));
+        ok = ok && (M->ctx_off = (int64_t*)dev_alloc(8 * (map->n + 1), st, kKept));
+        ok = ok && (M->ctx_bytes = (uint8_t*)dev_alloc(map->ctx_nbytes ? map->ctx_nbytes : 1, st, kKept));
     }
     uint32_t* flag = ok ? (uint32_t*)dev_alloc(64, st) : nullptr;
     if (!ok || !flag) {

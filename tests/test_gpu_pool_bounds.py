@@ -1,0 +1,97 @@
+"""GPU test of what the library's own memory holds beside its maps: little more than their tables
+while many maps of one size live, as many go and others stay, and where maps of many sizes come
+and go; and lookups that take their scratch while the stream is busy do not wait for it."""
+import time
+
+import numpy as np
+import pytest
+
+from paper_2508_11443_amd import fks, workloads
+from tests.gpu_util import announce
+
+pytestmark = pytest.mark.gpu
+
+
+def _free():
+    import torch
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    return torch.cuda.mem_get_info()
+
+
+def _build(n, seed):
+    import torch
+    keys = workloads.mix_keys_torch(torch.arange(seed << 40, (seed << 40) + n, device="cuda"))
+    return fks.fks_build_u64(keys, torch.arange(n, dtype=torch.int32, device="cuda"), seed)
+
+
+def _held(maps):
+    return sum(m.info()["device_bytes"] for m in maps)
+
+
+def test_many_resident_maps():
+    n, count, slack = 1 << 25, 44, 1 << 30
+    announce(f"gpu pool bounds: {count} maps of {n} keys")
+    before, total = _free()
+    maps = [_build(n, k) for k in range(count)]
+    assert before - _free()[0] - _held(maps) <= total // 8 + slack
+    # a map's table is counted without the end that was given back
+    assert _held(maps) <= count * n * 38
+    for m in maps[::2]:
+        m.destroy()
+    kept = maps[1::2]
+    assert before - _free()[0] - _held(kept) <= total // 8 + slack
+    for m in kept:
+        m.destroy()
+    assert before - _free()[0] <= total // 8 + slack
+
+
+def test_maps_of_many_sizes():
+    """What is held beside the live maps stays within the bound, and the answers are right."""
+    import torch
+    announce("gpu pool bounds: maps of many sizes")
+    rng = np.random.default_rng(5)
+    before, total = _free()
+    maps = []
+    for k in range(200):
+        n = int(2 ** rng.uniform(8, 24))
+        maps.append((_build(n, k), n, k))
+        while len(maps) > 24:
+            maps.pop(int(rng.integers(len(maps))))[0].destroy()
+    assert before - _free()[0] - _held([m for m, _, _ in maps]) <= total // 8 + (1 << 30)
+    for m, n, k in maps:
+        keys = workloads.mix_keys_torch(torch.arange(k << 40, (k << 40) + n, device="cuda"))
+        v = torch.empty(n, dtype=torch.int32, device="cuda")
+        f = torch.empty(n, dtype=torch.uint8, device="cuda")
+        fks.fks_lookup_u64(m, keys, v, f)
+        assert bool(f.all()) and torch.equal(v, torch.arange(n, dtype=torch.int32, device="cuda"))
+        m.destroy()
+
+
+@pytest.mark.parametrize("own_stream", [False, True])
+def test_lookups_do_not_wait_for_a_busy_stream(own_stream):
+    import torch
+    n, m = 1 << 22, 1 << 24
+    announce(f"gpu pool bounds: lookups behind long work, own stream {own_stream}")
+    mp = _build(n, 1)
+    q = workloads.mix_keys_torch((1 << 40) + torch.randint(0, n, (m,), device="cuda"))
+    outs = [(torch.empty(m, dtype=torch.int32, device="cuda"), torch.empty(m, dtype=torch.uint8, device="cuda"))
+            for _ in range(6)]
+    a = torch.randn(8192, 8192, device="cuda")
+    stream = torch.cuda.Stream() if own_stream else torch.cuda.current_stream()
+    with torch.cuda.stream(stream):
+        (a @ a).sum()
+        torch.cuda.synchronize()
+        began = time.perf_counter()
+        for _ in range(40):
+            a = a @ a * 1e-4
+        queued = time.perf_counter()
+        for v, f in outs:
+            fks.fks_lookup_u64(mp, q, v, f, stream=stream)
+        asked = time.perf_counter() - queued
+        torch.cuda.synchronize()
+        whole = time.perf_counter() - began
+    for v, f in outs:
+        assert bool(f.all())
+    assert asked < whole / 2, (asked, whole)
+    mp.destroy()
