@@ -49,8 +49,9 @@ constexpr size_t kPage = 64 << 10, kLargePage = 2 << 20;   // segments are whole
 constexpr size_t kLarge = 64 << 20;
 constexpr int kMaxDevices = 64;
 
-// hipMalloc and hipFree are refused, and spoil the capture, while another thread captures a
-// graph in the default (global) mode; they do not touch its streams
+// While another thread captures a graph in the default (global) mode, hipMalloc, hipFree and calls on
+// events (hipEventQuery, which every call here may make) are refused, and spoil the capture; none
+// of them touches its streams.  Held by whatever calls a pool.
 struct RelaxedCapture {
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
     RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
@@ -302,7 +303,6 @@ class Pool {
         return bytes <= kSmall ? kSmallSegment : round_up(bytes, bytes >= kLarge ? kLargePage : kPage);
     }
     bool grow(size_t bytes) {
-        RelaxedCapture relaxed;
         void* p = nullptr;
         if (hipMalloc(&p, segment(bytes)) != hipSuccess) {
             (void)hipGetLastError();
@@ -332,7 +332,6 @@ class Pool {
         return out;
     }
     static void to_driver(const std::vector<char*>& segments) {
-        RelaxedCapture relaxed;
         for (char* p : segments)
             if (hipFree(p) != hipSuccess) (void)hipGetLastError();
     }
@@ -365,6 +364,7 @@ Pool* pool_of(int dev, bool create) {
 }  // namespace
 
 void* pool_take(size_t bytes, hipStream_t s, PoolUse use) {
+    RelaxedCapture relaxed;
     int dev = 0;
     (void)hipGetDevice(&dev);
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -382,6 +382,7 @@ void* pool_take(size_t bytes, hipStream_t s, PoolUse use) {
 }
 
 void* pool_take_room(size_t most, size_t least, hipStream_t s) {
+    RelaxedCapture relaxed;
     int dev = 0;
     (void)hipGetDevice(&dev);
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -391,6 +392,7 @@ void* pool_take_room(size_t most, size_t least, hipStream_t s) {
 }
 
 void pool_give(void* p, hipStream_t s, bool settled, PoolUse use) {
+    RelaxedCapture relaxed;
     int dev = 0;
     (void)hipGetDevice(&dev);
     Pool* pool = pool_of(dev, false);
