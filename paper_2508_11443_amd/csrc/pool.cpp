@@ -361,16 +361,34 @@ Pool* pool_of(int dev, bool create) {
     return g_pool[dev];
 }
 
-}  // namespace
+// The lists above take host memory, and callers are C entry points: what they throw ends here, and
+// counts as no memory (a block that could not be listed stays unused).
+template <typename Call, typename Result>
+Result guarded(Call call, Result otherwise) {
+    try {
+        return call();
+    } catch (...) {
+        return otherwise;
+    }
+}
 
-void* pool_take(size_t bytes, hipStream_t s, PoolUse use) {
-    RelaxedCapture relaxed;
+// the current device's pool, for work on stream s; null while s is captured
+Pool* pool_for(hipStream_t s) {
     int dev = 0;
     (void)hipGetDevice(&dev);
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (s != nullptr && hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
-    Pool* pool = cap == hipStreamCaptureStatusNone ? pool_of(dev, true) : nullptr;
-    void* p = pool ? pool->take(bytes, s, use) : nullptr;
+    return cap == hipStreamCaptureStatusNone ? pool_of(dev, true) : nullptr;
+}
+
+}  // namespace
+
+void* pool_take(size_t bytes, hipStream_t s, PoolUse use) {
+    RelaxedCapture relaxed;
+    void* p = guarded([&]() -> void* {
+        Pool* pool = pool_for(s);
+        return pool ? pool->take(bytes, s, use) : nullptr;
+    }, (void*)nullptr);
     if (p || use == kTry) return p;
     const hipError_t e = hipMallocAsync(&p, bytes, s);
     if (e != hipSuccess) {
@@ -383,28 +401,30 @@ void* pool_take(size_t bytes, hipStream_t s, PoolUse use) {
 
 void* pool_take_room(size_t most, size_t least, hipStream_t s) {
     RelaxedCapture relaxed;
-    int dev = 0;
-    (void)hipGetDevice(&dev);
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (s != nullptr && hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
-    Pool* pool = cap == hipStreamCaptureStatusNone ? pool_of(dev, true) : nullptr;
-    return pool ? pool->take_room(most, least, s) : nullptr;
+    return guarded([&]() -> void* {
+        Pool* pool = pool_for(s);
+        return pool ? pool->take_room(most, least, s) : nullptr;
+    }, (void*)nullptr);
 }
 
 void pool_give(void* p, hipStream_t s, bool settled, PoolUse use) {
     RelaxedCapture relaxed;
     int dev = 0;
     (void)hipGetDevice(&dev);
-    Pool* pool = pool_of(dev, false);
-    if (pool && pool->give(p, s, settled, use)) return;
-    (void)hipFreeAsync(p, s);
+    const bool ours = guarded([&] {
+        Pool* pool = pool_of(dev, false);
+        return pool && pool->give(p, s, settled, use);
+    }, true);
+    if (!ours) (void)hipFreeAsync(p, s);
 }
 
 bool pool_trim(void* p, size_t bytes) {
     int dev = 0;
     (void)hipGetDevice(&dev);
-    Pool* pool = pool_of(dev, false);
-    return pool && bytes && pool->trim(p, bytes);
+    return guarded([&] {
+        Pool* pool = pool_of(dev, false);
+        return pool && bytes && pool->trim(p, bytes);
+    }, false);
 }
 
 }  // namespace fks
