@@ -1575,7 +1575,9 @@ static size_t wide_carve(uint32_t nseg, uint64_t parts, uint64_t tiles, char* ba
 
 uint32_t wide_tiles(uint32_t n) { return (n + kWideItems * kPScatterThreads - 1) / (kWideItems * kPScatterThreads); }
 
-uint64_t wide_parts_max() { return (1ull << 32) / part_region(kPartBuckets) - 1; }
+// runs are placed by 32 bits, which a cursor stays within also when all records of a map land past its
+// region's end
+uint64_t wide_parts_max() { return ((1ull << 32) - (uint64_t)kSegParts * kPartBuckets) / part_region(kPartBuckets) - 1; }
 
 size_t wide_scratch_bytes(uint32_t nseg, uint64_t parts, uint64_t tiles) {
     WideLists none{};
