@@ -5,8 +5,9 @@
 // partition; one workgroup per pair of partitions then collects its distinct keys in an LDS
 // table, where every occurrence lowers the slot's smallest input index with an atomic minimum
 // (a repeated key keeps the value of its first occurrence, in whatever order the threads
-// arrive), and appends each key's first occurrence to a dense list.  The list is handed to
-// from_array_nodup, whose table does not depend on the order of its input.
+// arrive), and appends each key's first occurrence to a dense list.  Should keys crowd some pair
+// under the hashes tried, one table in device memory, which has no such limit, collects them
+// instead.  The list is handed to from_array_nodup, whose table does not depend on the order of its input.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -22,14 +23,14 @@ constexpr uint32_t kDdThreads = 512;
 constexpr uint32_t kDdParts = 2;              // partitions per workgroup
 constexpr uint32_t kDdSlots = 4096;           // slots of a workgroup's table (about 2048 records without repeats)
 constexpr uint32_t kDdHeld = 6;               // records per thread held in registers (3072; two regions hold 2944)
-constexpr uint32_t kDdAttempts = 16;          // partition hashes tried before the build gives up
+constexpr uint32_t kDdAttempts = 2;           // partition hashes tried before the table in device memory
 
 // what the host reads back
 struct DdCtrl {
     uint32_t count;      // distinct keys
     uint32_t full;       // a workgroup's table had no room for its keys
     uint32_t overflow;   // a region of the cursor passes overflowed
-    uint32_t pad;
+    uint32_t side;       // the table in device memory: all ones less the smallest index of the key kEmpty, or 0
 };
 
 __global__ void k_dd_clear(DdCtrl* c) {
@@ -170,6 +171,79 @@ __global__ __launch_bounds__(kDdThreads) void k_dd_distinct(
     }
 }
 
+// The table in device memory: linear probing at a load of at most 1/2, a compare-and-swap per record.
+__global__ void k_dd_table(uint64_t* __restrict__ tkey, uint32_t* __restrict__ tidx, uint64_t cap) {
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < cap; i += (uint64_t)gridDim.x * blockDim.x) {
+        tkey[i] = kEmpty;
+        tidx[i] = 0xFFFFFFFFu;
+    }
+}
+__global__ void k_dd_insert(const uint64_t* __restrict__ keys, uint64_t u, uint64_t* __restrict__ tkey,
+                            uint32_t* __restrict__ tidx, uint64_t mask, DdCtrl* __restrict__ ctrl) {
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < u; i += (uint64_t)gridDim.x * blockDim.x) {
+        const uint64_t x = keys[i];
+        if (x == kEmpty) {
+            atomicMax(&ctrl->side, 0xFFFFFFFFu - (uint32_t)i);
+            continue;
+        }
+        uint64_t h = sm_fin(x) & mask;
+        for (uint64_t probe = 0; probe <= mask; ++probe) {   // half the slots stay free
+            const unsigned long long old = atomicCAS(reinterpret_cast<unsigned long long*>(tkey + h),
+                                                     (unsigned long long)kEmpty, (unsigned long long)x);
+            if (old == kEmpty || old == x) {
+                atomicMin(tidx + h, (uint32_t)i);
+                break;
+            }
+            h = (h + 1) & mask;
+        }
+    }
+}
+// the list of the table's keys, a wave's at a time; cap: a multiple of 64
+__global__ void k_dd_compact(const uint64_t* __restrict__ tkey, const uint32_t* __restrict__ tidx, uint64_t cap,
+                             const uint32_t* __restrict__ vals, uint64_t* __restrict__ out_keys,
+                             uint32_t* __restrict__ out_vals, DdCtrl* __restrict__ ctrl) {
+    const uint32_t lane = threadIdx.x & 63u;
+    auto put = [&](bool have, uint64_t x, uint32_t at) {
+        const uint64_t all = __ballot(have);
+        uint32_t base = 0;
+        if (lane == 0 && all) base = atomicAdd(&ctrl->count, (uint32_t)__popcll(all));
+        base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+        if (have) {
+            const uint32_t pos = base + (uint32_t)__popcll(all & ((1ull << lane) - 1));
+            out_keys[pos] = x;
+            out_vals[pos] = vals[at];
+        }
+    };
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < cap; i += (uint64_t)gridDim.x * blockDim.x)
+        put(tkey[i] != kEmpty, tkey[i], tidx[i]);
+    if (blockIdx.x == 0 && threadIdx.x < 64) put(lane == 0 && ctrl->side, kEmpty, 0xFFFFFFFFu - ctrl->side);
+}
+
+// The distinct keys by the table in device memory, and their number.
+static int dd_by_table(const uint64_t* d_keys, const uint32_t* d_vals, uint64_t u, uint64_t* dk, uint32_t* dv,
+                       DdCtrl* ctrl, DdCtrl* pinned, hipStream_t st) {
+    uint64_t cap = 64;
+    while (cap < 2 * u) cap <<= 1;
+    uint64_t* tkey = (uint64_t*)dev_alloc(8 * cap, st);
+    uint32_t* tidx = (uint32_t*)dev_alloc(4 * cap, st);
+    int rc = tkey && tidx ? FKS_OK : FKS_ENOMEM;
+    if (rc == FKS_OK) {
+        auto grid = [](uint64_t items) { return (unsigned)std::min<uint64_t>(65536, (items + 255) / 256); };
+        hipLaunchKernelGGL(k_dd_clear, 1, 64, 0, st, ctrl);
+        hipLaunchKernelGGL(k_dd_table, grid(cap), 256, 0, st, tkey, tidx, cap);
+        FKS_TIMED("fks_dedup_insert", st,
+                  hipLaunchKernelGGL(k_dd_insert, grid(u), 256, 0, st, d_keys, u, tkey, tidx, cap - 1, ctrl));
+        FKS_TIMED("fks_dedup_compact", st,
+                  hipLaunchKernelGGL(k_dd_compact, grid(cap), 256, 0, st, tkey, tidx, cap, d_vals, dk, dv, ctrl));
+        hipError_t e = hipGetLastError();
+        if (e == hipSuccess) e = words_to_host(pinned, ctrl, sizeof(DdCtrl), st);
+        if (e != hipSuccess) rc = hip_fail(e);
+    }
+    dev_free(tkey, st, rc == FKS_OK);
+    dev_free(tidx, st, rc == FKS_OK);
+    return rc;
+}
+
 }  // namespace fks
 
 using namespace fks;
@@ -210,7 +284,8 @@ extern "C" int fks_build_u64_from_array(const uint64_t* d_keys, const uint32_t* 
     a.fused = true;   // no size pass: only the partitions' records are wanted
     a.cursor = cursor;
     uint32_t n = 0;
-    int rc = FKS_EBUILD;
+    int rc = FKS_OK;
+    bool listed = false;
     for (uint32_t r = 0; r < kDdAttempts; ++r) {
         // partition and slot hashes of a stream of their own (~seed), fresh in every attempt
         a.A = level1_triple(~seed, r);
@@ -238,16 +313,15 @@ extern "C" int fks_build_u64_from_array(const uint64_t* d_keys, const uint32_t* 
             --r;
             continue;
         }
-        if (got.full) {
-            rc = FKS_EBUILD;   // more distinct keys than slots: another hash
-            continue;
-        }
+        if (got.full) continue;   // more distinct keys than slots: another hash
         n = got.count;
-        rc = FKS_OK;
+        listed = true;
         break;
     }
     dev_free(scratch, st, rc == FKS_OK);
     scratch = nullptr;
+    if (rc == FKS_OK && !listed && (rc = dd_by_table(d_keys, d_vals, u, dk, dv, ctrl, pinned, st)) == FKS_OK)
+        n = pinned->count;
     if (rc == FKS_OK) rc = fks_build_u64(dk, dv, n, seed, params, alloc, stream, out);
     cleanup(rc == FKS_OK);   // the build has waited for its own last kernel
     return rc;
