@@ -17,7 +17,9 @@
 // Lookup: a search through an index of separators (every 16th key in order, every
 // 256th and so on; Eytzinger: every 4th, every 64th), whose top level is staged in
 // LDS, a line of sixteen at a time by eight lanes together; the last step runs on
-// the keys themselves.
+// the keys themselves.  Many needles against few keys, which stay in the nearest
+// caches, have no lines to save: each lane searches alone (a branch-free binary
+// search, or the descent with the tree's top levels in LDS).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -228,6 +230,106 @@ __global__ void k_separators(const uint64_t* __restrict__ keys, SepIndex sep, ui
             x = keys[EYTZ ? node_at(p, sep.depth) - 1 : p];
         }
         index[e] = x;
+    }
+}
+
+constexpr uint32_t kQ = 4;   // needles per lane in lockstep
+constexpr uint32_t kTopLevels = 12;           // Eytzinger levels staged in LDS
+constexpr uint32_t kTopNodes = (1u << kTopLevels) - 1;
+
+// Whether each lane searches alone.  Kernel, alone and by lines: 2^22 needles over 16, 256 and 1024 keys
+// in order 27 and 56 us, 54 and 60, 68 and 62; 2^20 over 64 and 256 keys 12.9 and 16.0, 17.0 and 16.0; 2^18 over
+// 64 7.4 and 7.5.  In Eytzinger order 2^22 over 16, 4096, 16384 and 32768 keys 26 and 45, 44 and 53, 70 and 77,
+// 87 and 76; 2^20 9.5 and 12.4, 14.2 and 17.0, 20.6 and 21.6, 25.0 and 22.8; 2^18 over 4096 10.6 and 8.1.
+static bool search_alone(uint64_t n, uint64_t m, bool eytz) {
+    return m >= (eytz ? 1u << 20 : 1u << 19) && n <= (eytz ? 1u << 14 : 1u << 8);
+}
+
+template <bool WANT_VALS>
+__global__ __launch_bounds__(256) void k_bsearch(const uint64_t* __restrict__ sk, const uint32_t* __restrict__ sv,
+                                                   uint64_t n, const uint64_t* __restrict__ q, uint64_t m,
+                                                   uint32_t* __restrict__ out_vals, uint8_t* __restrict__ out_found,
+                                                   uint32_t missing) {
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x * kQ;
+    for (uint64_t j0 = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) * kQ; j0 < m; j0 += stride) {
+        uint64_t x[kQ], lo[kQ];
+#pragma unroll
+        for (uint32_t u = 0; u < kQ; ++u) {
+            x[u] = j0 + u < m ? q[j0 + u] : 0;
+            lo[u] = 0;
+        }
+        // the lower bound stays in [lo, lo + len]; len shrinks the same way for every needle
+        uint64_t len = n;
+        while (len > 1) {
+            const uint64_t half = len >> 1;
+#pragma unroll
+            for (uint32_t u = 0; u < kQ; ++u) lo[u] = sk[lo[u] + half] < x[u] ? lo[u] + half : lo[u];
+            len -= half;
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < kQ; ++u) {
+            if (j0 + u >= m) break;
+            // the lower bound is lo or lo + 1
+            uint64_t pos = lo[u];
+            bool hit = false;
+            if (n) {
+                const uint64_t kk = sk[pos];
+                if (kk < x[u]) {
+                    ++pos;
+                    hit = pos < n && sk[pos] == x[u];
+                } else {
+                    hit = kk == x[u];
+                }
+            }
+            out_found[j0 + u] = hit;
+            if (WANT_VALS) out_vals[j0 + u] = hit ? sv[pos] : missing;
+        }
+    }
+}
+
+template <bool WANT_VALS>
+__global__ __launch_bounds__(256) void k_eytz_search(const uint64_t* __restrict__ ek,
+                                                       const uint32_t* __restrict__ ev, uint64_t n,
+                                                       const uint64_t* __restrict__ q, uint64_t m,
+                                                       uint32_t* __restrict__ out_vals,
+                                                       uint8_t* __restrict__ out_found, uint32_t missing) {
+    __shared__ uint64_t top[kTopNodes];
+    const uint64_t ntop = min(n, (uint64_t)kTopNodes);
+    for (uint32_t i = threadIdx.x; i < ntop; i += blockDim.x) top[i] = ek[i];
+    __syncthreads();
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x * kQ;
+    for (uint64_t j0 = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) * kQ; j0 < m; j0 += stride) {
+        uint64_t x[kQ], i[kQ];
+#pragma unroll
+        for (uint32_t u = 0; u < kQ; ++u) {
+            x[u] = j0 + u < m ? q[j0 + u] : 0;
+            i[u] = 1;
+        }
+        // descend: a right turn appends a 1 to the node number, a left turn a 0
+        for (uint32_t lvl = 0; lvl < kTopLevels; ++lvl) {
+#pragma unroll
+            for (uint32_t u = 0; u < kQ; ++u)
+                if (i[u] <= ntop) i[u] = 2 * i[u] + (top[i[u] - 1] < x[u] ? 1 : 0);
+        }
+        bool more = true;
+        while (more) {
+            more = false;
+#pragma unroll
+            for (uint32_t u = 0; u < kQ; ++u)
+                if (i[u] <= n) {
+                    i[u] = 2 * i[u] + (ek[i[u] - 1] < x[u] ? 1 : 0);
+                    more = true;
+                }
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < kQ; ++u) {
+            if (j0 + u >= m) break;
+            // the lower bound is the node of the last left turn (0: none)
+            const uint64_t lb = i[u] >> (__ffsll((long long)~i[u]));
+            const bool hit = lb != 0 && ek[lb - 1] == x[u];
+            out_found[j0 + u] = hit;
+            if (WANT_VALS) out_vals[j0 + u] = hit ? ev[lb - 1] : missing;
+        }
     }
 }
 
@@ -685,6 +787,18 @@ extern "C" int fks_sorted_lookup_u64(const fks_sorted* S, const uint64_t* d_q, u
         return e == hipSuccess ? FKS_OK : hip_fail(e);
     }
     if (ordered_search(S, d_q, m, d_vals_out, d_found_out, missing_value, st)) {
+        const hipError_t e = hipGetLastError();
+        return e == hipSuccess ? FKS_OK : hip_fail(e);
+    }
+    if (search_alone(S->n, m, S->layout == 1)) {
+        auto alone = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, sgrid(m, 256 * kQ, 16384), 256, 0, st, S->keys, S->vals, S->n, d_q, m, d_vals_out,
+                               d_found_out, missing_value);
+        };
+        if (S->layout == 0)
+            FKS_TIMED("fks_bsearch_u64", st, d_vals_out ? alone(k_bsearch<true>) : alone(k_bsearch<false>));
+        else
+            FKS_TIMED("fks_eytzinger_u64", st, d_vals_out ? alone(k_eytz_search<true>) : alone(k_eytz_search<false>));
         const hipError_t e = hipGetLastError();
         return e == hipSuccess ? FKS_OK : hip_fail(e);
     }
