@@ -97,6 +97,7 @@ __global__ __launch_bounds__(kBlock) void k_fingerprint(const int64_t* __restric
 }
 
 constexpr uint32_t kStageBytes = 64 * 64 + 32;   // of a wave's 64 strings
+constexpr uint64_t kCopyMean = 1024;             // longest strings, on average, that the pass copies
 
 // The fingerprints, and the map's copy of the offsets and bytes (both 16-byte aligned) in the
 // same pass: a wave reads the bytes of its 64 strings, which lie one after the other, as aligned 16-byte
@@ -511,8 +512,10 @@ static int build_common(fks_map* M, const uint64_t* d_keys_in, const uint32_t* d
         M->ctx_nbytes = nbytes;
         M->device_bytes += 8 * (n + 1) + nbytes;
         // the offsets are checked by the fingerprint pass, before any byte is read through them; the
-        // first such pass copies both arrays where its 16-byte accesses are aligned
-        if (((uintptr_t)d_bytes | (uintptr_t)M->ctx_bytes) & 15) {
+        // first such pass copies both arrays where its 16-byte accesses are aligned and it has
+        // waves enough (one for 64 strings): 64 MB of strings of about 250 bytes 169 us with the copy in
+        // the pass and 173 with copies before it, of 1000 162 and 164, of 2000 225 and 201, of 8000 549 and 386
+        if ((((uintptr_t)d_bytes | (uintptr_t)M->ctx_bytes) & 15) || nbytes / n > kCopyMean) {
             hipError_t e = hipMemcpyAsync(M->ctx_off, d_off, 8 * (n + 1), hipMemcpyDeviceToDevice, st);
             if (e == hipSuccess && nbytes)
                 e = hipMemcpyAsync(M->ctx_bytes, d_bytes, nbytes, hipMemcpyDeviceToDevice, st);
