@@ -18,10 +18,11 @@
 // Segments.  A block that lives on (a map's) has a segment to itself, so that its memory can go back
 // to the driver when it comes back; a free segment is taken for it only if it is at most an eighth
 // larger.  Scratch, which comes back when its call is over, is cut from any free memory.  Blocks of
-// up to kSmall bytes of either kind share segments of kSmallSegment.  A build that cannot know its
-// table's size yet takes room for a larger one (take_room) and gives back the end; such ends, which
-// only scratch can use while the table lives, hold at most a 64th of the device's memory, and beyond
-// that no room is to be had.  (When every table had room and later tables' blocks were cut from the ends
+// up to kSmall bytes of either kind share segments of kSmallSegment (the driver's own allocations are
+// multiples of 2 MiB: 4000 maps of 20000 keys, 2.7 GB, held 8.4 GB with a segment for each table).  A
+// build that cannot know its table's size yet takes room for a larger one (take_room) and gives back the
+// end; such ends, which only scratch and small blocks can use while the table lives, hold at most
+// a 64th of the device's memory, and beyond that no room is to be had.  (When every table had room and later tables' blocks were cut from the ends
 // of earlier ones, 44 maps of 2^25 keys held 43 GB more than their tables, and none of it could go back.)
 //
 // Bounds.  Of free memory, at most an eighth of the device's is kept: whole free segments go back to
@@ -43,10 +44,9 @@ namespace fks {
 namespace {
 
 constexpr size_t kAlign = 512;
-constexpr size_t kSmall = 256 << 10;         // largest block of a small segment
-constexpr size_t kSmallSegment = 4 << 20;
-constexpr size_t kPage = 64 << 10, kLargePage = 2 << 20;   // segments are whole pages, large ones from kLarge on
-constexpr size_t kLarge = 64 << 20;
+constexpr size_t kSmall = 4 << 20;           // largest block of a small segment
+constexpr size_t kSmallSegment = 32 << 20;
+constexpr size_t kPage = 2 << 20;            // large segments are whole pages
 constexpr int kMaxDevices = 64;
 
 // While another thread captures a graph in the default (global) mode, hipMalloc, hipFree and calls on
@@ -85,7 +85,7 @@ class Pool {
     // a block that lives on, of `most` bytes, of which about `least` will be used and the rest trimmed
     void* take_room(size_t most, size_t least, hipStream_t s) {
         most = round_up(most, kAlign);
-        const size_t spare = most <= kSmall ? 0 : most - std::min(most, least);
+        const size_t spare = most - std::min(most, least);
         std::lock_guard<std::mutex> lk(mu_);
         if (ends_ + spare > eighth_ / 8) return nullptr;
         collect(false);
@@ -141,10 +141,8 @@ class Pool {
         auto it = chunks_.find((char*)p);
         if (it == chunks_.end() || it->second.state != kUsed) return false;
         const size_t end = it->second.size < bytes + kAlign ? 0 : it->second.size - bytes;
-        if (!it->second.small) {
-            ends_ += end - it->second.end;
-            it->second.end = end;
-        }
+        ends_ += end - it->second.end;
+        it->second.end = end;
         if (!end) return true;
         it->second.size = bytes;
         Chunk rest{end, 0, kUsed, false, it->second.small};
@@ -300,7 +298,7 @@ class Pool {
 
     // bytes of a segment for such a block
     static size_t segment(size_t bytes) {
-        return bytes <= kSmall ? kSmallSegment : round_up(bytes, bytes >= kLarge ? kLargePage : kPage);
+        return bytes <= kSmall ? kSmallSegment : round_up(bytes, kPage);
     }
     bool grow(size_t bytes) {
         void* p = nullptr;
