@@ -51,7 +51,7 @@ constexpr int kMaxDevices = 64;
 
 // While another thread captures a graph in the default (global) mode, hipMalloc, hipFree and calls on
 // events (hipEventQuery, which every call here may make) are refused, and spoil the capture; none
-// of them touches its streams.  Held by whatever calls a pool.
+// of them touches its streams.  Held wherever a pool makes such calls.
 struct RelaxedCapture {
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
     RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
@@ -61,6 +61,7 @@ struct RelaxedCapture {
 class Pool {
   public:
     Pool() {
+        RelaxedCapture relaxed;
         size_t free_now = 0, total = 0;
         if (hipMemGetInfo(&free_now, &total) == hipSuccess) eighth_ = total / 8;
     }
@@ -110,6 +111,7 @@ class Pool {
         } else if (s == nullptr) {
             release(it, kNull);
         } else {
+            RelaxedCapture relaxed;
             hipEvent_t ev = nullptr;
             if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) ev = nullptr;
             if (ev && hipEventRecord(ev, s) != hipSuccess) {
@@ -246,6 +248,7 @@ class Pool {
 
     // stream s waits for everything queued on the null stream so far
     static bool after_null(hipStream_t s) {
+        RelaxedCapture relaxed;
         hipEvent_t ev = nullptr;
         if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) return false;
         const bool ok = hipEventRecord(ev, nullptr) == hipSuccess && hipStreamWaitEvent(s, ev, 0) == hipSuccess;
@@ -256,6 +259,8 @@ class Pool {
 
     // blocks whose events are done become free
     void collect(bool wait) {
+        if (pending_.empty()) return;
+        RelaxedCapture relaxed;
         for (size_t i = 0; i < pending_.size();) {
             const hipError_t e = wait ? hipEventSynchronize(pending_[i].done) : hipEventQuery(pending_[i].done);
             if (e != hipSuccess) {
@@ -280,6 +285,8 @@ class Pool {
     // new one), or any, once more waits on its way back than the pool keeps free.  So calls queued
     // one behind the other share a block, and calls on many streams cannot pile up memory.
     void* adopt(size_t bytes, hipStream_t s, PoolUse use) {
+        if (pending_.empty()) return nullptr;
+        RelaxedCapture relaxed;
         for (size_t i = 0; i < pending_.size(); ++i) {
             auto it = chunks_.find(pending_[i].block);
             if (it->second.small || it->second.size < bytes) continue;
@@ -301,6 +308,7 @@ class Pool {
         return bytes <= kSmall ? kSmallSegment : round_up(bytes, kPage);
     }
     bool grow(size_t bytes) {
+        RelaxedCapture relaxed;
         void* p = nullptr;
         if (hipMalloc(&p, segment(bytes)) != hipSuccess) {
             (void)hipGetLastError();
@@ -330,6 +338,7 @@ class Pool {
         return out;
     }
     static void to_driver(const std::vector<char*>& segments) {
+        RelaxedCapture relaxed;
         for (char* p : segments)
             if (hipFree(p) != hipSuccess) (void)hipGetLastError();
     }
@@ -382,7 +391,6 @@ Pool* pool_for(hipStream_t s) {
 }  // namespace
 
 void* pool_take(size_t bytes, hipStream_t s, PoolUse use) {
-    RelaxedCapture relaxed;
     void* p = guarded([&]() -> void* {
         Pool* pool = pool_for(s);
         return pool ? pool->take(bytes, s, use) : nullptr;
@@ -398,7 +406,6 @@ void* pool_take(size_t bytes, hipStream_t s, PoolUse use) {
 }
 
 void* pool_take_room(size_t most, size_t least, hipStream_t s) {
-    RelaxedCapture relaxed;
     return guarded([&]() -> void* {
         Pool* pool = pool_for(s);
         return pool ? pool->take_room(most, least, s) : nullptr;
@@ -406,7 +413,6 @@ void* pool_take_room(size_t most, size_t least, hipStream_t s) {
 }
 
 void pool_give(void* p, hipStream_t s, bool settled, PoolUse use) {
-    RelaxedCapture relaxed;
     int dev = 0;
     (void)hipGetDevice(&dev);
     const bool ours = guarded([&] {
