@@ -109,6 +109,7 @@ class Pool {
         if (settled) {
             release(it, kIdle);
         } else if (s == nullptr) {
+            ++null_gives_;
             release(it, kNull);
         } else {
             RelaxedCapture relaxed;
@@ -246,13 +247,21 @@ class Pool {
         return bytes <= kSmall ? nullptr : adopt(bytes, s, use);
     }
 
-    // stream s waits for everything queued on the null stream so far
-    static bool after_null(hipStream_t s) {
+    // Stream s waits for everything that was queued on the null stream when its last block came back.  One
+    // event serves all blocks that came back until then (2^16 keys' build, lookup and release on a stream
+    // of the caller's 82 us, 126 with an event created and waited for by each block).
+    bool after_null(hipStream_t s) {
         RelaxedCapture relaxed;
-        hipEvent_t ev = nullptr;
-        if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) return false;
-        const bool ok = hipEventRecord(ev, nullptr) == hipSuccess && hipStreamWaitEvent(s, ev, 0) == hipSuccess;
-        (void)hipEventDestroy(ev);   // released once it is done
+        if (!fence_ && hipEventCreateWithFlags(&fence_, hipEventDisableTiming) != hipSuccess) fence_ = nullptr;
+        bool ok = fence_ != nullptr;
+        if (ok && fenced_ != null_gives_) {
+            ok = hipEventRecord(fence_, nullptr) == hipSuccess;
+            if (ok) fenced_ = null_gives_;
+        }
+        if (ok && hipEventQuery(fence_) != hipSuccess) {
+            (void)hipGetLastError();   // not done
+            ok = hipStreamWaitEvent(s, fence_, 0) == hipSuccess;
+        }
         if (!ok) (void)hipGetLastError();
         return ok;
     }
@@ -354,6 +363,8 @@ class Pool {
         hipEvent_t done;
         hipStream_t stream;   // compared, never used: it may have been destroyed
     };
+    hipEvent_t fence_ = nullptr;             // on the null stream, behind the first fenced_ blocks returned on it
+    uint64_t null_gives_ = 0, fenced_ = 0;
     std::vector<Pending> pending_;
     size_t pending_bytes_ = 0;
 };
