@@ -86,7 +86,7 @@ int has_equal_keys(const uint64_t* keys, uint64_t n, const int64_t* off, const u
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = hipMemcpyAsync(&h_found, found, 4, hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
-    dev_free(table, st);
+    dev_free(table, st, e == hipSuccess);
     if (e != hipSuccess) return hip_fail(e);
     *equal = h_found != 0;
     return FKS_OK;

@@ -248,8 +248,8 @@ int rounds_search(const uint64_t* keys, uint64_t n, uint64_t S, const Triple& A,
     w.npos = (uint32_t*)grab(4 * n);
     w.counts = (uint32_t*)grab(4 * (S ? S : 1));
     w.cell = (uint32_t*)grab(4 * n);
-    auto release = [&]() {
-        for (void* p : owned) dev_free(p, st);
+    auto release = [&](bool settled = false) {
+        for (void* p : owned) dev_free(p, st, settled);
     };
     for (void* p : owned)
         if (!p) {
@@ -305,7 +305,7 @@ int rounds_search(const uint64_t* keys, uint64_t n, uint64_t S, const Triple& A,
         cur = nxt;
     }
     *exhausted = K > 0;
-    release();
+    release(true);   // every round's totals were waited for
     e = hipGetLastError();
     return e == hipSuccess ? FKS_OK : hip_fail(e);
 }
