@@ -154,10 +154,10 @@ struct BucketPart {
     }
 };
 
-// Needles grouped by part, answered at their places.  Bound by the requests that reach L2 (a
-// group record and a cell for each needle, 5.1 ps of it per needle at L2's 270 G requests/s when all hit) and by the
-// lines that miss it (the table once).  10^7 needles over as many keys: 160 us, 80 of it without
-// the cells and 45 without any table access.  Workgroups of 1024 threads with two needles each in
+// Needles grouped by part, answered at their places.  Bound by the chain of a needle's two dependent
+// reads, which the lines that miss L2 (the table once) lengthen: 10^7 needles over as many keys
+// take 160 us, 80 of it without the cells and 45 without any table access, where their 1.4 to 2 requests each
+// would take 51 to 75 us at the 270 G requests/s of L2.  Workgroups of 1024 threads with two needles each in
 // flight keep few parts open at a time: with 256 threads and four needles 181 us; with 128 or
 // 512 parts instead of 256 10-20 us more.
 template <bool V64>

@@ -532,7 +532,7 @@ struct SquareMagics {
 };
 __constant__ const SquareMagics kSquareMagics{};
 
-template <bool AUX, uint32_t BT>
+template <bool AUX>
 struct FinalLds {
     uint64_t key[kFinalKeyCap];
     uint32_t val[kFinalKeyCap];
@@ -628,7 +628,7 @@ __device__ __forceinline__ uint32_t min_trial_small(TriAt tri, uint32_t T, uint3
 }
 
 // waves per SIMD the final pass is compiled for (registers within 80, or 96 with an aux
-// word): the LDS of six workgroups (26.5 KB each), or five with an aux word (31.5 KB),
+// word): the LDS of six workgroups (25.4 KB each), or five with an aux word (30.3 KB),
 // fits a CU
 template <bool AUX>
 constexpr unsigned kFinalWaves = AUX ? 5u : 6u;
@@ -657,7 +657,7 @@ __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(BT == kPB ? 
                                                   const uint32_t* __restrict__ reject = nullptr,
                                                   uint64_t cap = ~0ull, FuseArgs fa = FuseArgs{}) {
     static_assert(!MULTI || FUSED, "the maps of a batch are sized by the final pass");
-    __shared__ FinalLds<AUX, BT> L;
+    __shared__ FinalLds<AUX> L;
     const uint32_t tid = threadIdx.x;
     // few partitions: the last workgroup to end writes the attempt's outcome to the host (a launch
     // less; with many, one more atomic on one word for each would cost more)
