@@ -4,7 +4,7 @@ Uniform unique 64-bit keys with 32-bit values (the values are the key index),
 lowercase byte strings, batches of independent maps and serving request
 streams.  Only random numbers and set membership live here -- none of the
 hash map's own arithmetic -- so the same arrays can feed both the GPU library
-and the CPU checker.
+and the CPU oracle.
 """
 from __future__ import annotations
 
